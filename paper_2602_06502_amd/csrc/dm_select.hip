@@ -10,8 +10,8 @@
 // budget, least load is the equal-match rule for every request (both take
 // the fast path), and minimum TTFT compares the two estimates (serial path).
 //
-// Fast path (at most 256 live instances, uncached counts within 32 bits,
-// live loads within 2^62 of the smallest; checked on the device), on 32-bit
+// Fast path (uncached counts within 32 bits, live loads within 2^62 of the
+// smallest; checked on the device), on 32-bit
 // absolute loads when every load stays below 2^31, else on 64-bit loads
 // relative to the smallest:
 //   sel_prep_kernel   one thread per request packs a 16-byte record: the
@@ -37,7 +37,12 @@
 //                     its recorded pre-update loads, in parallel.
 // Slow path: the same rule, one request at a time, on 64-bit loads in
 // registers (at most 256 slots) or in LDS.
+//
+// The windowed path once stopped at 256 live instances (8-bit dense indices);
+// a batch on more took the slow path: 65,536 requests on 512 instances
+// 14.2 ms, 0.21 us each, against 0.66 ms in windows.
 #include <algorithm>
+#include <type_traits>
 
 #include "dm_internal.h"
 
@@ -264,7 +269,7 @@ constexpr uint32_t kRunMax = 3;
 
 // Per-request record of the packing kernel.
 struct SelPack {
-    uint32_t w;   // a | o << 8 (dense indices)
+    uint32_t w;   // a | o << 16 (dense indices)
     uint32_t ua;  // uncached tokens on a
     uint32_t uo;  // uncached tokens on o
     int32_t th;   // take a iff L_a <= max(th, L_o), relative loads
@@ -272,7 +277,8 @@ struct SelPack {
 
 // Per-lane record of one lane set of a window, in the form the window's
 // depth steps consume:
-// the LDS byte offsets (within the load array, 4-byte slots) of L_a and
+// the LDS byte offsets (within the walk's array of 4-byte slots: a spare
+// slot per lane, then the loads) of L_a and
 // L_o, where the request writes them (its spare slot unless it is the last
 // member of its run), rel = its depth in the window (0-based) + the
 // window's entry step e, and the window's control word e | (passes - 1) << 4.
@@ -318,7 +324,9 @@ __global__ __launch_bounds__(256) void sel_base_kernel(const int64_t* __restrict
         base[0] = smin[0];
 }
 
-constexpr uint32_t kFastMaxLive = 256;
+// Dense indices fit the level kernel's byte codes up to this many live
+// instances; past it, the kernel's wide form (two bytes each).
+constexpr uint32_t kByteLive = 256;
 constexpr int kPrefetch = 6;  // record windows in flight ahead of the walk
 // Lane sets of a window: every lane holds one request for the window's steps
 // of even number and one for its steps of odd number.
@@ -340,11 +348,9 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
     uint32_t qshift, int64_t slo, uint32_t policy, SelPack* __restrict__ rec,
     unsigned long long* __restrict__ grow)
 {
-    __shared__ unsigned long long sg[kFastMaxLive];
-    const bool track = n_live <= kFastMaxLive;
-    if (track)
-        for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
-            sg[k] = 0;
+    extern __shared__ unsigned long long sg[];  // [n_live]
+    for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
+        sg[k] = 0;
     __syncthreads();
     unsigned long long bad = 0;
     for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n;
@@ -370,14 +376,14 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
             th = (int32_t)(t < -1 ? -1 : (t > INT32_MAX ? INT32_MAX : t));
         }
         SelPack p;
-        p.w = aff2 ? ((d2 & 0xFF) | (d1 & 0xFF) << 8) : ((d1 & 0xFF) | (d2 & 0xFF) << 8);
+        p.w = aff2 ? d2 | d1 << 16 : d1 | d2 << 16;
         p.ua = (uint32_t)(aff2 ? u2 : u1);
         p.uo = (uint32_t)(aff2 ? u1 : u2);
         p.th = th;
         rec[r] = p;
         const bool ok = u1 >= 0 && u2 >= 0 && u1 <= INT32_MAX && u2 <= INT32_MAX;
         bad |= ok ? 0ull : 1ull;
-        if (track && ok) {
+        if (ok) {
             const unsigned long long g = (unsigned long long)(u1 > u2 ? u1 : u2);
             atomicAdd(&sg[d1], g);
             if (d2 != d1)
@@ -385,16 +391,14 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
         }
     }
     __syncthreads();
-    if (track)
-        for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
-            if (sg[k])
-                atomicAdd(&grow[k], sg[k]);
+    for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
+        if (sg[k])
+            atomicAdd(&grow[k], sg[k]);
     if (bad)
         atomicOr(&grow[kMaxSlots], 1ull);
 }
 
-// Windowed path iff at most 256 instances are live and every record's
-// uncached counts fit 32 bits (plan[1]).  Its loads are absolute 32-bit
+// Windowed path iff every record's uncached counts fit 32 bits (plan[1]).  Its loads are absolute 32-bit
 // values when every live load lies in [0, 2^30) and grows by less than 2^30
 // whatever the decisions; otherwise (plan[2]) 64-bit values relative to the
 // smallest live load, as long as they stay below it + 2^62.  Otherwise the
@@ -410,11 +414,11 @@ __global__ __launch_bounds__(256) void sel_plan_kernel(const int64_t* __restrict
     __shared__ int ok_all, narrow;
     if (threadIdx.x == 0) {
         // the minimum-TTFT rule has no windowed form: serial path
-        ok_all = n_live <= kFastMaxLive && grow[kMaxSlots] == 0 && policy != DM_POLICY_MIN_TTFT;
+        ok_all = grow[kMaxSlots] == 0 && policy != DM_POLICY_MIN_TTFT;
         narrow = 1;
     }
     __syncthreads();
-    for (uint32_t k = threadIdx.x; k < n_live && k < kFastMaxLive; k += blockDim.x) {
+    for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x) {
         // loads - base cannot wrap in unsigned arithmetic: base is the minimum
         const int64_t v = loads[live_ids[k]];
         const unsigned long long span = (unsigned long long)v - (unsigned long long)base[0];
@@ -500,16 +504,21 @@ static BlockShape block_shape(uint64_t n)
 //   - the levels are cut into parts (a lane per level), and the parts placed
 //     into windows by one uniform greedy pass over their sizes.
 // Every LDS access is by this one wave, so no barrier is needed.
-template <uint32_t LB>
+// LIVE: most live instances, kByteLive (pair codes of two bytes) or
+// kMaxSlots; the per-instance tables of the larger form take 40 KB more LDS
+// (two blocks a compute unit instead of four).
+template <uint32_t LB, uint32_t LIVE>
 __global__ __launch_bounds__(kWave) void sel_level_kernel(
     const SelPack* __restrict__ prep, uint64_t n, uint32_t* __restrict__ info,
     uint16_t* __restrict__ slotmap, uint8_t* __restrict__ wdepth, uint32_t* __restrict__ wcount,
     uint32_t* __restrict__ status)
 {
     constexpr uint32_t kWinCap = LevelShape<LB>::wincap;
-    __shared__ unsigned long long cm[kFastMaxLive];  // lanes of the chunk on each instance
-    __shared__ uint16_t last[kFastMaxLive];         // latest request of earlier chunks, + 1
-    __shared__ uint16_t W[LB];              // a | o << 8
+    constexpr uint32_t kBits = LIVE <= kByteLive ? 8 : 16, kMask = (1u << kBits) - 1;
+    using Code = std::conditional_t<kBits == 8, uint16_t, uint32_t>;
+    __shared__ unsigned long long cm[LIVE];  // lanes of the chunk on each instance
+    __shared__ uint16_t last[LIVE];          // latest request of earlier chunks, + 1
+    __shared__ Code W[LB];                   // a | o << kBits
     __shared__ int16_t P[LB];               // latest earlier request on a
     __shared__ uint8_t psn[LB];             // position in the run
     __shared__ uint16_t hd[LB];             // the run's first member
@@ -530,8 +539,10 @@ __global__ __launch_bounds__(kWave) void sel_level_kernel(
     const uint64_t r0 = (uint64_t)blockIdx.x * LB;
     const uint32_t nb = (uint32_t)std::min<uint64_t>(LB, n - r0);
     const unsigned long long below = (1ull << lane) - 1, above = ~below << 1;
-    for (uint32_t k = lane; k < kFastMaxLive; k += kWave)
+    for (uint32_t k = lane; k < LIVE; k += kWave) {
         last[k] = 0;
+        cm[k] = 0;
+    }
     for (uint32_t k = lane; k < LB + 2; k += kWave)
         cnt[k] = 0;
     for (uint32_t k = lane; k < kWinCap * kSets * kWave; k += kWave)
@@ -546,22 +557,22 @@ __global__ __launch_bounds__(kWave) void sel_level_kernel(
         }
 #pragma unroll
         for (uint32_t k = 0; k < LB / kWave; k++)
-            W[k * kWave + lane] = (uint16_t)(wv[k] & 0xFFFFu);
+            W[k * kWave + lane] = (Code)((wv[k] & kMask) | (wv[k] >> 16) << kBits);
     }
     uint32_t lmax = 0;
     for (uint32_t c0 = 0; c0 < nb; c0 += kWave) {
         const uint32_t t = c0 + lane;
         const bool valid = t < nb;
-        const uint32_t w = W[t], a = w & 0xFF, o = w >> 8;
+        const uint32_t w = W[t], a = w & kMask, o = w >> kBits;
         has1[t] = has2[t] = 0;
-        for (uint32_t k = lane; k < kFastMaxLive; k += kWave)
-            cm[k] = 0;
         if (valid) {
             atomicOr(&cm[a], 1ull << lane);
             if (o != a)
                 atomicOr(&cm[o], 1ull << lane);
         }
         const unsigned long long ma = valid ? cm[a] : 0, mo = valid ? cm[o] : 0;
+        if (valid)  // read by every lane of the wave above
+            cm[a] = cm[o] = 0;
         auto latest = [&](unsigned long long m, uint32_t x) -> int {
             m &= below;
             return m ? (int)(c0 + 63 - __clzll(m)) : (int)last[x] - 1;
@@ -820,7 +831,7 @@ __global__ __launch_bounds__(4 * kWave) void sel_fill_kernel(
     const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const uint64_t ws = gw / kSets;  // window of capacity
     const uint32_t set = (uint32_t)(gw % kSets);
-    const uint32_t sp = 4u * (kFastMaxLive + lane);
+    const uint32_t sp = 4u * lane;
     uint64_t win;
     uint32_t k = 0xFFFF, depth = 1;
     uint64_t blk = 0;
@@ -845,8 +856,8 @@ __global__ __launch_bounds__(4 * kWave) void sel_fill_kernel(
         const SelPack me = prep[r];
         const uint32_t f = info[r], pos = (f >> 6) & 3;
         const bool not_last = (f >> 8) & 1;
-        q.a4 = 4u * (me.w & 0xFF);
-        q.o4 = 4u * ((me.w >> 8) & 0xFF);
+        q.a4 = 4u * (kWave + (me.w & 0xFFFF));
+        q.o4 = 4u * (kWave + (me.w >> 16));
         q.wa = not_last ? sp : q.a4;
         q.wo = not_last ? sp : q.o4;
         q.rel = (f & 63) + e;
@@ -1012,14 +1023,16 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
 {
     constexpr bool wide = sizeof(T) == 8;
     const int lane = lane_id();
-    for (uint32_t d = lane; d < kFastMaxLive + kWave; d += kWave)
-        L[d] = d < n_live ? (T)(loads[live_ids[d]] - b0) : (T)0;
+    // a spare slot per lane, then the loads
+    L[lane] = (T)0;
+    for (uint32_t d = lane; d < n_live; d += kWave)
+        L[kWave + d] = (T)(loads[live_ids[d]] - b0);
     __syncthreads();
     const uint64_t nw = __builtin_amdgcn_readfirstlane(nwin[0]);
     // the records hold offsets within L in 4-byte slots; the LDS address of
     // L itself is a link-time constant (zero when it is the only array)
     const uint32_t lbase = lds_addr(reinterpret_cast<int32_t*>(L));
-    const uint32_t sp4 = lbase + 4u * (kFastMaxLive + lane);
+    const uint32_t sp4 = lbase + 4u * lane;
     int32_t LaA32 = 0, LoA32 = 0, LaB32 = 0, LoB32 = 0;
     // window w: set A's records cA, set B's cB (same control word)
     auto window = [&](WalkRec& cA, WalkRec& cB, uint64_t w) {
@@ -1040,7 +1053,7 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
             // other than the last, write their own spare slot.
             const uint32_t ctl = __builtin_amdgcn_readfirstlane(cA.ctl), e = ctl & 15u;
             const uint32_t depth = 16u * (((ctl >> 4) & 3u) + 1u) - e;
-            const uint32_t sp = kFastMaxLive + lane;
+            const uint32_t sp = lane;
             T La[kSets] = {0, 0}, Lo[kSets] = {0, 0};
             auto step = [&](const WalkRec& c, uint32_t l, T& la, T& lo) {
                 const T th = exact(c.th, c.ua), pth = exact(c.pth, c.pua);
@@ -1123,8 +1136,8 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
         }
     }
     __syncthreads();
-    for (uint32_t d = lane; d < n_live && d < kFastMaxLive; d += kWave)
-        loads[live_ids[d]] = b0 + (int64_t)L[d];
+    for (uint32_t d = lane; d < n_live; d += kWave)
+        loads[live_ids[d]] = b0 + (int64_t)L[kWave + d];
 }
 
 #undef DM_WALK_BLOCK
@@ -1148,7 +1161,7 @@ __global__ __launch_bounds__(kWave) void select_fast_kernel(
     asm volatile("" ::: "v255", "a255");
     if (!plan[1])
         return;
-    __shared__ int64_t L[kFastMaxLive + kWave];  // loads, then one spare slot per lane
+    __shared__ int64_t L[kWave + kMaxSlots];  // one spare slot per lane, then the loads
     const int64_t b0 = plan[2] ? base[0] : 0;  // 32-bit walks use absolute loads
     if (plan[2])
         walk_windows<int64_t>(rec, nwin, live_ids, n_live, loads, b0, lpre, tbase, per, qshift, slo,
@@ -1342,16 +1355,21 @@ hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uin
     const dm_config& k = c->cfg;
     // few workgroups: each adds its per-instance growth sums to the global
     // ones with one atomic per instance, and those atomics meet on a few lines
-    sel_prep_kernel<<<grid_for(n, 256, 512), 256, 0, st>>>(
+    sel_prep_kernel<<<grid_for(n, 256, 512), 256, NL * sizeof(unsigned long long), st>>>(
         offsets, n, block_shift(c), out->cand, out->match, c->d_dense, NL, k.ttft_base_us,
         k.ttft_per_token_us, c->shift_div, k.slo_us, c->policy, b.prep, b.grow);
     if (b.nblk > 0) {
-        if (b.shape.block == LevelShape<2048>::block)
-            sel_level_kernel<2048><<<(uint32_t)b.nblk, kWave, 0, st>>>(
-                b.prep, n, b.info, b.slotmap, b.wdepth, b.wcount, c->d_status);
+        auto level = [&](auto kernel) {
+            kernel<<<(uint32_t)b.nblk, kWave, 0, st>>>(b.prep, n, b.info, b.slotmap, b.wdepth,
+                                                       b.wcount, c->d_status);
+        };
+        const bool large = b.shape.block == LevelShape<2048>::block;
+        if (NL <= kByteLive)
+            large ? level(sel_level_kernel<2048, kByteLive>)
+                  : level(sel_level_kernel<1024, kByteLive>);
         else
-            sel_level_kernel<1024><<<(uint32_t)b.nblk, kWave, 0, st>>>(
-                b.prep, n, b.info, b.slotmap, b.wdepth, b.wcount, c->d_status);
+            large ? level(sel_level_kernel<2048, kMaxSlots>)
+                  : level(sel_level_kernel<1024, kMaxSlots>);
     }
     sel_scan_kernel<<<1, 1024, 0, st>>>(b.wcount, b.nblk, b.woff, b.total);
     sel_fill_kernel<<<(uint32_t)((fill_waves + 3) / 4), 4 * kWave, 0, st>>>(

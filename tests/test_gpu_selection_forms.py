@@ -1,0 +1,56 @@
+"""Selection forms chosen by size or rule, each against the oracle, element by
+element: dense indices past one byte (more than 256 live instances)."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import oracle.harness as oh
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_06502_amd as pk
+    pk.load_library()
+    oracle.build(force=False)
+    yield
+
+
+def _pair(wl, L0, policy="slo_aware"):
+    import paper_2602_06502_amd.harness as gh
+    print("[case]", wl.name, wl.route.n_inst, wl.n_req, policy, flush=True)
+    sys.stdout.flush()
+    eng, o = gh.engine_for(wl), oh.oracle_for(wl)
+    gh.prefill_from_prior(eng, wl)
+    oh.prefill_from_prior(o, wl)
+    eng.set_policy(policy)
+    assert o.set_policy(policy) == oracle.OK
+    tok, off = workloads.prompts(wl, wl.n_req, sub=0)
+    Ld = gh.to_dev(L0, eng.device)
+    g = eng.route(gh.to_dev(tok, eng.device), gh.to_dev(off, eng.device), Ld)
+    eng.sync()
+    r = o.route(tok, off, L0)
+    for k in ("key", "cand", "match", "chosen", "ttft", "flags", "key_len"):
+        assert np.array_equal(g[k].cpu().numpy()[:len(r[k])], r[k]), k
+    assert np.array_equal(Ld.cpu().numpy(), r["loads"])
+    return r
+
+
+@pytest.mark.parametrize("n_inst,n_req,wide", [(256, 1100, False), (257, 1100, False), (257, 1100, True),
+                                               (700, 5000, False), (4093, 2100, False), (4093, 2100, True)])
+def test_windows_on_many_instances(n_inst, n_req, wide):
+    """256 live instances keep the byte codes, more take the wide ones (up to
+    every slot of the id space); wide: loads past 2^30 (the 64-bit walk)."""
+    wl = workloads.small_random(211 + n_inst, n_inst, 2, 16, n_req, slo_us=6_000_000_000 if wide else 3_000)
+    L0 = workloads.initial_loads(wl, wl.route.max_slots)
+    if wide:
+        L0[::3] += 1 << 40
+    _pair(wl, L0)
