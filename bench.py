@@ -748,7 +748,7 @@ def main():
                              "request; with pipelining, select runs from the batch's "
                              "hash_match end to its selection end"},
         "pipelined": True,
-        "select_bound": {"kernel": "select_fast_kernel", "bound": "latency",
+        "select_bound": {"kernel": "select_walk_kernel", "bound": "latency",
                          "depth_steps": depth_steps, "windows": walk_windows,
                          "depth_steps_without_runs": depth_steps_no_runs,
                          "ns_per_step": ref_stage[2] * 1e6 / depth_steps,

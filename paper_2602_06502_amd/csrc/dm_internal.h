@@ -345,11 +345,14 @@ hipError_t lookup_group(dm_ctx* c, uint64_t n, const uint64_t* key, const uint64
                         const uint32_t* bad, uint32_t* cand, uint8_t* flags, GroupView* gv);
 
 // dm_select.hip: SLO-aware choice in request order; chosen, ttft_us and
-// flags bits 0-2 written, loads updated.  select_prepare packs the batch's
+// flags bits 0-2 written, loads updated.  select_growth gives the batch's
+// growth bounds ([kMaxSlots + 1] words), whose first n_live and last word the
+// caller clears before select_prepare; select_prepare packs the batch's
 // records (no loads needed); select_run takes the loads' base and plan, walks
 // the batch on ss and writes the outputs on os (after an event when os is
 // another stream).  par picks one of two work-array sets.  select_batch is
 // both on one stream.
+hipError_t select_growth(dm_ctx* c, uint64_t n, int par, unsigned long long** grow);
 hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uint64_t n,
                           const dm_route_out* out, int par);
 hipError_t select_run(dm_ctx* c, hipStream_t ss, hipStream_t os, hipEvent_t sel_done,

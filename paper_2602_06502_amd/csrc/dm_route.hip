@@ -26,13 +26,21 @@ namespace {
 
 constexpr int kKeySlot = kSlotKeys;  // block keys when the caller keeps none
 
-// Clears the batch's malformed-offsets word (a kernel rather than a memset,
-// so that a captured graph replays it like the rest of the batch).
-__global__ void route_zero_kernel(uint32_t* bad, unsigned long long* ext_count)
+// Clears the batch's malformed-offsets word, the tree's count and the
+// selection's growth bounds (a kernel rather than a memset, so that a
+// captured graph replays it like the rest of the batch).
+__global__ __launch_bounds__(256) void route_zero_kernel(uint32_t* bad,
+                                                         unsigned long long* ext_count,
+                                                         unsigned long long* grow, uint32_t n_live)
 {
-    *bad = 0;
-    if (ext_count)
-        *ext_count = 0;
+    for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
+        grow[k] = 0;
+    if (threadIdx.x == 0) {
+        grow[kMaxSlots] = 0;
+        *bad = 0;
+        if (ext_count)
+            *ext_count = 0;
+    }
 }
 
 }  // namespace
@@ -137,7 +145,10 @@ hipError_t route(dm_ctx* c, const int32_t* tokens, uint64_t n_tokens, const int6
         ext_list = reinterpret_cast<uint32_t*>(w + 256);
         kl_work = reinterpret_cast<uint64_t*>(w + 256 + list_bytes);
     }
-    route_zero_kernel<<<1, 1, 0, st>>>(bad, ext_count);
+    unsigned long long* grow = nullptr;
+    if ((e = select_growth(c, n, par, &grow)) != hipSuccess)
+        return e;
+    route_zero_kernel<<<1, 256, 0, st>>>(bad, ext_count, grow, c->n_live);
     if ((e = block_starts(c, offsets, n, n_tokens, bstart, bad)) != hipSuccess)
         return e;
     uint64_t* hkeys = out->block_keys;

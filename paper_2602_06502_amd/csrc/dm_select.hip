@@ -7,8 +7,8 @@
 // batch result is therefore defined by processing the requests one by one.
 // The single-criterion rules of the ablation study (Sec. 4.3) run on the same
 // machinery: cache affinity is the SLO-aware rule with an unbounded TTFT
-// budget, least load is the equal-match rule for every request (both take
-// the fast path), and minimum TTFT compares the two estimates (serial path).
+// budget, least load is the equal-match rule for every request, and minimum
+// TTFT has a bound of its own in the walk's steps (see DM_BOUND_TTFT).
 //
 // Fast path (uncached counts within 32 bits, live loads within 2^62 of the
 // smallest; checked on the device), on 32-bit
@@ -26,17 +26,17 @@
 //                     packing of whole levels into windows of two sets of
 //                     64 lanes (one set for the window's even depths, one
 //                     for its odd ones);
-//   sel_scan_kernel,  the windows' places, the walk records of every lane
-//   sel_fill_kernel   of both sets of every window and each request's slot;
-//   select_fast_kernel one wave walks the windows in order and, inside a
+//   sel_fill_kernel   the windows' places, the walk records of every lane
+//                     of both sets of every window and each request's slot;
+//   select_walk_kernel one wave picks the path and the load width, then walks
+//                     the windows in order and, inside a
 //                     window, the levels in order: requests of one level
 //                     share no instance, so they run together on loads kept
 //                     in LDS, and each sees exactly the loads that the
 //                     request-order walk would show it;
 //   sel_out_kernel    chosen instance, TTFT and flags of every request from
 //                     its recorded pre-update loads, in parallel.
-// Slow path: the same rule, one request at a time, on 64-bit loads in
-// registers (at most 256 slots) or in LDS.
+// Slow path: the same rule, one request at a time, on 64-bit loads in LDS.
 //
 // The windowed path once stopped at 256 live instances (8-bit dense indices);
 // a batch on more took the slow path: 65,536 requests on 512 instances
@@ -72,6 +72,25 @@ __device__ __forceinline__ bool pick_first(uint32_t kind, int64_t L1, int64_t L2
     return !(L2 < th || !(L1 < L2));
 }
 
+// One batch and its rule, as the walk and the epilogue read them.
+struct SelArgs {
+    const int64_t* offsets;
+    uint64_t n;
+    uint32_t bshift;
+    const uint32_t* cand;
+    const uint32_t* match;
+    uint8_t* flags;
+    uint32_t* chosen;
+    int64_t* ttft;
+    int64_t* loads;
+    const uint32_t* live_ids;
+    uint32_t n_live, S;
+    int64_t tbase, per;
+    uint32_t qshift;
+    int64_t slo;
+    uint32_t policy;
+};
+
 // Per-lane request record for the serial loop and the output epilogue.
 struct SelRec {
     uint32_t c1, c2, kind;
@@ -80,178 +99,101 @@ struct SelRec {
     int64_t u1, u2, th;
 };
 
-__device__ __forceinline__ SelRec load_rec(const int64_t* offsets, uint64_t n, uint64_t r, bool ok,
-                                           uint32_t bshift, const uint32_t* cand,
-                                           const uint32_t* match, int64_t base, int64_t per,
-                                           uint32_t qshift, int64_t slo, uint32_t policy)
+__device__ __forceinline__ SelRec load_rec(const SelArgs& g, uint64_t r, bool ok)
 {
     SelRec s;
-    s.c1 = ok ? cand[r] : 0;
-    s.c2 = ok ? cand[n + r] : 0;
-    const uint32_t m1 = ok ? match[r] : 0, m2 = ok ? match[n + r] : 0;
-    const int64_t len = ok ? offsets[r + 1] - offsets[r] : 0;
-    s.u1 = len - ((int64_t)m1 << bshift);
-    s.u2 = len - ((int64_t)m2 << bshift);
+    s.c1 = ok ? g.cand[r] : 0;
+    s.c2 = ok ? g.cand[g.n + r] : 0;
+    const uint32_t m1 = ok ? g.match[r] : 0, m2 = ok ? g.match[g.n + r] : 0;
+    const int64_t len = ok ? g.offsets[r + 1] - g.offsets[r] : 0;
+    s.u1 = len - ((int64_t)m1 << g.bshift);
+    s.u2 = len - ((int64_t)m2 << g.bshift);
     s.eq = m1 == m2;
     s.aff1 = m1 > m2;
     // T_a <= slo  <=>  floor(L_a / 2^q) <= slo - base - per*u_a  <=>  L_a < th
-    s.th = (slo - base - per * (s.aff1 ? s.u1 : s.u2) + 1) * ((int64_t)1 << qshift);
+    s.th = (g.slo - g.tbase - g.per * (s.aff1 ? s.u1 : s.u2) + 1) * ((int64_t)1 << g.qshift);
     s.kind = (s.eq ? 1u : 0u) | (s.aff1 ? 2u : 0u);
     s.a2 = !s.eq && !s.aff1;
-    if (policy == DM_POLICY_CACHE_AFFINITY) {
+    if (g.policy == DM_POLICY_CACHE_AFFINITY) {
         s.kind |= 8u;
-    } else if (policy == DM_POLICY_LEAST_LOADED) {
+    } else if (g.policy == DM_POLICY_LEAST_LOADED) {
         s.kind = 1u;
         s.a2 = false;
-    } else if (policy == DM_POLICY_MIN_TTFT) {
+    } else if (g.policy == DM_POLICY_MIN_TTFT) {
         s.kind = 4u;
-        s.th = per * (s.u2 - s.u1);
+        s.th = g.per * (s.u2 - s.u1);
         s.a2 = false;
     }
     return s;
 }
 
-__device__ __forceinline__ void store_out(const SelRec& s, uint64_t r, int64_t L1, int64_t L2,
-                                          uint8_t* flags, uint32_t* chosen, int64_t* ttft,
-                                          int64_t base, int64_t per, uint32_t qshift, int64_t slo)
+__device__ __forceinline__ void store_out(const SelArgs& g, const SelRec& s, uint64_t r,
+                                          int64_t L1, int64_t L2)
 {
-    const bool pick1 = pick_first(s.kind, L1, L2, s.th, qshift);
-    const int64_t t1 = base + per * s.u1 + (L1 >> qshift);
-    const int64_t t2 = base + per * s.u2 + (L2 >> qshift);
-    uint32_t f = flags[r];
-    if (t1 > slo && t2 > slo)
+    const bool pick1 = pick_first(s.kind, L1, L2, s.th, g.qshift);
+    const int64_t t1 = g.tbase + g.per * s.u1 + (L1 >> g.qshift);
+    const int64_t t2 = g.tbase + g.per * s.u2 + (L2 >> g.qshift);
+    uint32_t f = g.flags[r];
+    if (t1 > g.slo && t2 > g.slo)
         f |= 2;
     if (s.eq)
         f |= 4;
     else if (pick1 != s.aff1)
         f |= 1;
-    chosen[r] = pick1 ? s.c1 : s.c2;
-    ttft[r] = pick1 ? t1 : t2;
-    flags[r] = (uint8_t)f;
+    g.chosen[r] = pick1 ? s.c1 : s.c2;
+    g.ttft[r] = pick1 ? t1 : t2;
+    g.flags[r] = (uint8_t)f;
 }
 
-// Serial selection, loads in R register banks of one wave.
-template <int R>
-__global__ __launch_bounds__(kWave) void select_kernel(
-    const int64_t* __restrict__ offsets, uint64_t n, uint32_t bshift,
-    const uint32_t* __restrict__ cand, const uint32_t* __restrict__ match,
-    uint8_t* __restrict__ flags, uint32_t* __restrict__ chosen, int64_t* __restrict__ ttft,
-    int64_t* __restrict__ loads, uint32_t S, int64_t base, int64_t per, uint32_t qshift, int64_t slo,
-    uint32_t policy, const uint32_t* __restrict__ plan)
+// Serial selection by one wave: L holds every slot's load.  All lanes read
+// the pair of the request in turn (broadcast) and take its decision; lane 0
+// writes the chosen load.  Rules other than minimum TTFT read "take a iff
+// L_a <= max(bound, L_o)", a the cache-affine candidate (c1 for equal
+// matches and the least-load rule).
+template <bool TTFT>
+__device__ void select_serial(const SelArgs& g, int64_t* L)
 {
-    if (!plan[0])
-        return;
     const int lane = lane_id();
-    uint32_t Llo[R], Lhi[R];
-#pragma unroll
-    for (int k = 0; k < R; k++) {
-        const uint32_t i = 64 * k + lane;
-        const int64_t v = i < S ? loads[i] : 0;
-        Llo[k] = (uint32_t)v;
-        Lhi[k] = (uint32_t)((uint64_t)v >> 32);
-    }
-    auto get = [&](uint32_t c) -> int64_t {
-        const uint32_t bank = c >> 6, l = c & 63;
-        uint32_t lo = __builtin_amdgcn_readlane(Llo[0], l), hi = __builtin_amdgcn_readlane(Lhi[0], l);
-#pragma unroll
-        for (int k = 1; k < R; k++) {
-            const uint32_t lo_k = __builtin_amdgcn_readlane(Llo[k], l);
-            const uint32_t hi_k = __builtin_amdgcn_readlane(Lhi[k], l);
-            lo = bank == (uint32_t)k ? lo_k : lo;
-            hi = bank == (uint32_t)k ? hi_k : hi;
-        }
-        return (int64_t)(((uint64_t)hi << 32) | lo);
-    };
-    for (uint64_t r0 = 0; r0 < n; r0 += kWave) {
-        const uint64_t r = r0 + lane;
-        const bool ok = r < n;
-        const SelRec s = load_rec(offsets, n, r, ok, bshift, cand, match, base, per, qshift, slo,
-                                  policy);
-        int64_t myL1 = 0, myL2 = 0;
-        const int cnt = (int)(n - r0 < (uint64_t)kWave ? n - r0 : kWave);
-        for (int j = 0; j < cnt; j++) {
-            const uint32_t C1 = __builtin_amdgcn_readlane(s.c1, j);
-            const uint32_t C2 = __builtin_amdgcn_readlane(s.c2, j);
-            const uint32_t K = __builtin_amdgcn_readlane(s.kind, j);
-            const int64_t TH = (int64_t)readlane_u64((uint64_t)s.th, j);
-            const int64_t U1 = (int64_t)readlane_u64((uint64_t)s.u1, j);
-            const int64_t U2 = (int64_t)readlane_u64((uint64_t)s.u2, j);
-            const int64_t L1 = get(C1), L2 = get(C2);
-            const bool pick1 = pick_first(K, L1, L2, TH, qshift);
-            const uint32_t ch = pick1 ? C1 : C2;
-            const int64_t nv = (pick1 ? L1 : L2) + (pick1 ? U1 : U2);
-            const uint32_t bank = ch >> 6, l = ch & 63;
-            const bool mine = lane == (int)l;
-#pragma unroll
-            for (int k = 0; k < R; k++)
-                if (bank == (uint32_t)k) {
-                    Llo[k] = mine ? (uint32_t)nv : Llo[k];
-                    Lhi[k] = mine ? (uint32_t)((uint64_t)nv >> 32) : Lhi[k];
-                }
-            if (lane == j) {
-                myL1 = L1;
-                myL2 = L2;
-            }
-        }
-        if (ok)
-            store_out(s, r, myL1, myL2, flags, chosen, ttft, base, per, qshift, slo);
-    }
-#pragma unroll
-    for (int k = 0; k < R; k++) {
-        const uint32_t i = 64 * k + lane;
-        if (i < S)
-            loads[i] = (int64_t)(((uint64_t)Lhi[k] << 32) | Llo[k]);
-    }
-}
-
-// Same rule with loads in LDS, for slot spaces beyond the register banks.
-__global__ __launch_bounds__(kWave) void select_lds_kernel(
-    const int64_t* __restrict__ offsets, uint64_t n, uint32_t bshift,
-    const uint32_t* __restrict__ cand, const uint32_t* __restrict__ match,
-    uint8_t* __restrict__ flags, uint32_t* __restrict__ chosen, int64_t* __restrict__ ttft,
-    int64_t* __restrict__ loads, uint32_t S, int64_t base, int64_t per, uint32_t qshift, int64_t slo,
-    uint32_t policy, const uint32_t* __restrict__ plan)
-{
-    if (!plan[0])
-        return;
-    __shared__ int64_t L[kMaxSlots];
-    const int lane = lane_id();
-    for (uint32_t i = lane; i < S; i += kWave)
-        L[i] = loads[i];
+    for (uint32_t i = lane; i < g.S; i += kWave)
+        L[i] = g.loads[i];
     __syncthreads();
-    for (uint64_t r0 = 0; r0 < n; r0 += kWave) {
+    for (uint64_t r0 = 0; r0 < g.n; r0 += kWave) {
         const uint64_t r = r0 + lane;
-        const bool ok = r < n;
-        const SelRec s = load_rec(offsets, n, r, ok, bshift, cand, match, base, per, qshift, slo,
-                                  policy);
-        int64_t myL1 = 0, myL2 = 0;
-        const int cnt = (int)(n - r0 < (uint64_t)kWave ? n - r0 : kWave);
+        const bool ok = r < g.n;
+        const SelRec s = load_rec(g, r, ok);
+        const uint32_t pair = s.a2 ? s.c2 | s.c1 << 16 : s.c1 | s.c2 << 16;
+        const int64_t ua = s.a2 ? s.u2 : s.u1, uo = s.a2 ? s.u1 : s.u2;
+        int64_t bound = s.th;
+        if constexpr (!TTFT)
+            bound = (s.kind & 1) || s.th == INT64_MIN ? INT64_MIN
+                    : (s.kind & 8)                    ? INT64_MAX
+                                                      : s.th - 1;
+        int64_t myA = 0, myO = 0;
+        const int cnt = (int)(g.n - r0 < (uint64_t)kWave ? g.n - r0 : kWave);
         for (int j = 0; j < cnt; j++) {
-            const uint32_t C1 = __builtin_amdgcn_readlane(s.c1, j);
-            const uint32_t C2 = __builtin_amdgcn_readlane(s.c2, j);
-            const uint32_t K = __builtin_amdgcn_readlane(s.kind, j);
-            const int64_t TH = (int64_t)readlane_u64((uint64_t)s.th, j);
-            const int64_t U1 = (int64_t)readlane_u64((uint64_t)s.u1, j);
-            const int64_t U2 = (int64_t)readlane_u64((uint64_t)s.u2, j);
-            const int64_t L1 = L[C1], L2 = L[C2];
-            const bool pick1 = pick_first(K, L1, L2, TH, qshift);
-            const uint32_t ch = pick1 ? C1 : C2;
-            const int64_t nv = (pick1 ? L1 : L2) + (pick1 ? U1 : U2);
+            const uint32_t P = __builtin_amdgcn_readlane(pair, j), A = P & 0xFFFF, O = P >> 16;
+            const int64_t T = (int64_t)readlane_u64((uint64_t)bound, j);
+            const int64_t UA = (int64_t)readlane_u64((uint64_t)ua, j);
+            const int64_t UO = (int64_t)readlane_u64((uint64_t)uo, j);
+            const int64_t La = L[A], Lo = L[O];
+            const bool take = TTFT ? (La >> g.qshift) - (Lo >> g.qshift) <= T
+                                   : La <= (T > Lo ? T : Lo);
+            const int64_t nv = take ? La + UA : Lo + UO;
             __syncthreads();
             if (lane == 0)
-                L[ch] = nv;
+                L[take ? A : O] = nv;
             __syncthreads();
             if (lane == j) {
-                myL1 = L1;
-                myL2 = L2;
+                myA = La;
+                myO = Lo;
             }
         }
         if (ok)
-            store_out(s, r, myL1, myL2, flags, chosen, ttft, base, per, qshift, slo);
+            store_out(g, s, r, s.a2 ? myO : myA, s.a2 ? myA : myO);
     }
     __syncthreads();
-    for (uint32_t i = lane; i < S; i += kWave)
-        loads[i] = L[i];
+    for (uint32_t i = lane; i < g.S; i += kWave)
+        g.loads[i] = L[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -297,33 +239,6 @@ struct WalkRec {
 };
 constexpr uint32_t kInertRel = 0xFFFFFFFFu;
 
-// plan[0] = 1 for the serial path; plan[1] = 1 for the windowed path, whose
-// loads are 64-bit when plan[2] = 1.
-// base[0] = smallest live load; grow[d] bounds how much live instance d's
-// load can grow in this batch (the larger uncached count of every request
-// that has it as a candidate).
-__global__ __launch_bounds__(256) void sel_base_kernel(const int64_t* __restrict__ loads,
-                                                       const uint32_t* __restrict__ live_ids,
-                                                       uint32_t n_live, int64_t* __restrict__ base,
-                                                       unsigned long long* __restrict__ grow)
-{
-    __shared__ int64_t smin[256];
-    int64_t mn = INT64_MAX;
-    for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x) {
-        const int64_t v = loads[live_ids[k]];
-        mn = v < mn ? v : mn;
-    }
-    smin[threadIdx.x] = mn;
-    __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if (threadIdx.x < d)
-            smin[threadIdx.x] = std::min(smin[threadIdx.x], smin[threadIdx.x + d]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        base[0] = smin[0];
-}
-
 // Dense indices fit the level kernel's byte codes up to this many live
 // instances; past it, the kernel's wide form (two bytes each).
 constexpr uint32_t kByteLive = 256;
@@ -332,15 +247,10 @@ constexpr int kPrefetch = 6;  // record windows in flight ahead of the walk
 // of even number and one for its steps of odd number.
 constexpr uint32_t kSets = 2;
 
-// grow[0..n_live) and the bad-record word grow[kMaxSlots] start at zero.
-__global__ void sel_zero_kernel(unsigned long long* __restrict__ grow, uint32_t n_live)
-{
-    for (uint32_t k = threadIdx.x; k < n_live && k < kMaxSlots; k += blockDim.x)
-        grow[k] = 0;
-    if (threadIdx.x == 0)
-        grow[kMaxSlots] = 0;
-}
-
+// grow[d] bounds how much live instance d's load can grow in this batch (the
+// larger uncached count of every request that has it as a candidate);
+// grow[kMaxSlots] is set by a record whose counts do not fit 32 bits.  Both
+// start at zero.
 __global__ __launch_bounds__(256) void sel_prep_kernel(
     const int64_t* __restrict__ offsets, uint64_t n, uint32_t bshift,
     const uint32_t* __restrict__ cand, const uint32_t* __restrict__ match,
@@ -360,7 +270,8 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
         const int64_t u1 = len - ((int64_t)m1 << bshift), u2 = len - ((int64_t)m2 << bshift);
         // least load: every request as an equal match, c1 as "a"
         const bool eq = m1 == m2 || policy == DM_POLICY_LEAST_LOADED;
-        const bool aff2 = m2 > m1 && policy != DM_POLICY_LEAST_LOADED;
+        const bool aff2 = m2 > m1 && policy != DM_POLICY_LEAST_LOADED &&
+                          policy != DM_POLICY_MIN_TTFT;
         const uint32_t d1 = dense[cand[r]], d2 = dense[cand[n + r]];
         // T_a <= slo  <=>  floor(L_a / 2^q) <= slo - tbase - per*u_a  <=>
         // L_a < (slo - tbase - per*u_a + 1) 2^q, i.e. "take a iff L_a <=
@@ -368,8 +279,17 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
         // in [0, 2^31 - 1), so th is clamped to that range; equal matches:
         // take c1 iff L1 <= L2, th = -2^31; cache affinity: always a,
         // th = 2^31 - 1.
+        // Minimum TTFT, a = c1, D = 2^q: floor(L_a / D) - floor(L_o / D) <= d
+        // with d = per (u_o - u_a)  <=>  L_a <= (L_o | (D - 1)) + d D; th = d D
+        // clamped to 32 bits, which the walk adds saturating (loads are in
+        // [0, 2^31), so a saturated sum decides as the exact one).
         int32_t th = INT32_MIN;
-        if (!eq && policy == DM_POLICY_CACHE_AFFINITY) {
+        if (policy == DM_POLICY_MIN_TTFT) {
+            const int64_t d = per * (u2 - u1), lim = (int64_t)1 << 31;
+            const int64_t t = d >= lim ? lim : d <= -lim ? -lim : qshift < 31 ? d * (1ll << qshift)
+                              : d > 0  ? lim : d < 0 ? -lim : 0;
+            th = (int32_t)(t >= lim ? INT32_MAX : t <= -lim ? INT32_MIN : t);
+        } else if (!eq && policy == DM_POLICY_CACHE_AFFINITY) {
             th = INT32_MAX;
         } else if (!eq) {
             const int64_t t = (slo - tbase - per * (aff2 ? u2 : u1) + 1) * ((int64_t)1 << qshift) - 1;
@@ -396,43 +316,6 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
             atomicAdd(&grow[k], sg[k]);
     if (bad)
         atomicOr(&grow[kMaxSlots], 1ull);
-}
-
-// Windowed path iff every record's uncached counts fit 32 bits (plan[1]).  Its loads are absolute 32-bit
-// values when every live load lies in [0, 2^30) and grows by less than 2^30
-// whatever the decisions; otherwise (plan[2]) 64-bit values relative to the
-// smallest live load, as long as they stay below it + 2^62.  Otherwise the
-// serial path (plan[0]).
-__global__ __launch_bounds__(256) void sel_plan_kernel(const int64_t* __restrict__ loads,
-                                                       const uint32_t* __restrict__ live_ids,
-                                                       uint32_t n_live,
-                                                       const int64_t* __restrict__ base,
-                                                       const unsigned long long* __restrict__ grow,
-                                                       uint32_t policy,
-                                                       uint32_t* __restrict__ plan)
-{
-    __shared__ int ok_all, narrow;
-    if (threadIdx.x == 0) {
-        // the minimum-TTFT rule has no windowed form: serial path
-        ok_all = grow[kMaxSlots] == 0 && policy != DM_POLICY_MIN_TTFT;
-        narrow = 1;
-    }
-    __syncthreads();
-    for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x) {
-        // loads - base cannot wrap in unsigned arithmetic: base is the minimum
-        const int64_t v = loads[live_ids[k]];
-        const unsigned long long span = (unsigned long long)v - (unsigned long long)base[0];
-        if (v < 0 || v >= (1ll << 30) || grow[k] >= (1ull << 30))
-            atomicAnd(&narrow, 0);
-        if (span >= (1ull << 62) || grow[k] >= (1ull << 62))
-            atomicAnd(&ok_all, 0);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        plan[0] = ok_all ? 0 : 1;
-        plan[1] = ok_all ? 1 : 0;
-        plan[2] = ok_all && !narrow ? 1 : 0;
-    }
 }
 
 // Walk windows from dependency levels.  Requests are grouped in blocks of
@@ -778,7 +661,10 @@ __global__ __launch_bounds__(kWave) void sel_level_kernel(
 }
 
 // Exclusive scan of the blocks' window counts (one workgroup); total[0] =
-// all windows.
+// all windows.  Batches of more than kScanFrom blocks only: below, each wave
+// of the fill kernel sums the counts before its block itself (at most 16
+// loads a lane), which spares a launch of 4.7 us.
+constexpr uint64_t kScanFrom = 1024;
 __global__ __launch_bounds__(1024) void sel_scan_kernel(const uint32_t* __restrict__ wcount,
                                                         uint64_t nblk, uint32_t* __restrict__ woff,
                                                         uint32_t* __restrict__ total)
@@ -818,12 +704,13 @@ __global__ __launch_bounds__(1024) void sel_scan_kernel(const uint32_t* __restri
 // One wave per lane set of every (block, window) of capacity, then of
 // 2 * kPrefetch padding windows: the walk records of every lane (inert past
 // the set's requests) and each request's slot.  The records of window w's
-// set s start at (w * kSets + s) * 64.
+// set s start at (w * kSets + s) * 64.  woff: the blocks' first windows, or
+// null to sum wcount here and write total[0].
 __global__ __launch_bounds__(4 * kWave) void sel_fill_kernel(
     const SelPack* __restrict__ prep, uint64_t n, const uint32_t* __restrict__ info,
     const uint16_t* __restrict__ slotmap, const uint8_t* __restrict__ wdepth,
     const uint32_t* __restrict__ wcount, const uint32_t* __restrict__ woff,
-    const uint32_t* __restrict__ total, uint64_t nblk, BlockShape bs, WalkRec* __restrict__ rec,
+    uint32_t* __restrict__ total, uint64_t nblk, BlockShape bs, WalkRec* __restrict__ rec,
     uint32_t* __restrict__ slot_of)
 {
     const uint32_t wincap = bs.wincap, bsize = bs.block;
@@ -832,6 +719,16 @@ __global__ __launch_bounds__(4 * kWave) void sel_fill_kernel(
     const uint64_t ws = gw / kSets;  // window of capacity
     const uint32_t set = (uint32_t)(gw % kSets);
     const uint32_t sp = 4u * lane;
+    auto windows_before = [&](uint64_t b) -> uint32_t {
+        if (woff)
+            return b < nblk ? woff[b] : total[0];
+        uint32_t v = 0;
+        for (uint64_t i = lane; i < b; i += kWave)
+            v += wcount[i];
+        for (int d = 1; d < kWave; d <<= 1)
+            v += (uint32_t)__shfl_xor((int)v, d);
+        return v;
+    };
     uint64_t win;
     uint32_t k = 0xFFFF, depth = 1;
     uint64_t blk = 0;
@@ -840,11 +737,14 @@ __global__ __launch_bounds__(4 * kWave) void sel_fill_kernel(
         const uint32_t lw = (uint32_t)(ws % wincap);
         if (lw >= wcount[blk])
             return;
-        win = (uint64_t)woff[blk] + lw;
+        win = (uint64_t)windows_before(blk) + lw;
         k = slotmap[gw * kWave + lane];
         depth = wdepth[ws];
     } else if (ws < nblk * wincap + 2 * kPrefetch) {
-        win = (uint64_t)total[0] + (ws - nblk * wincap);
+        const uint32_t all = windows_before(nblk);
+        if (!woff && gw == nblk * wincap * kSets && lane == 0)
+            total[0] = all;
+        win = (uint64_t)all + (ws - nblk * wincap);
     } else {
         return;
     }
@@ -923,7 +823,16 @@ __device__ __forceinline__ uint32_t lds_addr(T* p)
 // this step's reads only.  Every step has the same instructions with
 // fixed-size encodings (operands are registers and inline constants), which
 // the computed entry relies on; the assembler checks the sizes.
-#define DM_STEP_TEXT(K, XA, XO, X, M, XAP, XOP, MP, S, P)                                      \
+// BND(T, TH, XO) computes into T the bound that L_a is compared with: the larger
+// of the threshold and L_o, or for the minimum-TTFT rule L_o with its low q
+// bits set plus the threshold, saturating (one more instruction a decision;
+// 16,384 requests on 32 instances route in 0.45 ms against 2.98 ms one at a
+// time on the serial path, which this rule took before).
+#define DM_BOUND_SLO(T, TH, XO) "v_max_i32_e32 " T ", %[" TH "], " XO "\n\t"
+#define DM_BOUND_TTFT(T, TH, XO)                                                               \
+    "v_or_b32_e32 " T ", %[low], " XO "\n\t"                                                   \
+    "v_add_i32 " T ", " T ", %[" TH "] clamp\n\t"
+#define DM_STEP_TEXT(BND, K, XA, XO, X, M, XAP, XOP, MP, S, P)                                      \
     ".Ldmw%=_" #K ":\n\t"                                                                      \
     "ds_read_b32 " XO ", %[o4" S "]\n\t"                                                       \
     "ds_read_b32 " XA ", %[a4" S "]\n\t"                                                       \
@@ -933,18 +842,18 @@ __device__ __forceinline__ uint32_t lds_addr(T* p)
     "v_cndmask_b32_e64 %[da], %[sp], %[wa" S "], %[" M "]\n\t"                                 \
     "v_cndmask_b32_e64 %[dz], %[sp], %[wo" S "], %[" M "]\n\t"                                 \
     "s_waitcnt lgkmcnt(1)\n\t"                                                                 \
-    "v_max_i32_e32 v244, %[pth" S "], " XO "\n\t"                                              \
+    BND("v244", "pth" S, XO)                                                                   \
     "s_waitcnt lgkmcnt(0)\n\t"                                                                 \
     "v_cmp_le_i32_e32 vcc, " XA ", v244\n\t"                                                   \
     "v_cndmask_b32_e64 v244, 0, %[pua" S "], vcc\n\t"                                          \
     "v_cndmask_b32_e64 v245, %[puo" S "], 0, vcc\n\t"                                          \
     "v_lshl_add_u64 " X ", " X ", 0, v[244:245]\n\t"                                           \
-    "v_max_i32_e32 v244, %[pth2" S "], " XO "\n\t"                                             \
+    BND("v244", "pth2" S, XO)                                                                  \
     "v_cmp_le_i32_e32 vcc, " XA ", v244\n\t"                                                   \
     "v_cndmask_b32_e64 v244, 0, %[pua2" S "], vcc\n\t"                                         \
     "v_cndmask_b32_e64 v245, %[puo2" S "], 0, vcc\n\t"                                         \
     "v_lshl_add_u64 " X ", " X ", 0, v[244:245]\n\t"                                           \
-    "v_max_i32_e32 v246, %[th" S "], " XO "\n\t"                                               \
+    BND("v246", "th" S, XO)                                                                    \
     "v_cmp_le_i32_e32 vcc, " XA ", v246\n\t"                                                   \
     "v_cndmask_b32_e64 v244, 0, %[ua" S "], vcc\n\t"                                           \
     "v_cndmask_b32_e64 v245, %[uo" S "], 0, vcc\n\t"                                           \
@@ -952,9 +861,9 @@ __device__ __forceinline__ uint32_t lds_addr(T* p)
     "ds_write_b32 %[dz], v247\n\t"                                                             \
     "ds_write_b32 %[da], v246\n\t"
 
-#define DM_STEP_PAIR(K0, K1)                                                                   \
-    DM_STEP_TEXT(K0, "v240", "v241", "v[240:241]", "m0", "v242", "v243", "m1", "A", "B")       \
-    DM_STEP_TEXT(K1, "v242", "v243", "v[242:243]", "m1", "v240", "v241", "m0", "B", "A")
+#define DM_STEP_PAIR(BND, K0, K1)                                                              \
+    DM_STEP_TEXT(BND, K0, "v240", "v241", "v[240:241]", "m0", "v242", "v243", "m1", "A", "B")    \
+    DM_STEP_TEXT(BND, K1, "v242", "v243", "v[242:243]", "m1", "v240", "v241", "m0", "B", "A")
 
 #define DM_SIZE_CHECK(K0, K1)                                                                  \
     ".if (.Ldmw%=_" #K1 " - .Ldmw%=_" #K0 ") != (.Ldmw%=_1 - .Ldmw%=_0)\n\t"                   \
@@ -979,27 +888,28 @@ __device__ __forceinline__ uint32_t lds_addr(T* p)
 // last pass the last depth's reads (an odd step: set B) are captured into
 // (LaB, LoB).  e < 16 and np1 < 4 by the masks, and the assembler checks
 // that the 16 steps have one size.
-#define DM_WALK_BLOCK()                                                                        \
-    asm volatile("v_readfirstlane_b32 s99, %[ctl]\n\t"                                         \
-                 "s_getpc_b64 s[96:97]\n"                                                      \
+// J0..J3 name the scalar registers of the jump (JP the pair of J0 and J1).
+#define DM_WALK_BLOCK(BND, JP, J0, J1, J2, J3)                                                   \
+    asm volatile("v_readfirstlane_b32 " J3 ", %[ctl]\n\t"                                       \
+                 "s_getpc_b64 " JP "\n"                                                       \
                  ".Ldmw%=_pc:\n\t"                                                             \
-                 "s_and_b32 s98, s99, 15\n\t"                                                  \
-                 "s_mul_i32 s98, s98, (.Ldmw%=_1 - .Ldmw%=_0)\n\t"                             \
-                 "s_add_u32 s98, s98, (.Ldmw%=_0 - .Ldmw%=_pc)\n\t"                            \
-                 "s_add_u32 s96, s96, s98\n\t"                                                 \
-                 "s_addc_u32 s97, s97, 0\n\t"                                                  \
-                 "s_bfe_u32 s99, s99, 0x20004\n\t"                                             \
-                 "s_setpc_b64 s[96:97]\n"                                                      \
-                 DM_STEP_PAIR(0, 1) DM_STEP_PAIR(2, 3) DM_STEP_PAIR(4, 5) DM_STEP_PAIR(6, 7)  \
-                 DM_STEP_PAIR(8, 9) DM_STEP_PAIR(10, 11) DM_STEP_PAIR(12, 13)                 \
-                 DM_STEP_PAIR(14, 15)                                                          \
+                 "s_and_b32 " J2 ", " J3 ", 15\n\t"                                            \
+                 "s_mul_i32 " J2 ", " J2 ", (.Ldmw%=_1 - .Ldmw%=_0)\n\t"                       \
+                 "s_add_u32 " J2 ", " J2 ", (.Ldmw%=_0 - .Ldmw%=_pc)\n\t"                      \
+                 "s_add_u32 " J0 ", " J0 ", " J2 "\n\t"                                        \
+                 "s_addc_u32 " J1 ", " J1 ", 0\n\t"                                            \
+                 "s_bfe_u32 " J3 ", " J3 ", 0x20004\n\t"                                       \
+                 "s_setpc_b64 " JP "\n"                                                       \
+                 DM_STEP_PAIR(BND, 0, 1) DM_STEP_PAIR(BND, 2, 3) DM_STEP_PAIR(BND, 4, 5)             \
+                 DM_STEP_PAIR(BND, 6, 7) DM_STEP_PAIR(BND, 8, 9) DM_STEP_PAIR(BND, 10, 11)           \
+                 DM_STEP_PAIR(BND, 12, 13) DM_STEP_PAIR(BND, 14, 15)                               \
                  ".Ldmw%=_16:\n\t"                                                             \
                  "v_add_u32_e32 %[relA], -16, %[relA]\n\t"                                     \
                  "v_add_u32_e32 %[relB], -16, %[relB]\n\t"                                     \
-                 "s_sub_u32 s99, s99, 1\n\t"                                                   \
+                 "s_sub_u32 " J3 ", " J3 ", 1\n\t"                                             \
                  "s_cbranch_scc0 .Ldmw%=_0\n\t"                                                \
-                 "v_cndmask_b32_e64 %[LaB], %[LaB], v242, %[m1]\n\t"                             \
-                 "v_cndmask_b32_e64 %[LoB], %[LoB], v243, %[m1]\n\t"                             \
+                 "v_cndmask_b32_e64 %[LaB], %[LaB], v242, %[m1]\n\t"                           \
+                 "v_cndmask_b32_e64 %[LoB], %[LoB], v243, %[m1]\n\t"                           \
                  DM_SIZE_CHECK(1, 2) DM_SIZE_CHECK(2, 3) DM_SIZE_CHECK(3, 4)                   \
                  DM_SIZE_CHECK(4, 5) DM_SIZE_CHECK(5, 6) DM_SIZE_CHECK(6, 7)                   \
                  DM_SIZE_CHECK(7, 8) DM_SIZE_CHECK(8, 9) DM_SIZE_CHECK(9, 10)                  \
@@ -1008,31 +918,30 @@ __device__ __forceinline__ uint32_t lds_addr(T* p)
                  : [m0] "=&s"(m0), [m1] "=&s"(m1), [LaA] "+v"(LaA), [LoA] "+v"(LoA),          \
                    [LaB] "+v"(LaB), [LoB] "+v"(LoB), [da] "=&v"(da), [dz] "=&v"(dz),          \
                    [relA] "+v"(relA), [relB] "+v"(relB)                                        \
-                 : DM_SET_OPERANDS(A), DM_SET_OPERANDS(B), [sp] "v"(sp4), [ctl] "v"(ctl)      \
-                 : "s96", "s97", "s98", "s99", "v240", "v241", "v242", "v243", "v244", "v245",  \
-                   "v246", "v247", "vcc", "scc", "memory")
+                 : DM_SET_OPERANDS(A), DM_SET_OPERANDS(B), [sp] "v"(sp4), [ctl] "v"(ctl),     \
+                   [low] "s"(low)                                                              \
+                 : J0, J1, J2, J3, "v240", "v241", "v242", "v243", "v244", "v245", "v246",     \
+                   "v247", "vcc", "scc", "memory")
 
-template <typename T>
-__device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
-                                             const uint32_t* __restrict__ nwin,
-                                             const uint32_t* __restrict__ live_ids,
-                                             uint32_t n_live, int64_t* __restrict__ loads,
-                                             int64_t b0, longlong2* __restrict__ lpre,
-                                             int64_t tbase, int64_t per, uint32_t qshift,
-                                             int64_t slo, uint32_t policy, T* L)
+template <typename T, bool TTFT>
+__device__ __forceinline__ void walk_windows(const SelArgs& g, const WalkRec* __restrict__ rec,
+                                             const uint32_t* __restrict__ nwin, int64_t b0,
+                                             longlong2* __restrict__ lpre, T* L)
 {
     constexpr bool wide = sizeof(T) == 8;
     const int lane = lane_id();
     // a spare slot per lane, then the loads
     L[lane] = (T)0;
-    for (uint32_t d = lane; d < n_live; d += kWave)
-        L[kWave + d] = (T)(loads[live_ids[d]] - b0);
+    for (uint32_t d = lane; d < g.n_live; d += kWave)
+        L[kWave + d] = (T)(g.loads[g.live_ids[d]] - b0);
     __syncthreads();
     const uint64_t nw = __builtin_amdgcn_readfirstlane(nwin[0]);
     // the records hold offsets within L in 4-byte slots; the LDS address of
     // L itself is a link-time constant (zero when it is the only array)
     const uint32_t lbase = lds_addr(reinterpret_cast<int32_t*>(L));
     const uint32_t sp4 = lbase + 4u * lane;
+    // the low q bits (loads of the 32-bit walk are below 2^31)
+    const int32_t low = g.qshift < 31 ? (int32_t)((1u << g.qshift) - 1) : INT32_MAX;
     int32_t LaA32 = 0, LoA32 = 0, LaB32 = 0, LoB32 = 0;
     // window w: set A's records cA, set B's cB (same control word)
     auto window = [&](WalkRec& cA, WalkRec& cB, uint64_t w) {
@@ -1040,13 +949,21 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
             // the packed bounds are clamped to 32 bits: recompute them
             // exactly, relative to the base (equal matches: -inf; cache
             // affinity: +inf)
-            const bool keep_a = policy == DM_POLICY_CACHE_AFFINITY;
+            const bool keep_a = g.policy == DM_POLICY_CACHE_AFFINITY;
             auto exact = [&](int32_t packed, uint32_t u) -> T {
                 return packed == INT32_MIN ? (T)INT64_MIN
                        : keep_a            ? (T)INT64_MAX
-                                           : (T)((slo - tbase - per * (int64_t)u + 1) *
-                                                     ((int64_t)1 << qshift) -
+                                           : (T)((g.slo - g.tbase - g.per * (int64_t)u + 1) *
+                                                     ((int64_t)1 << g.qshift) -
                                                  1 - b0);
+            };
+            // take a, on the loads xa and xo relative to b0
+            auto takes = [&](T xa, T xo, int32_t packed, uint32_t ua, uint32_t uo) -> bool {
+                if constexpr (TTFT)
+                    return ((xa + b0) >> g.qshift) - ((xo + b0) >> g.qshift) <=
+                           g.per * ((int64_t)uo - (int64_t)ua);
+                else
+                    return xa <= std::max(exact(packed, ua), xo);
             };
             // Every lane reads and writes at every depth, without branches on
             // lane data; a lane not on the current depth, and a run member
@@ -1056,18 +973,16 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
             const uint32_t sp = lane;
             T La[kSets] = {0, 0}, Lo[kSets] = {0, 0};
             auto step = [&](const WalkRec& c, uint32_t l, T& la, T& lo) {
-                const T th = exact(c.th, c.ua), pth = exact(c.pth, c.pua);
-                const T pth2 = exact(c.pth2, c.pua2);
                 const T ua = (T)c.ua, uo = (T)c.uo, pua = (T)c.pua, puo = (T)c.puo;
                 const T pua2 = (T)c.pua2, puo2 = (T)c.puo2;
                 const uint32_t a = c.a4 >> 2, o = c.o4 >> 2, wa = c.wa >> 2, wo = c.wo >> 2;
                 const bool act = c.rel - e == l;
                 const T xa = L[a], xo = L[o];
-                const bool p1 = xa <= std::max(pth, xo);
+                const bool p1 = takes(xa, xo, c.pth, c.pua, c.puo);
                 const T x0 = xa + (p1 ? pua : (T)0), y0 = xo + (p1 ? (T)0 : puo);
-                const bool p2 = x0 <= std::max(pth2, y0);
+                const bool p2 = takes(x0, y0, c.pth2, c.pua2, c.puo2);
                 const T x1 = x0 + (p2 ? pua2 : (T)0), y1 = y0 + (p2 ? (T)0 : puo2);
-                const bool take_a = x1 <= std::max(th, y1);
+                const bool take_a = takes(x1, y1, c.th, c.ua, c.uo);
                 L[act ? wo : sp] = take_a ? y1 : y1 + uo;
                 L[act ? wa : sp] = take_a ? x1 + ua : x1;
                 la = act ? x1 : la;
@@ -1096,7 +1011,10 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
             int32_t da, dz;
             uint64_t m0, m1;
             int32_t LaA = LaA32, LoA = LoA32, LaB = LaB32, LoB = LoB32;
-            DM_WALK_BLOCK();
+            if constexpr (TTFT)
+                DM_WALK_BLOCK(DM_BOUND_TTFT, "s[92:93]", "s92", "s93", "s94", "s95");
+            else
+                DM_WALK_BLOCK(DM_BOUND_SLO, "s[96:97]", "s96", "s97", "s98", "s99");
             (void)m0; (void)m1; (void)da; (void)dz;
             LaA32 = LaA;
             LoA32 = LoA;
@@ -1136,8 +1054,8 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
         }
     }
     __syncthreads();
-    for (uint32_t d = lane; d < n_live; d += kWave)
-        loads[live_ids[d]] = b0 + (int64_t)L[kWave + d];
+    for (uint32_t d = lane; d < g.n_live; d += kWave)
+        g.loads[g.live_ids[d]] = b0 + (int64_t)L[kWave + d];
 }
 
 #undef DM_WALK_BLOCK
@@ -1145,50 +1063,79 @@ __device__ __forceinline__ void walk_windows(const WalkRec* __restrict__ rec,
 #undef DM_SIZE_CHECK
 #undef DM_STEP_PAIR
 #undef DM_STEP_TEXT
+#undef DM_BOUND_TTFT
+#undef DM_BOUND_SLO
 
-// One wave: 32-bit relative loads unless plan[2] asks for 64-bit ones.
-__global__ __launch_bounds__(kWave) void select_fast_kernel(
-    const WalkRec* __restrict__ rec, const uint32_t* __restrict__ nwin,
-    const uint32_t* __restrict__ live_ids, uint32_t n_live, int64_t* __restrict__ loads,
-    const uint32_t* __restrict__ plan,
-    const int64_t* __restrict__ base, longlong2* __restrict__ lpre, int64_t tbase, int64_t per,
-    uint32_t qshift, int64_t slo, uint32_t policy)
+// One wave.  First the plan: the windowed path iff every record's uncached
+// counts fit 32 bits; its loads are absolute 32-bit values when every live
+// load lies in [0, 2^30) and grows by less than 2^30 whatever the decisions,
+// else 64-bit values relative to the smallest live load, as long as they stay
+// below it + 2^62; otherwise the serial path.  (Three kernels of 4.5 us each
+// -- smallest load, plan, an empty serial path -- once ran around the walk.)
+// plan[0] = 1 for the windowed path, plan[1] = 1 for its 64-bit loads, and
+// base[0] their base, for the epilogue.
+template <bool TTFT>
+__global__ __launch_bounds__(kWave) void select_walk_kernel(
+    SelArgs g, const WalkRec* __restrict__ rec, const uint32_t* __restrict__ nwin,
+    const unsigned long long* __restrict__ grow, uint32_t* __restrict__ plan,
+    int64_t* __restrict__ base, longlong2* __restrict__ lpre)
 {
     // Claim the whole register file of this wave's SIMD (256 + 256
     // registers), so that no wave of another kernel shares its issue slots:
     // this single wave is the serial critical path of a batch, and with
     // pipelining the next batch's kernels run beside it.
     asm volatile("" ::: "v255", "a255");
-    if (!plan[1])
-        return;
     __shared__ int64_t L[kWave + kMaxSlots];  // one spare slot per lane, then the loads
-    const int64_t b0 = plan[2] ? base[0] : 0;  // 32-bit walks use absolute loads
-    if (plan[2])
-        walk_windows<int64_t>(rec, nwin, live_ids, n_live, loads, b0, lpre, tbase, per, qshift, slo,
-                              policy, L);
+    const int lane = lane_id();
+    int64_t mn = INT64_MAX, mx = INT64_MIN;
+    unsigned long long gmax = 0;
+    for (uint32_t d = lane; d < g.n_live; d += kWave) {
+        const int64_t v = g.loads[g.live_ids[d]];
+        const unsigned long long u = grow[d];
+        mn = v < mn ? v : mn;
+        mx = v > mx ? v : mx;
+        gmax = u > gmax ? u : gmax;
+    }
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int64_t a = (int64_t)shfl_xor_u64((uint64_t)mn, d);
+        const int64_t b = (int64_t)shfl_xor_u64((uint64_t)mx, d);
+        const unsigned long long u = shfl_xor_u64(gmax, d);
+        mn = a < mn ? a : mn;
+        mx = b > mx ? b : mx;
+        gmax = u > gmax ? u : gmax;
+    }
+    // mx - mn cannot wrap in unsigned arithmetic
+    const bool windowed = __builtin_amdgcn_readfirstlane(
+        grow[kMaxSlots] == 0 && (unsigned long long)mx - (unsigned long long)mn < (1ull << 62) &&
+        gmax < (1ull << 62));
+    const bool narrow =
+        __builtin_amdgcn_readfirstlane(mn >= 0 && mx < (1ll << 30) && gmax < (1ull << 30));
+    const int64_t b0 = narrow ? 0 : (int64_t)readlane_u64((uint64_t)mn, 0);
+    if (lane == 0) {
+        plan[0] = windowed ? 1 : 0;
+        plan[1] = windowed && !narrow ? 1 : 0;
+        base[0] = b0;
+    }
+    if (!windowed)
+        select_serial<TTFT>(g, L);
+    else if (!narrow)
+        walk_windows<int64_t, TTFT>(g, rec, nwin, b0, lpre, L);
     else
-        walk_windows<int32_t>(rec, nwin, live_ids, n_live, loads, b0, lpre, tbase, per, qshift, slo,
-                              policy, reinterpret_cast<int32_t*>(L));
+        walk_windows<int32_t, TTFT>(g, rec, nwin, 0, lpre, reinterpret_cast<int32_t*>(L));
 }
 
-__global__ void sel_out_kernel(const int64_t* __restrict__ offsets, uint64_t n, uint32_t bshift,
-                               const uint32_t* __restrict__ cand, const uint32_t* __restrict__ match,
-                               const longlong2* __restrict__ lpre,
+__global__ void sel_out_kernel(SelArgs g, const longlong2* __restrict__ lpre,
                                const uint32_t* __restrict__ slot_of, uint64_t nslots,
                                const int64_t* __restrict__ base,
-                               const uint32_t* __restrict__ plan, uint8_t* __restrict__ flags,
-                               uint32_t* __restrict__ chosen, int64_t* __restrict__ ttft,
-                               int64_t tbase, int64_t per, uint32_t qshift, int64_t slo,
-                               uint32_t policy)
+                               const uint32_t* __restrict__ plan)
 {
-    if (!plan[1])
+    if (!plan[0])
         return;
-    const bool wide = plan[2] != 0;
+    const bool wide = plan[1] != 0;
     const int64_t b0 = wide ? base[0] : 0;
-    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n;
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < g.n;
          r += (uint64_t)gridDim.x * blockDim.x) {
-        SelRec s = load_rec(offsets, n, r, true, bshift, cand, match, tbase, per, qshift, slo,
-                            policy);
+        const SelRec s = load_rec(g, r, true);
         const uint32_t q = slot_of[r];
         if (q >= nslots)  // only when the packing failed, which the status reports
             continue;
@@ -1203,24 +1150,10 @@ __global__ void sel_out_kernel(const int64_t* __restrict__ offsets, uint64_t n, 
             Lo = lp.y;
         }
         // the walk records (L_a, L_o); a is c2 when c2 has the longer match
-        // (never under the least-load rule)
-        const bool a_is_c2 = s.a2;
-        store_out(s, r, b0 + (a_is_c2 ? Lo : La), b0 + (a_is_c2 ? La : Lo), flags, chosen, ttft,
-                  tbase, per, qshift, slo);
+        // (never under the least-load and minimum-TTFT rules)
+        store_out(g, s, r, b0 + (s.a2 ? Lo : La), b0 + (s.a2 ? La : Lo));
     }
 }
-
-template <int R>
-void launch_select(dm_ctx* c, hipStream_t st, const int64_t* offsets, uint64_t n, uint32_t bshift,
-                   const dm_route_out* out, int64_t* loads, const uint32_t* plan)
-{
-    const dm_config& k = c->cfg;
-    select_kernel<R><<<1, kWave, 0, st>>>(offsets, n, bshift, out->cand, out->match,
-                                                 out->flags, out->chosen, out->ttft_us, loads,
-                                                 k.max_slots, k.ttft_base_us, k.ttft_per_token_us,
-                                                 c->shift_div, k.slo_us, c->policy, plan);
-}
-
 
 }  // namespace
 
@@ -1340,6 +1273,14 @@ static uint32_t block_shift(const dm_ctx* c)
     return bshift;
 }
 
+hipError_t select_growth(dm_ctx* c, uint64_t n, int par, unsigned long long** grow)
+{
+    SelBuf b;
+    const hipError_t e = sel_buffers(c, n, par, &b);
+    *grow = b.grow;
+    return e;
+}
+
 hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uint64_t n,
                           const dm_route_out* out, int par)
 {
@@ -1351,7 +1292,6 @@ hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uin
     if (b.nblk > 0x7FFFFFFFull || fill_waves > 0x7FFFFFFFull)
         return hipErrorInvalidValue;
     const uint32_t NL = c->n_live;
-    sel_zero_kernel<<<1, 256, 0, st>>>(b.grow, NL);
     const dm_config& k = c->cfg;
     // few workgroups: each adds its per-instance growth sums to the global
     // ones with one atomic per instance, and those atomics meet on a few lines
@@ -1371,10 +1311,12 @@ hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uin
             large ? level(sel_level_kernel<2048, kMaxSlots>)
                   : level(sel_level_kernel<1024, kMaxSlots>);
     }
-    sel_scan_kernel<<<1, 1024, 0, st>>>(b.wcount, b.nblk, b.woff, b.total);
+    const bool scan = b.nblk > kScanFrom;
+    if (scan)
+        sel_scan_kernel<<<1, 1024, 0, st>>>(b.wcount, b.nblk, b.woff, b.total);
     sel_fill_kernel<<<(uint32_t)((fill_waves + 3) / 4), 4 * kWave, 0, st>>>(
-        b.prep, n, b.info, b.slotmap, b.wdepth, b.wcount, b.woff, b.total, b.nblk, b.shape,
-        b.rec, b.slot_of);
+        b.prep, n, b.info, b.slotmap, b.wdepth, b.wcount, scan ? b.woff : nullptr, b.total, b.nblk,
+        b.shape, b.rec, b.slot_of);
     return hipGetLastError();
 }
 
@@ -1387,26 +1329,15 @@ hipError_t select_run(dm_ctx* c, hipStream_t ss, hipStream_t os, hipEvent_t sel_
     if (e != hipSuccess)
         return e;
     const dm_config& k = c->cfg;
-    const uint32_t S = k.max_slots, NL = c->n_live, bshift = block_shift(c);
-    sel_base_kernel<<<1, 256, 0, ss>>>(loads, c->d_live_ids, NL, b.base, b.grow);
-    sel_plan_kernel<<<1, 256, 0, ss>>>(loads, c->d_live_ids, NL, b.base, b.grow, c->policy,
-                                       b.plan);
-    select_fast_kernel<<<1, kWave, 0, ss>>>(b.rec, b.total, c->d_live_ids, NL, loads, b.plan,
-                                            b.base, b.lpre, k.ttft_base_us, k.ttft_per_token_us,
-                                            c->shift_div, k.slo_us, c->policy);
-    if (S <= 64)
-        launch_select<1>(c, ss, offsets, n, bshift, out, loads, b.plan);
-    else if (S <= 128)
-        launch_select<2>(c, ss, offsets, n, bshift, out, loads, b.plan);
-    else if (S <= 192)
-        launch_select<3>(c, ss, offsets, n, bshift, out, loads, b.plan);
-    else if (S <= 256)
-        launch_select<4>(c, ss, offsets, n, bshift, out, loads, b.plan);
+    const SelArgs g{offsets, n, block_shift(c), out->cand, out->match, out->flags, out->chosen,
+                    out->ttft_us, loads, c->d_live_ids, c->n_live, k.max_slots, k.ttft_base_us,
+                    k.ttft_per_token_us, c->shift_div, k.slo_us, c->policy};
+    if (c->policy == DM_POLICY_MIN_TTFT)
+        select_walk_kernel<true><<<1, kWave, 0, ss>>>(g, b.rec, b.total, b.grow, b.plan, b.base,
+                                                      b.lpre);
     else
-        select_lds_kernel<<<1, kWave, 0, ss>>>(offsets, n, bshift, out->cand, out->match,
-                                               out->flags, out->chosen, out->ttft_us, loads, S,
-                                               k.ttft_base_us, k.ttft_per_token_us, c->shift_div,
-                                               k.slo_us, c->policy, b.plan);
+        select_walk_kernel<false><<<1, kWave, 0, ss>>>(g, b.rec, b.total, b.grow, b.plan, b.base,
+                                                       b.lpre);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     if (os != ss) {
@@ -1414,10 +1345,8 @@ hipError_t select_run(dm_ctx* c, hipStream_t ss, hipStream_t os, hipEvent_t sel_
             (e = hipStreamWaitEvent(os, sel_done, 0)) != hipSuccess)
             return e;
     }
-    sel_out_kernel<<<grid_for(n, 256, 8192), 256, 0, os>>>(
-        offsets, n, bshift, out->cand, out->match, b.lpre, b.slot_of, b.nslots, b.base, b.plan,
-        out->flags, out->chosen, out->ttft_us, k.ttft_base_us, k.ttft_per_token_us, c->shift_div,
-        k.slo_us, c->policy);
+    sel_out_kernel<<<grid_for(n, 256, 8192), 256, 0, os>>>(g, b.lpre, b.slot_of, b.nslots, b.base,
+                                                           b.plan);
     return hipGetLastError();
 }
 

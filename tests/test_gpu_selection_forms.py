@@ -1,5 +1,7 @@
 """Selection forms chosen by size or rule, each against the oracle, element by
-element: dense indices past one byte (more than 256 live instances)."""
+element: dense indices past one byte (more than 256 live instances), the
+minimum-TTFT rule's walks, the serial path."""
+import dataclasses
 import sys
 
 import numpy as np
@@ -54,3 +56,29 @@ def test_windows_on_many_instances(n_inst, n_req, wide):
     if wide:
         L0[::3] += 1 << 40
     _pair(wl, L0)
+
+
+@pytest.mark.parametrize("n_inst,div,wide", [(1, 4, 0), (3, 4, 0), (8, 1, 0), (8, 1 << 14, 0), (8, 1 << 31, 0),
+                                             (200, 4, 0), (300, 4, 0), (8, 4, 1), (8, 1 << 33, 1), (300, 4, 1),
+                                             (8, 4, 2)])
+def test_min_ttft_windows(n_inst, div, wide):
+    """The minimum-TTFT rule: 32-bit walk (its bound in the steps), 64-bit walk
+    (wide=1) and serial path (wide=2: loads spread past 2^62), under queue
+    divisors from none to past every load."""
+    wl = workloads.small_random(91 + n_inst, n_inst, 3, 16, 2600)
+    wl = dataclasses.replace(wl, n_prior=300, route=dataclasses.replace(wl.route, queue_div=div))
+    L0 = workloads.initial_loads(wl, wl.route.max_slots)
+    if wide:
+        L0[::3] += 1 << 40
+        L0[1] = (1 << 62) + ((1 << 50) if wide == 2 else -(1 << 50))
+    _pair(wl, L0, "min_ttft")
+
+
+@pytest.mark.parametrize("policy", ["slo_aware", "cache_affinity", "least_loaded", "min_ttft"])
+@pytest.mark.parametrize("n_inst", [2, 64, 260])
+def test_serial_path(n_inst, policy):
+    """Loads spread past 2^62: one request at a time, whatever the rule."""
+    wl = workloads.small_random(17 + n_inst, n_inst, 3, 16, 200, slo_us=3_000)
+    L0 = workloads.initial_loads(wl, wl.route.max_slots)
+    L0[1] = (1 << 62) + (1 << 50)
+    _pair(wl, L0, policy)
