@@ -339,31 +339,43 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
 //
 // Larger blocks give fewer depth steps and windows (on the large batch,
 // 78,742 steps in 9,832 windows with blocks of 2048 against 79,786 in
-// 10,225 with 1024) but take the level kernel twice as long per block, which
-// only a batch long enough to hide it behind its walk repays: batches of
-// at least kLargeFrom requests use blocks of 2048, others blocks of 1024.
+// 10,225 with 1024) but take the level kernel longer per block, in
+// proportion.  Batches of at least kLargeFrom requests use blocks of 2048,
+// others blocks of 1024, and unpipelined ones of at most kSmallTo requests
+// blocks of 256, whose kernel ends in a quarter of the time (124 to 31 us on
+// 8 instances) for a walk some 5% longer.  Whole calls, 1024 against 256:
+// 1,024 requests 245 and 142 us, 4,096 chat requests 333 and 267, 32,768 on
+// 512 instances 417 and 374, 65,536 chat requests 1,804 and 1,780; at 131,072
+// the two meet.  Pipelined, the kernel runs beside the previous walk, which is
+// what the batches wait for.
 template <uint32_t LB>
 struct LevelShape {
     static constexpr uint32_t block = LB;
-    static constexpr uint32_t wincap = LB == 1024 ? 36u : 66u;  // windows per block
+    static constexpr uint32_t wincap = LB == 256 ? 9u : LB == 1024 ? 36u : 66u;  // windows per block
     static_assert(wincap >= 2 * ((LB + 64) / 65) + 1, "room for the windows of a block");
 };
-constexpr uint64_t kLargeFrom = 1u << 19;
-// The batch limit follows the large layout; the small one only serves
+constexpr uint64_t kLargeFrom = 1u << 19, kSmallTo = 1u << 16;
+// The batch limit follows the large layout; the others only serve
 // batches whose slots stay far inside 32 bits.
 static_assert(LevelShape<2048>::block == kSelBlock &&
                   LevelShape<2048>::wincap == kSelWindowsPerBlock &&
                   kLargeFrom / 1024 * LevelShape<1024>::wincap * kSets * kWave < (1ull << 32),
               "dm_route_batch's batch limit assumes this layout");
+// A batch's work arrays have one size whichever of the two smaller layouts
+// it takes (see sel_sizes).
+static_assert(4 * LevelShape<256>::wincap == LevelShape<1024>::wincap, "windows per 1024 requests");
 
 // Block size and window capacity of a batch of n requests.
 struct BlockShape {
     uint32_t block, wincap;
 };
-static BlockShape block_shape(uint64_t n)
+static BlockShape block_shape(uint64_t n, bool pipelined)
 {
-    return n >= kLargeFrom ? BlockShape{LevelShape<2048>::block, LevelShape<2048>::wincap}
-                           : BlockShape{LevelShape<1024>::block, LevelShape<1024>::wincap};
+    if (n >= kLargeFrom)
+        return BlockShape{LevelShape<2048>::block, LevelShape<2048>::wincap};
+    if (n <= kSmallTo && !pipelined)
+        return BlockShape{LevelShape<256>::block, LevelShape<256>::wincap};
+    return BlockShape{LevelShape<1024>::block, LevelShape<1024>::wincap};
 }
 
 // One wave per block.  Writes, per request, info = depth in its window |
@@ -393,7 +405,7 @@ static BlockShape block_shape(uint64_t n)
 template <uint32_t LB, uint32_t LIVE>
 __global__ __launch_bounds__(kWave) void sel_level_kernel(
     const SelPack* __restrict__ prep, uint64_t n, uint32_t* __restrict__ info,
-    uint16_t* __restrict__ slotmap, uint8_t* __restrict__ wdepth, uint32_t* __restrict__ wcount,
+    uint16_t* __restrict__ slotmap, uint8_t* __restrict__ wdepth, uint8_t* __restrict__ wcount,
     uint32_t* __restrict__ status)
 {
     constexpr uint32_t kWinCap = LevelShape<LB>::wincap;
@@ -657,7 +669,7 @@ __global__ __launch_bounds__(kWave) void sel_level_kernel(
     if (lane < kWinCap)
         wdepth[(uint64_t)blockIdx.x * kWinCap + lane] = okw && lane < nwin ? wdep[lane] : 0;
     if (lane == 0)
-        wcount[blockIdx.x] = okw ? nwin : 0;
+        wcount[blockIdx.x] = (uint8_t)(okw ? nwin : 0);
 }
 
 // Exclusive scan of the blocks' window counts (one workgroup); total[0] =
@@ -665,7 +677,7 @@ __global__ __launch_bounds__(kWave) void sel_level_kernel(
 // of the fill kernel sums the counts before its block itself (at most 16
 // loads a lane), which spares a launch of 4.7 us.
 constexpr uint64_t kScanFrom = 1024;
-__global__ __launch_bounds__(1024) void sel_scan_kernel(const uint32_t* __restrict__ wcount,
+__global__ __launch_bounds__(1024) void sel_scan_kernel(const uint8_t* __restrict__ wcount,
                                                         uint64_t nblk, uint32_t* __restrict__ woff,
                                                         uint32_t* __restrict__ total)
 {
@@ -709,7 +721,7 @@ __global__ __launch_bounds__(1024) void sel_scan_kernel(const uint32_t* __restri
 __global__ __launch_bounds__(4 * kWave) void sel_fill_kernel(
     const SelPack* __restrict__ prep, uint64_t n, const uint32_t* __restrict__ info,
     const uint16_t* __restrict__ slotmap, const uint8_t* __restrict__ wdepth,
-    const uint32_t* __restrict__ wcount, const uint32_t* __restrict__ woff,
+    const uint8_t* __restrict__ wcount, const uint32_t* __restrict__ woff,
     uint32_t* __restrict__ total, uint64_t nblk, BlockShape bs, WalkRec* __restrict__ rec,
     uint32_t* __restrict__ slot_of)
 {
@@ -1170,7 +1182,7 @@ struct SelBuf {
     uint32_t* slot_of;
     uint16_t* slotmap;
     uint8_t* wdepth;
-    uint32_t* wcount;
+    uint8_t* wcount;
     uint32_t* woff;
     uint32_t* total;
     int64_t* base;
@@ -1186,9 +1198,10 @@ static size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // Sizes of one set's arrays for a batch of n requests, in layout order.
 static void sel_sizes(uint64_t n, size_t* sizes)
 {
-    const BlockShape bs = block_shape(n);
+    const BlockShape bs = block_shape(n, true);
     const uint64_t nblk = (n + bs.block - 1) / bs.block;
     const uint64_t wcap = nblk * bs.wincap;
+    const uint64_t counts = n <= kSmallTo ? 4 * nblk : nblk;  // blocks of 256 included
     const size_t z[] = {
         up256(n * sizeof(SelPack)),                                  // prep
         up256((wcap + 2 * kPrefetch) * kSets * kWave * sizeof(WalkRec)),  // rec
@@ -1197,8 +1210,8 @@ static void sel_sizes(uint64_t n, size_t* sizes)
         up256(n * sizeof(uint32_t)),                                 // slot_of
         up256(wcap * kSets * kWave * sizeof(uint16_t)),              // slotmap
         up256(wcap),                                                 // wdepth
-        up256(nblk * sizeof(uint32_t)),                              // wcount
-        up256(nblk * sizeof(uint32_t)),                              // woff
+        up256(counts),                                               // wcount
+        nblk > kScanFrom ? up256(nblk * sizeof(uint32_t)) : 0,       // woff
         256 + 256 + (kMaxSlots + 1) * sizeof(unsigned long long),   // total, base/plan, grow
     };
     for (int i = 0; i < 10; i++)
@@ -1217,7 +1230,7 @@ uint64_t select_scratch_bytes(uint64_t n)
 static hipError_t sel_buffers(dm_ctx* c, uint64_t n, int par, SelBuf* b)
 {
     hipError_t e = hipSuccess;
-    b->shape = block_shape(n);
+    b->shape = block_shape(n, c->pipelined);
     b->nblk = (n + b->shape.block - 1) / b->shape.block;
     b->nslots = b->nblk * b->shape.wincap * kSets * kWave;
     size_t sizes[10];
@@ -1255,7 +1268,7 @@ static hipError_t sel_buffers(dm_ctx* c, uint64_t n, int par, SelBuf* b)
     b->slot_of = reinterpret_cast<uint32_t*>(at[4]);
     b->slotmap = reinterpret_cast<uint16_t*>(at[5]);
     b->wdepth = at[6];
-    b->wcount = reinterpret_cast<uint32_t*>(at[7]);
+    b->wcount = at[7];
     b->woff = reinterpret_cast<uint32_t*>(at[8]);
     uint8_t* tail = at[9];
     b->total = reinterpret_cast<uint32_t*>(tail);
@@ -1303,13 +1316,19 @@ hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uin
             kernel<<<(uint32_t)b.nblk, kWave, 0, st>>>(b.prep, n, b.info, b.slotmap, b.wdepth,
                                                        b.wcount, c->d_status);
         };
-        const bool large = b.shape.block == LevelShape<2048>::block;
+        auto sized = [&](auto live) {
+            constexpr uint32_t LIVE = decltype(live)::value;
+            if (b.shape.block == LevelShape<2048>::block)
+                level(sel_level_kernel<2048, LIVE>);
+            else if (b.shape.block == LevelShape<1024>::block)
+                level(sel_level_kernel<1024, LIVE>);
+            else
+                level(sel_level_kernel<256, LIVE>);
+        };
         if (NL <= kByteLive)
-            large ? level(sel_level_kernel<2048, kByteLive>)
-                  : level(sel_level_kernel<1024, kByteLive>);
+            sized(std::integral_constant<uint32_t, kByteLive>{});
         else
-            large ? level(sel_level_kernel<2048, kMaxSlots>)
-                  : level(sel_level_kernel<1024, kMaxSlots>);
+            sized(std::integral_constant<uint32_t, kMaxSlots>{});
     }
     const bool scan = b.nblk > kScanFrom;
     if (scan)

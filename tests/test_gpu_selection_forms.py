@@ -82,3 +82,14 @@ def test_serial_path(n_inst, policy):
     L0 = workloads.initial_loads(wl, wl.route.max_slots)
     L0[1] = (1 << 62) + (1 << 50)
     _pair(wl, L0, policy)
+
+
+@pytest.mark.parametrize("n_inst,n_req", [(1, 255), (2, 256), (3, 257), (8, 511), (64, 513), (200, 1024),
+                                          (300, 700), (40, 65_536), (40, 65_537)])
+def test_small_level_blocks(n_inst, n_req):
+    """Blocks of 256 requests at their edges (one to three instances: every
+    level one pair, 64-depth windows), and both sides of the line to blocks
+    of 1024."""
+    wl = workloads.small_random(131 + n_inst, n_inst, 4, 16, n_req, slo_us=3_000)
+    wl = dataclasses.replace(wl, n_prior=300)
+    _pair(wl, workloads.initial_loads(wl, wl.route.max_slots))
