@@ -227,6 +227,7 @@ dm_status dm_create(const dm_config* cfg, void* hip_stream, dm_ctx** out)
     c->home_stream = c->stream;
     c->shift_div = log2u((uint64_t)k.queue_div);
     c->live.assign(k.max_slots, 0);
+    c->occ_bound.assign(k.max_slots, 0);
     make_params(c->hp, k);
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess)

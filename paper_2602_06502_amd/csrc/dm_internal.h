@@ -141,6 +141,9 @@ struct dm_ctx {
     uint64_t* d_tables = nullptr;  // [max_slots << log2slots]
     uint64_t* d_counts = nullptr;  // [2 * max_slots] live keys, then occupied slots
     uint32_t* d_status = nullptr;  // device status word
+    // [max_slots] most slots of each index that can be occupied (dm_index.hip);
+    // UINT64_MAX: not known
+    std::vector<uint64_t> occ_bound;
 
     dm::Scratch scratch[dm::kScratchSlots];
     dm::Arena arena;                  // set only for the duration of an allocation-free call
@@ -184,6 +187,16 @@ namespace dm {
 dm_status fail(dm_ctx* c, dm_status s, const std::string& msg);
 dm_status hip_fail(dm_ctx* c, hipError_t e, const char* what);
 void* scratch_get(dm_ctx* c, int slot, size_t bytes, hipError_t* e);
+// Is the context's stream recording a graph (or may it be)?
+inline bool stream_capturing(const dm_ctx* c)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &s) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return s != hipStreamCaptureStatusNone;
+}
 // Wait for the context's stream and, with pipelining, its other streams.
 hipError_t sync_streams(dm_ctx* c);
 

@@ -1,0 +1,93 @@
+"""Index inserts by the form they take: with room whatever the keys are (one
+kernel), and without (rebuild, reservations, overflow list), each against a
+set model."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _engine(log2):
+    import paper_2602_06502_amd as pk
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = workloads.small_random(5, 3, 2, 16, 10)
+    cfg = dict(wl.route.as_dict(), index_log2_slots=log2)
+    eng = pk.DualMap(cfg, device="cuda:0")
+    eng.build_rings(range(3))
+    return eng, pk
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def _held(eng, inst, keys):
+    """Which keys instance inst's index holds, by pricing one queued record per
+    key (its chain that key, 16 tokens) on it."""
+    n = len(keys)
+    S = eng.max_slots
+    qoff = np.zeros(S + 1, np.int64)
+    qoff[inst + 1:] = n
+    z = lambda t: _dev(np.zeros(n, t))
+    q = (_dev(qoff), _dev(np.arange(n, dtype=np.uint64)), z(np.uint32), z(np.uint32), z(np.uint32),
+         _dev(np.zeros(S, np.int64)))
+    out = eng.queue_reprobe(q, _dev(np.arange(n + 1, dtype=np.int64)), _dev(keys),
+                            _dev(np.full(n, 16, np.int64)))
+    return out[2].cpu().numpy() == 0
+
+
+@pytest.mark.parametrize("log2,sizes", [(4, (1, 3, 4)), (10, (255, 256, 1)), (10, (257, 200, 400)),
+                                        (12, (2048,)), (12, (1500, 500, 400)), (16, (20_000, 12_768))])
+def test_inserts_up_to_and_past_the_limit(log2, sizes):
+    eng, pk = _engine(log2)
+    rng = np.random.default_rng(log2 + len(sizes))
+    limit = 1 << (log2 - 1)
+    have, sent = set(), []
+    for n in sizes:
+        keys = rng.integers(0, 2**64, size=n, dtype=np.uint64)
+        keys[::7] = keys[0]  # repeated within a batch and across workgroups
+        eng.index_insert(1, _dev(keys))
+        sent.append(keys)
+        want = have | set(keys.tolist())
+        if len(want) <= limit:
+            eng.sync()
+            have = want
+            assert eng.index_size(1) == len(have)
+        else:
+            with pytest.raises(pk.DMError) as ei:
+                eng.sync()
+            assert ei.value.status == pk.DM_EFULL
+            assert eng.index_size(1) == limit
+            break
+    every = np.unique(np.concatenate(sent))
+    held = _held(eng, 1, every)
+    assert held.sum() == eng.index_size(1)
+    assert set(every[held].tolist()) >= have
+
+
+def test_rebuild_after_erases_and_clear():
+    """Erased slots count against the limit until a rebuild or a clear."""
+    eng, _ = _engine(12)
+    rng = np.random.default_rng(2)
+    keys = rng.integers(2, 2**64, size=6000, dtype=np.uint64)
+    live = set()
+    for k in range(6):
+        part = keys[1000 * k:1000 * (k + 1)]
+        eng.index_insert(0, _dev(part))
+        live |= set(part.tolist())
+        gone = np.array(sorted(live), np.uint64)[::2]
+        eng.index_erase(0, _dev(gone))
+        live -= set(gone.tolist())
+        eng.sync()
+        assert eng.index_size(0) == len(live)
+        if k == 3:
+            eng.index_clear(0)
+            live = set()
+            eng.sync()
+    every = np.unique(keys)
+    assert set(every[_held(eng, 0, every)].tolist()) == live
