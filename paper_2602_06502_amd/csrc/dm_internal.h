@@ -105,12 +105,17 @@ struct KeyLen {
 };
 
 // Record of the keys saved through dm_kv_save: (instance, key, time of the
-// latest touch) per entry, one flat array.
+// latest touch) per entry, in any order, in two sets of arrays (a save reads
+// one and writes the other).
 struct KvRecord {
-    uint64_t* key = nullptr;
-    uint64_t* t = nullptr;
-    uint32_t* inst = nullptr;
-    uint64_t n = 0, cap = 0;
+    uint64_t* key[2] = {nullptr, nullptr};
+    uint64_t* t[2] = {nullptr, nullptr};
+    uint32_t* inst[2] = {nullptr, nullptr};
+    uint64_t cap[2] = {0, 0};
+    int cur = 0;
+    uint64_t n = 0;
+    uint32_t* count = nullptr;         // device [max_slots]: entries per instance
+    uint64_t tmin = 0, tmax = 0;       // bounds of the entries' times (n > 0)
 };
 
 }  // namespace dm
@@ -268,13 +273,7 @@ hipError_t ring_remap(dm_ctx* c, const Ring old_r[2], const Ring new_r[2], const
 // dm_index.hip
 hipError_t index_insert(dm_ctx* c, uint32_t id, const uint64_t* keys, uint64_t n);
 hipError_t index_erase(dm_ctx* c, uint32_t id, const uint64_t* keys, uint64_t n);
-// Lists of several instances at once: keys[seg[i] .. seg[i+1]) are instance
-// i's (seg: device [max_slots + 1], seg_host its host copy).  The insert
-// runs as one kernel when every table has room for its keys, else table by
-// table as index_insert.
-hipError_t index_erase_many(dm_ctx* c, const uint64_t* keys, const uint64_t* seg, uint64_t n);
-hipError_t index_insert_many(dm_ctx* c, const uint64_t* keys, const uint64_t* seg,
-                             const uint64_t* seg_host, uint64_t n);
+void index_note_occupied(dm_ctx* c, uint32_t id, uint64_t occupied);
 hipError_t index_clear(dm_ctx* c, uint32_t id);
 // the tables of n instances (host list) emptied by one launch
 hipError_t index_clear_many(dm_ctx* c, const uint32_t* ids_host, uint32_t n);
@@ -519,6 +518,73 @@ __device__ __forceinline__ int bucket_probe(const uint64_t* tab, uint32_t bkt, u
     const bool hit = s0.x == key || s0.y == key || s1.x == key || s1.y == key || s2.x == key ||
                      s2.y == key || s3.x == key || s3.y == key;
     return hit ? kHit : (s3.y == kEmpty ? kMiss : kNext);
+}
+
+// Where canonical key k is, or would go, in a bucket's eight slots as this
+// thread sees them: bit q of the first mask, slot q holds k; of the second,
+// slot q is empty.  Four 16-byte loads in flight instead of a chain of eight
+// dependent ones; a slot seen empty may have been taken since, which the
+// claim's compare-and-swap finds out.
+struct BucketView {
+    uint32_t hit, empty;
+};
+
+__device__ __forceinline__ BucketView bucket_view(const uint64_t* line64, uint64_t k)
+{
+    const v2u64* line = reinterpret_cast<const v2u64*>(line64);
+    const v2u64 s[4] = {line[0], line[1], line[2], line[3]};
+    BucketView v{0, 0};
+#pragma unroll
+    for (uint32_t q = 0; q < 4; q++) {
+        v.hit |= (s[q].x == k ? 1u : 0u) << (2 * q) | (s[q].y == k ? 2u : 0u) << (2 * q);
+        v.empty |= (s[q].x == kEmpty ? 1u : 0u) << (2 * q) |
+                   (s[q].y == kEmpty ? 2u : 0u) << (2 * q);
+    }
+    return v;
+}
+
+// Canonical key k into a table known to have room: stored now, or already
+// there; every slot scanned otherwise.
+enum class Put { kStored, kThere, kNoRoom };
+
+__device__ __forceinline__ Put put_key(uint64_t* slots, uint32_t log2slots, uint64_t k)
+{
+    const uint64_t nbk = 1ull << (log2slots - 3);
+    uint64_t b = home_bucket(k, log2slots);
+    for (uint64_t step = 0; step < nbk; step++, b = (b + 1) & (nbk - 1)) {
+        uint64_t* line = slots + b * kBucket;
+        const BucketView v = bucket_view(line, k);
+        if (v.hit)
+            return Put::kThere;
+        // from the first empty slot on: others may have taken slots since
+        for (uint32_t q = v.empty ? __builtin_ctz(v.empty) : kBucket; q < kBucket; q++) {
+            const unsigned long long prev = atomicCAS((unsigned long long*)(line + q),
+                                                      (unsigned long long)kEmpty,
+                                                      (unsigned long long)k);
+            if (prev == kEmpty)
+                return Put::kStored;
+            if (prev == k)
+                return Put::kThere;
+        }
+    }
+    return Put::kNoRoom;
+}
+
+// Canonical key k erased; true if this thread did it.
+__device__ __forceinline__ bool take_key(uint64_t* slots, uint32_t log2slots, uint64_t k)
+{
+    const uint64_t nbk = 1ull << (log2slots - 3);
+    uint64_t b = home_bucket(k, log2slots);
+    for (uint64_t step = 0; step < nbk; step++, b = (b + 1) & (nbk - 1)) {
+        uint64_t* line = slots + b * kBucket;
+        const BucketView v = bucket_view(line, k);
+        if (v.hit)
+            return atomicCAS((unsigned long long*)(line + __builtin_ctz(v.hit)),
+                             (unsigned long long)k, (unsigned long long)kTomb) == k;
+        if (v.empty)
+            return false;
+    }
+    return false;
 }
 
 // Is canonical key ck in the table?  Walks its probe sequence.
