@@ -31,7 +31,7 @@ hipError_t sync_streams(dm_ctx* c)
     hipError_t e = hipStreamSynchronize(c->stream);
     if (e == hipSuccess && c->home_stream != c->stream)
         e = hipStreamSynchronize(c->home_stream);
-    for (hipStream_t s : {c->work_stream, c->sel_stream, c->out_stream})
+    for (hipStream_t s : {c->work_stream, c->sel_stream, c->out_stream, c->side_stream})
         if (e == hipSuccess && s)
             e = hipStreamSynchronize(s);
     return e;
@@ -76,6 +76,17 @@ hipError_t join_selection(dm_ctx* c)
     if (!c->pipelined || c->batches == 0)
         return hipSuccess;
     return hipStreamWaitEvent(c->stream, c->out_done[(c->batches - 1) & 1], 0);
+}
+
+hipError_t make_side_stream(dm_ctx* c)
+{
+    hipError_t e = hipSuccess;
+    if (!c->side_stream)
+        e = hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking);
+    for (hipEvent_t* ev : {&c->prep_done, &c->sel_done})
+        if (e == hipSuccess && !*ev)
+            e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
+    return e;
 }
 
 // Host checks shared by both routing entry points (what = the caller's name).
@@ -272,7 +283,7 @@ void dm_destroy(dm_ctx* c)
         return;
     DeviceGuard g(c->device);
     (void)hipStreamSynchronize(c->stream);
-    for (hipStream_t s : {c->work_stream, c->sel_stream, c->out_stream})
+    for (hipStream_t s : {c->work_stream, c->sel_stream, c->out_stream, c->side_stream})
         if (s)
             (void)hipStreamSynchronize(s);
     for (auto& b : c->ring)
@@ -288,7 +299,7 @@ void dm_destroy(dm_ctx* c)
     for (hipEvent_t ev : {c->in_ready, c->prep_done, c->sel_done, c->out_done[0], c->out_done[1]})
         if (ev)
             (void)hipEventDestroy(ev);
-    for (hipStream_t s : {c->work_stream, c->sel_stream, c->out_stream})
+    for (hipStream_t s : {c->work_stream, c->sel_stream, c->out_stream, c->side_stream})
         if (s)
             (void)hipStreamDestroy(s);
     (void)hipFree(c->d_hp);
@@ -690,40 +701,6 @@ dm_status dm_route_stage_ms(dm_ctx* c, float* ms, int n)
     return DM_OK;
 }
 
-// Streams of pipelined routing: the serial selection gets one compute unit
-// of its own and the work and output streams all the others, so that the
-// next batches' kernels never share the selection's unit.  Without CU
-// masks (a runtime that refuses them), plain streams are used.
-static hipError_t make_streams(dm_ctx* c)
-{
-    int cus = 0;
-    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
-    if (e != hipSuccess)
-        return e;
-    std::vector<uint32_t> one((cus + 31) / 32, 0u), rest((cus + 31) / 32, 0u);
-    for (int i = 0; i < cus; i++)
-        (i == 0 ? one : rest)[i / 32] |= 1u << (i % 32);
-    const bool masked = cus >= 2 &&
-        hipExtStreamCreateWithCUMask(&c->sel_stream, (uint32_t)one.size(), one.data()) == hipSuccess &&
-        hipExtStreamCreateWithCUMask(&c->work_stream, (uint32_t)rest.size(), rest.data()) == hipSuccess &&
-        hipExtStreamCreateWithCUMask(&c->out_stream, (uint32_t)rest.size(), rest.data()) == hipSuccess;
-    if (!masked) {
-        for (hipStream_t* s : {&c->work_stream, &c->sel_stream, &c->out_stream}) {
-            if (*s)
-                (void)hipStreamDestroy(*s);
-            *s = nullptr;
-        }
-        (void)hipGetLastError();
-        for (hipStream_t* s : {&c->work_stream, &c->sel_stream, &c->out_stream})
-            if (e == hipSuccess)
-                e = hipStreamCreateWithFlags(s, hipStreamNonBlocking);
-    }
-    for (hipEvent_t* ev : {&c->in_ready, &c->prep_done, &c->sel_done, &c->out_done[0], &c->out_done[1]})
-        if (e == hipSuccess)
-            e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
-    return e;
-}
-
 dm_status dm_keylen_enable(dm_ctx* c, uint64_t max_nodes, uint64_t max_window_blocks)
 {
     if (!c)
@@ -758,6 +735,40 @@ dm_status dm_set_policy(dm_ctx* c, int policy)
         return fail(c, DM_EINVAL, "dm_set_policy: unknown selection rule");
     c->policy = (uint32_t)policy;
     return DM_OK;
+}
+
+// Streams of pipelined routing: the serial selection gets one compute unit
+// of its own and the work and output streams all the others, so that the
+// next batches' kernels never share the selection's unit.  Without CU
+// masks (a runtime that refuses them), plain streams are used.
+static hipError_t make_streams(dm_ctx* c)
+{
+    int cus = 0;
+    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
+    if (e != hipSuccess)
+        return e;
+    std::vector<uint32_t> one((cus + 31) / 32, 0u), rest((cus + 31) / 32, 0u);
+    for (int i = 0; i < cus; i++)
+        (i == 0 ? one : rest)[i / 32] |= 1u << (i % 32);
+    const bool masked = cus >= 2 &&
+        hipExtStreamCreateWithCUMask(&c->sel_stream, (uint32_t)one.size(), one.data()) == hipSuccess &&
+        hipExtStreamCreateWithCUMask(&c->work_stream, (uint32_t)rest.size(), rest.data()) == hipSuccess &&
+        hipExtStreamCreateWithCUMask(&c->out_stream, (uint32_t)rest.size(), rest.data()) == hipSuccess;
+    if (!masked) {
+        for (hipStream_t* s : {&c->work_stream, &c->sel_stream, &c->out_stream}) {
+            if (*s)
+                (void)hipStreamDestroy(*s);
+            *s = nullptr;
+        }
+        (void)hipGetLastError();
+        for (hipStream_t* s : {&c->work_stream, &c->sel_stream, &c->out_stream})
+            if (e == hipSuccess)
+                e = hipStreamCreateWithFlags(s, hipStreamNonBlocking);
+    }
+    for (hipEvent_t* ev : {&c->in_ready, &c->prep_done, &c->sel_done, &c->out_done[0], &c->out_done[1]})
+        if (e == hipSuccess && !*ev)
+            e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
+    return e;
 }
 
 dm_status dm_set_pipelining(dm_ctx* c, int on)

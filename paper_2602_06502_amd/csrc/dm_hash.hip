@@ -82,6 +82,7 @@ struct HashArgs {
     const int32_t* tokens;
     const int64_t* offsets;
     uint64_t n;               // batch size (key_out, cand and match hold 2n entries)
+    uint64_t r0, r1;          // members: requests [r0, r1)
     const HashParams* hp;
     uint32_t key_blocks;
     uint32_t write_keys;      // members: store the block keys as well
@@ -401,8 +402,8 @@ struct alignas(16) MemberRec {
 };
 constexpr uint32_t kLeaderMark = 0xFFFFFFFFu;
 
-__global__ void member_record_kernel(const int64_t* __restrict__ offsets, uint64_t n,
-                                     uint32_t bshift, const uint64_t* __restrict__ bstart,
+__global__ void member_record_kernel(const int64_t* __restrict__ offsets, uint64_t n, uint64_t r0,
+                                     uint64_t r1, uint32_t bshift, const uint64_t* __restrict__ bstart,
                                      const uint32_t* bad_p, GroupView gv,
                                      const uint32_t* __restrict__ cand,
                                      const uint32_t* __restrict__ match,
@@ -412,7 +413,7 @@ __global__ void member_record_kernel(const int64_t* __restrict__ offsets, uint64
     const bool bad = *bad_p != 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *resume_count = 0;
-    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n;
+    for (uint64_t r = r0 + blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < r1;
          r += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t L = gv.leader[gv.group_of[r]];
         MemberRec m{};
@@ -533,8 +534,8 @@ __global__ __launch_bounds__(kHashThreads) void member_kernel(HashArgs a)
     // requests of this wave: its index, then every grid's worth of waves on
     // (one request per wave unless the batch has more than 4 Mi requests)
     const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-    uint64_t r = wave_index();
-    bool have = r < a.n;
+    uint64_t r = a.r0 + wave_index();
+    bool have = r < a.r1;
     RecRegs cur{};
     if (have)
         cur = load_rec(a.rec, r);
@@ -554,7 +555,7 @@ __global__ __launch_bounds__(kHashThreads) void member_kernel(HashArgs a)
     while (have) {
         // this request, then the wave's next one and its record
         const uint64_t rc = r, rn = r + nw;
-        const bool have_n = MULTI && rn < a.n;  // a grid of one request per wave has none
+        const bool have_n = MULTI && rn < a.r1;  // a grid of one request per wave has none
         RecRegs nxt{};
         if (have_n)
             nxt = load_rec(a.rec, rn);
@@ -651,7 +652,8 @@ __global__ __launch_bounds__(kHashThreads) void member_kernel(HashArgs a)
 // its kept keys of blocks [s, s + 8) in order up to the first absent one.
 // If all are present and blocks remain, the (request, candidate) goes to
 // the resume list (walked again from block s + 8 by walk_kernel<kResume>).
-__global__ void probe_pending_kernel(uint64_t n, const uint64_t* __restrict__ pend,
+__global__ void probe_pending_kernel(uint64_t n, uint64_t r0, uint64_t r1,
+                                     const uint64_t* __restrict__ pend,
                                      const MemberRec* __restrict__ rec,
                                      const uint64_t* __restrict__ pkeys,
                                      const uint32_t* __restrict__ cand,
@@ -659,7 +661,7 @@ __global__ void probe_pending_kernel(uint64_t n, const uint64_t* __restrict__ pe
                                      uint32_t* __restrict__ match, uint64_t* __restrict__ resume,
                                      unsigned long long* __restrict__ resume_count)
 {
-    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n;
+    for (uint64_t r = r0 + blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < r1;
          r += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t p = pend[r];  // nothing pending for leaders
         const uint32_t mask = (uint32_t)(p >> 32);
@@ -702,9 +704,10 @@ template <int B>
 hipError_t launch_members_b(dm_ctx* c, const HashArgs& a)
 {
     // one request per wave (the register-lean form, 8 waves per SIMD) unless
-    // the batch outnumbers the grid
-    const uint32_t grid = grid_for(a.n, kHashThreads / kWave, kHashBlocks);
-    if ((uint64_t)grid * (kHashThreads / kWave) < a.n)
+    // the range outnumbers the grid
+    const uint64_t m = a.r1 - a.r0;
+    const uint32_t grid = grid_for(m, kHashThreads / kWave, kHashBlocks);
+    if ((uint64_t)grid * (kHashThreads / kWave) < m)
         member_kernel<B, true><<<grid, kHashThreads, 0, c->stream>>>(a);
     else
         member_kernel<B, false><<<grid, kHashThreads, 0, c->stream>>>(a);
@@ -848,23 +851,33 @@ hipError_t hash_leaders(dm_ctx* c, const int32_t* tokens, const int64_t* offsets
 
 uint64_t member_scratch_bytes(uint64_t n) { return member_layout(n, nullptr, nullptr); }
 
-hipError_t hash_members(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
-                        const uint64_t* bstart, const uint32_t* bad, const GroupView& gv,
-                        const uint32_t* cand, uint64_t* hkeys, bool write_keys, uint32_t* match,
-                        const uint64_t* nh0)
+static hipError_t member_work(dm_ctx* c, uint64_t n, MemberWork* mw)
 {
     hipError_t e = hipSuccess;
     uint8_t* w = static_cast<uint8_t*>(scratch_get(c, kSlotMembers, member_scratch_bytes(n), &e));
-    if (!w)
-        return e;
+    if (w)
+        member_layout(n, w, mw);
+    return e;
+}
+
+hipError_t hash_members(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
+                        uint64_t r0, uint64_t m, int part, const uint64_t* bstart,
+                        const uint32_t* bad, const GroupView& gv, const uint32_t* cand,
+                        uint64_t* hkeys, bool write_keys, uint32_t* match, const uint64_t* nh0)
+{
     MemberWork mw;
-    member_layout(n, w, &mw);
+    hipError_t e = member_work(c, n, &mw);
+    if (e != hipSuccess)
+        return e;
     uint32_t bshift = 0;
     while ((1u << bshift) < c->cfg.block_size)
         bshift++;
-    member_record_kernel<<<grid_for(n, 256, 8192), 256, 0, c->stream>>>(
-        offsets, n, bshift, bstart, bad, gv, cand, match, mw.rec, mw.resume_count);
+    member_record_kernel<<<grid_for(m, 256, 8192), 256, 0, c->stream>>>(
+        offsets, n, r0, r0 + m, bshift, bstart, bad, gv, cand, match, mw.rec,
+        mw.resume_count + part);
     HashArgs a = base_args(c, tokens, offsets, n, bad);
+    a.r0 = r0;
+    a.r1 = r0 + m;
     a.bstart = bstart;
     a.hkeys = hkeys;
     a.write_keys = write_keys ? 1u : 0u;
@@ -875,15 +888,15 @@ hipError_t hash_members(dm_ctx* c, const int32_t* tokens, const int64_t* offsets
     a.rec = mw.rec;
     a.pkeys = mw.pkeys;
     a.pend = mw.pend;
-    a.resume = mw.resume;
-    a.resume_count = mw.resume_count;
+    a.resume = mw.resume + 2 * r0;  // at most two entries per request
+    a.resume_count = mw.resume_count + part;
     if ((e = launch_members(c, a)) != hipSuccess)
         return e;
-    probe_pending_kernel<<<grid_for(n, 256, 8192), 256, 0, c->stream>>>(
-        n, mw.pend, mw.rec, mw.pkeys, cand, c->d_tables, c->cfg.index_log2_slots, match,
-        mw.resume, mw.resume_count);
+    probe_pending_kernel<<<grid_for(m, 256, 8192), 256, 0, c->stream>>>(
+        n, r0, r0 + m, mw.pend, mw.rec, mw.pkeys, cand, c->d_tables, c->cfg.index_log2_slots,
+        match, mw.resume + 2 * r0, mw.resume_count + part);
     // the rare (request, candidate) whose kept keys were all present
-    return launch_walk<kResume>(c, a, grid_for(2 * n, kHashThreads / kWave, kLeaderBlocks));
+    return launch_walk<kResume>(c, a, grid_for(2 * m, kHashThreads / kWave, kLeaderBlocks));
 }
 
 }  // namespace dm

@@ -177,6 +177,7 @@ struct dm_ctx {
     dm::KeyLen kl;                          // adaptive hash-key length
     dm::KvRecord kv;                        // keys saved through dm_kv_save
     hipStream_t work_stream = nullptr, sel_stream = nullptr, out_stream = nullptr;
+    hipStream_t side_stream = nullptr;  // unpipelined: a first part's walk
     hipEvent_t in_ready = nullptr;                 // caller's stream: inputs of the batch
     hipEvent_t prep_done = nullptr;                // work stream: records packed
     hipEvent_t sel_done = nullptr;                 // selection stream: selection done
@@ -314,10 +315,12 @@ hipError_t hash_extend(dm_ctx* c, const int32_t* tokens, const int64_t* offsets,
 hipError_t hash_leaders(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                         const uint64_t* bstart, const uint32_t* bad, const GroupView& gv,
                         const uint32_t* cand, uint64_t* hkeys, uint32_t* match);
+//   hash_members takes requests [r0, r0 + m), the part-th range of the
+//     batch.
 hipError_t hash_members(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
-                        const uint64_t* bstart, const uint32_t* bad, const GroupView& gv,
-                        const uint32_t* cand, uint64_t* hkeys, bool write_keys, uint32_t* match,
-                        const uint64_t* nh0);
+                        uint64_t r0, uint64_t m, int part, const uint64_t* bstart,
+                        const uint32_t* bad, const GroupView& gv, const uint32_t* cand,
+                        uint64_t* hkeys, bool write_keys, uint32_t* match, const uint64_t* nh0);
 
 // dm_keylen.hip: the hotness tree's set-up, window close and export
 // (host entry points; they synchronise), and its release.
@@ -356,23 +359,39 @@ dm_status queue_reprobe(dm_ctx* c, const dm_queues* q, const int64_t* coff, cons
 hipError_t lookup_group(dm_ctx* c, uint64_t n, const uint64_t* key, const uint64_t* bstart,
                         const uint32_t* bad, uint32_t* cand, uint8_t* flags, GroupView* gv);
 
-// dm_select.hip: SLO-aware choice in request order; chosen, ttft_us and
-// flags bits 0-2 written, loads updated.  select_growth gives the batch's
-// growth bounds ([kMaxSlots + 1] words), whose first n_live and last word the
-// caller clears before select_prepare; select_prepare packs the batch's
-// records (no loads needed); select_run takes the loads' base and plan, walks
-// the batch on ss and writes the outputs on os (after an event when os is
-// another stream).  par picks one of two work-array sets.  select_batch is
-// both on one stream.
-hipError_t select_growth(dm_ctx* c, uint64_t n, int par, unsigned long long** grow);
+// dm_select.hip: the choice in request order; chosen, ttft_us and flags bits
+// 0-2 written, loads updated.  A batch is selected in one part, or in
+// two consecutive ones, the first one's walk beside the hashing of the
+// second; each part has its own work arrays (`at` bytes into the set).  select_growth gives a part's growth bounds ([kMaxSlots + 1] words),
+// whose first n_live and last word the caller clears before select_prepare;
+// select_prepare packs the part's records (no loads needed), select_walk
+// takes the loads' plan and walks the part, select_output writes its
+// results.  par picks one of two work-array sets.
+constexpr int kMaxParts = 2;
+struct SelPart {
+    uint64_t r0, m;          // requests [r0, r0 + m)
+    uint32_t block, wincap;  // requests per level block, windows per block
+    size_t at;
+};
+struct SelParts {
+    int count = 1;
+    size_t bytes = 0;
+    SelPart part[kMaxParts];
+};
+void select_parts(uint64_t n, bool pipelined, int parts, SelParts* out);
+hipError_t select_growth(dm_ctx* c, const SelParts& ps, int part, int par,
+                         unsigned long long** grow);
 hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uint64_t n,
-                          const dm_route_out* out, int par);
-hipError_t select_run(dm_ctx* c, hipStream_t ss, hipStream_t os, hipEvent_t sel_done,
-                      const int64_t* offsets, uint64_t n, const dm_route_out* out,
-                      int64_t* loads, int par);
-hipError_t select_batch(dm_ctx* c, hipStream_t st, const int64_t* offsets, uint64_t n,
-                        const dm_route_out* out, int64_t* loads);
+                          const dm_route_out* out, const SelParts& ps, int part, int par);
+hipError_t select_walk(dm_ctx* c, hipStream_t ss, const int64_t* offsets, uint64_t n,
+                       const dm_route_out* out, int64_t* loads, const SelParts& ps, int part,
+                       int par);
+hipError_t select_output(dm_ctx* c, hipStream_t os, const int64_t* offsets, uint64_t n,
+                         const dm_route_out* out, const SelParts& ps, int part, int par);
 
+// dm_api.hip: the side stream of an unpipelined batch that overlaps with
+// itself (with its two events), made at the first such batch.
+hipError_t make_side_stream(dm_ctx* c);
 // dm_api.hip: with pipelining on, make the context's stream wait for the
 // last selection (every call except dm_route_batch starts with this).
 hipError_t join_selection(dm_ctx* c);

@@ -18,7 +18,9 @@
 // two back), its serial selection on the selection stream (after the
 // batch's record packing and the previous selection), and the output
 // epilogue on the output stream; the next batch's hashing and probing thus
-// overlap this batch's selection.
+// overlap this batch's selection.  Unpipelined, a large batch overlaps with
+// itself (see kSplitTokens): the selection of its first requests runs beside
+// the hashing of the rest.
 #include "dm_internal.h"
 
 namespace dm {
@@ -26,22 +28,46 @@ namespace {
 
 constexpr int kKeySlot = kSlotKeys;  // block keys when the caller keeps none
 
+// Growth bounds of the selection's parts (those there are).
+struct Growth {
+    unsigned long long* of[kMaxParts];
+};
+
 // Clears the batch's malformed-offsets word, the tree's count and the
 // selection's growth bounds (a kernel rather than a memset, so that a
 // captured graph replays it like the rest of the batch).
 __global__ __launch_bounds__(256) void route_zero_kernel(uint32_t* bad,
                                                          unsigned long long* ext_count,
-                                                         unsigned long long* grow, uint32_t n_live)
+                                                         Growth grow, uint32_t n_live)
 {
-    for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
-        grow[k] = 0;
+    for (int p = 0; p < kMaxParts; p++) {
+        if (!grow.of[p])
+            break;
+        for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
+            grow.of[p][k] = 0;
+        if (threadIdx.x == 0)
+            grow.of[p][kMaxSlots] = 0;
+    }
     if (threadIdx.x == 0) {
-        grow[kMaxSlots] = 0;
         *bad = 0;
         if (ext_count)
             *ext_count = 0;
     }
 }
+
+// An unpipelined batch of at least kSplitTokens tokens (and kSplitFrom
+// requests) is selected in two parts: the walk of the first, one wave on one
+// SIMD, runs on a side stream beside the hashing of the second.  The walk
+// claims a whole SIMD's registers, so it starts only on an empty one: its
+// records are ready before the second part's member records are written, and
+// in the gap between that kernel and the hashing it finds one.  A first part
+// of a quarter walks about as long as the rest hashes (a fifth and three
+// tenths measured 2 and 1% longer).  The two streams' events cost some 130 us,
+// the time in which three quarters of 200 M tokens are hashed.  In one part
+// and in two: 1,048,576 requests (1.75 G tokens) 7.58 and 6.51 ms, 262,144
+// (438 M) 2.03 and 1.80 ms, 131,072 with the hotness tree (219 M) 2.55 and
+// 2.49 ms, 65,536 (109 M) 0.61 and 0.67 ms.
+constexpr uint64_t kSplitTokens = 200000000, kSplitFrom = 1u << 13;
 
 }  // namespace
 
@@ -96,12 +122,15 @@ void route_scratch_plan(const dm_ctx* c, uint64_t n, uint64_t n_tokens, bool key
                                 keylen_record_bytes(n);
 }
 
-hipError_t route(dm_ctx* c, const int32_t* tokens, uint64_t n_tokens, const int64_t* offsets,
-                 uint64_t n, int64_t* loads, const dm_route_out* out)
+static hipError_t route_parts(dm_ctx* c, const int32_t* tokens, uint64_t n_tokens,
+                              const int64_t* offsets, uint64_t n, int64_t* loads,
+                              const dm_route_out* out, bool split)
 {
     hipError_t e = hipSuccess;
     const bool pipe = c->pipelined;
     const int par = pipe ? (int)(c->batches & 1) : 0;
+    SelParts ps;
+    select_parts(n, pipe, split ? 2 : 1, &ps);
     if (pipe) {
         if ((e = hipEventRecord(c->in_ready, c->stream)) != hipSuccess ||
             (e = hipStreamWaitEvent(c->work_stream, c->in_ready, 0)) != hipSuccess)
@@ -145,9 +174,10 @@ hipError_t route(dm_ctx* c, const int32_t* tokens, uint64_t n_tokens, const int6
         ext_list = reinterpret_cast<uint32_t*>(w + 256);
         kl_work = reinterpret_cast<uint64_t*>(w + 256 + list_bytes);
     }
-    unsigned long long* grow = nullptr;
-    if ((e = select_growth(c, n, par, &grow)) != hipSuccess)
-        return e;
+    Growth grow{};
+    for (int k = 0; k < ps.count; k++)
+        if ((e = select_growth(c, ps, k, par, &grow.of[k])) != hipSuccess)
+            return e;
     route_zero_kernel<<<1, 256, 0, st>>>(bad, ext_count, grow, c->n_live);
     if ((e = block_starts(c, offsets, n, n_tokens, bstart, bad)) != hipSuccess)
         return e;
@@ -177,34 +207,62 @@ hipError_t route(dm_ctx* c, const int32_t* tokens, uint64_t n_tokens, const int6
     if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess)
         return e;
     if ((e = hash_leaders(c, tokens, offsets, n, bstart, bad, gv, out->cand, hkeys, out->match)) !=
-            hipSuccess ||
-        (e = hash_members(c, tokens, offsets, n, bstart, bad, gv, out->cand, hkeys, write_keys,
-                          out->match, nh0)) != hipSuccess)
+        hipSuccess)
         return e;
-    if (c->kl.on) {
-        if ((e = keylen_record(c, n, bstart, hkeys, kl_work)) != hipSuccess)
+    auto order = [&](hipStream_t waits, hipEvent_t event, hipStream_t on) -> hipError_t {
+        if (waits == on)
+            return hipSuccess;
+        const hipError_t r = hipEventRecord(event, on);
+        return r != hipSuccess ? r : hipStreamWaitEvent(waits, event, 0);
+    };
+    for (int k = 0; k < ps.count; k++) {
+        const SelPart& q = ps.part[k];
+        const bool last = k + 1 == ps.count;
+        if ((e = hash_members(c, tokens, offsets, n, q.r0, q.m, k, bstart, bad, gv, out->cand,
+                              hkeys, write_keys, out->match, nh0)) != hipSuccess)
             return e;
-        c->kl.win += n;
-    }
-    if (ev && (e = hipEventRecord(ev[3], st)) != hipSuccess)
-        return e;
-    if ((e = select_prepare(c, st, offsets, n, out, par)) != hipSuccess)
-        return e;
-    if (!pipe) {
-        if ((e = select_run(c, st, st, nullptr, offsets, n, out, loads, 0)) != hipSuccess)
+        if (last && c->kl.on) {
+            if ((e = keylen_record(c, n, bstart, hkeys, kl_work)) != hipSuccess)
+                return e;
+            c->kl.win += n;
+        }
+        if (last && ev && (e = hipEventRecord(ev[3], st)) != hipSuccess)
             return e;
-        return ev ? hipEventRecord(ev[4], st) : hipSuccess;
+        if ((e = select_prepare(c, st, offsets, n, out, ps, k, par)) != hipSuccess)
+            return e;
+        // the walks in order: a first part's on the side stream, the last
+        // part's after it (pipelined: all on the selection stream)
+        const hipStream_t ss = pipe ? c->sel_stream : last ? st : c->side_stream;
+        if ((e = order(ss, c->prep_done, st)) != hipSuccess ||
+            (split && last && (e = order(st, c->sel_done, c->side_stream)) != hipSuccess) ||
+            (e = select_walk(c, ss, offsets, n, out, loads, ps, k, par)) != hipSuccess)
+            return e;
     }
-    if ((e = hipEventRecord(c->prep_done, st)) != hipSuccess ||
-        (e = hipStreamWaitEvent(c->sel_stream, c->prep_done, 0)) != hipSuccess)
+    const hipStream_t os = pipe ? c->out_stream : st;
+    if (pipe && (e = order(os, c->sel_done, c->sel_stream)) != hipSuccess)
         return e;
-    if ((e = select_run(c, c->sel_stream, c->out_stream, c->sel_done, offsets, n, out, loads,
-                        par)) != hipSuccess)
-        return e;
-    if ((e = hipEventRecord(c->out_done[par], c->out_stream)) != hipSuccess)
-        return e;
-    c->batches++;
-    return ev ? hipEventRecord(ev[4], c->out_stream) : hipSuccess;
+    for (int k = 0; k < ps.count; k++)
+        if ((e = select_output(c, os, offsets, n, out, ps, k, par)) != hipSuccess)
+            return e;
+    if (pipe) {
+        if ((e = hipEventRecord(c->out_done[par], os)) != hipSuccess)
+            return e;
+        c->batches++;
+    }
+    return ev ? hipEventRecord(ev[4], os) : hipSuccess;
+}
+
+hipError_t route(dm_ctx* c, const int32_t* tokens, uint64_t n_tokens, const int64_t* offsets,
+                 uint64_t n, int64_t* loads, const dm_route_out* out)
+{
+    const bool split = !c->pipelined && !c->arena.on && n_tokens >= kSplitTokens &&
+                       n >= kSplitFrom && !stream_capturing(c);
+    hipError_t e = split ? make_side_stream(c) : hipSuccess;
+    if (e == hipSuccess)
+        e = route_parts(c, tokens, n_tokens, offsets, n, loads, out, split);
+    if (split && e != hipSuccess)
+        (void)sync_streams(c);  // nothing stays running behind the caller's stream
+    return e;
 }
 
 }  // namespace dm

@@ -73,9 +73,11 @@ __device__ __forceinline__ bool pick_first(uint32_t kind, int64_t L1, int64_t L2
 }
 
 // One batch and its rule, as the walk and the epilogue read them.
+// Requests 0..n-1 here are one part of the batch; the second candidates and
+// matches lie `second` entries after the first ones.
 struct SelArgs {
     const int64_t* offsets;
-    uint64_t n;
+    uint64_t n, second;
     uint32_t bshift;
     const uint32_t* cand;
     const uint32_t* match;
@@ -103,8 +105,8 @@ __device__ __forceinline__ SelRec load_rec(const SelArgs& g, uint64_t r, bool ok
 {
     SelRec s;
     s.c1 = ok ? g.cand[r] : 0;
-    s.c2 = ok ? g.cand[g.n + r] : 0;
-    const uint32_t m1 = ok ? g.match[r] : 0, m2 = ok ? g.match[g.n + r] : 0;
+    s.c2 = ok ? g.cand[g.second + r] : 0;
+    const uint32_t m1 = ok ? g.match[r] : 0, m2 = ok ? g.match[g.second + r] : 0;
     const int64_t len = ok ? g.offsets[r + 1] - g.offsets[r] : 0;
     s.u1 = len - ((int64_t)m1 << g.bshift);
     s.u2 = len - ((int64_t)m2 << g.bshift);
@@ -252,7 +254,7 @@ constexpr uint32_t kSets = 2;
 // grow[kMaxSlots] is set by a record whose counts do not fit 32 bits.  Both
 // start at zero.
 __global__ __launch_bounds__(256) void sel_prep_kernel(
-    const int64_t* __restrict__ offsets, uint64_t n, uint32_t bshift,
+    const int64_t* __restrict__ offsets, uint64_t n, uint64_t second, uint32_t bshift,
     const uint32_t* __restrict__ cand, const uint32_t* __restrict__ match,
     const uint32_t* __restrict__ dense, uint32_t n_live, int64_t tbase, int64_t per,
     uint32_t qshift, int64_t slo, uint32_t policy, SelPack* __restrict__ rec,
@@ -265,14 +267,14 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
     unsigned long long bad = 0;
     for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n;
          r += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t m1 = match[r], m2 = match[n + r];
+        const uint32_t m1 = match[r], m2 = match[second + r];
         const int64_t len = offsets[r + 1] - offsets[r];
         const int64_t u1 = len - ((int64_t)m1 << bshift), u2 = len - ((int64_t)m2 << bshift);
         // least load: every request as an equal match, c1 as "a"
         const bool eq = m1 == m2 || policy == DM_POLICY_LEAST_LOADED;
         const bool aff2 = m2 > m1 && policy != DM_POLICY_LEAST_LOADED &&
                           policy != DM_POLICY_MIN_TTFT;
-        const uint32_t d1 = dense[cand[r]], d2 = dense[cand[n + r]];
+        const uint32_t d1 = dense[cand[r]], d2 = dense[cand[second + r]];
         // T_a <= slo  <=>  floor(L_a / 2^q) <= slo - tbase - per*u_a  <=>
         // L_a < (slo - tbase - per*u_a + 1) 2^q, i.e. "take a iff L_a <=
         // max(th, L_o)" with th one less.  The 32-bit walk uses absolute loads
@@ -361,19 +363,16 @@ static_assert(LevelShape<2048>::block == kSelBlock &&
                   LevelShape<2048>::wincap == kSelWindowsPerBlock &&
                   kLargeFrom / 1024 * LevelShape<1024>::wincap * kSets * kWave < (1ull << 32),
               "dm_route_batch's batch limit assumes this layout");
-// A batch's work arrays have one size whichever of the two smaller layouts
-// it takes (see sel_sizes).
-static_assert(4 * LevelShape<256>::wincap == LevelShape<1024>::wincap, "windows per 1024 requests");
-
-// Block size and window capacity of a batch of n requests.
+// Block size and window capacity of a batch of n requests; hidden: the level
+// kernel runs beside an earlier walk.
 struct BlockShape {
     uint32_t block, wincap;
 };
-static BlockShape block_shape(uint64_t n, bool pipelined)
+static BlockShape block_shape(uint64_t n, bool hidden)
 {
     if (n >= kLargeFrom)
         return BlockShape{LevelShape<2048>::block, LevelShape<2048>::wincap};
-    if (n <= kSmallTo && !pipelined)
+    if (n <= kSmallTo && !hidden)
         return BlockShape{LevelShape<256>::block, LevelShape<256>::wincap};
     return BlockShape{LevelShape<1024>::block, LevelShape<1024>::wincap};
 }
@@ -1195,22 +1194,20 @@ struct SelBuf {
 
 static size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Sizes of one set's arrays for a batch of n requests, in layout order.
-static void sel_sizes(uint64_t n, size_t* sizes)
+// Sizes of the arrays of m requests in blocks of bs, in layout order.
+static void sel_sizes(uint64_t m, BlockShape bs, size_t* sizes)
 {
-    const BlockShape bs = block_shape(n, true);
-    const uint64_t nblk = (n + bs.block - 1) / bs.block;
+    const uint64_t nblk = (m + bs.block - 1) / bs.block;
     const uint64_t wcap = nblk * bs.wincap;
-    const uint64_t counts = n <= kSmallTo ? 4 * nblk : nblk;  // blocks of 256 included
     const size_t z[] = {
-        up256(n * sizeof(SelPack)),                                  // prep
+        up256(m * sizeof(SelPack)),                                  // prep
         up256((wcap + 2 * kPrefetch) * kSets * kWave * sizeof(WalkRec)),  // rec
         up256((wcap + kPrefetch) * kSets * kWave * sizeof(longlong2)),    // lpre
-        up256(n * sizeof(uint32_t)),                                 // info
-        up256(n * sizeof(uint32_t)),                                 // slot_of
+        up256(m * sizeof(uint32_t)),                                 // info
+        up256(m * sizeof(uint32_t)),                                 // slot_of
         up256(wcap * kSets * kWave * sizeof(uint16_t)),              // slotmap
         up256(wcap),                                                 // wdepth
-        up256(counts),                                               // wcount
+        up256(nblk),                                                 // wcount
         nblk > kScanFrom ? up256(nblk * sizeof(uint32_t)) : 0,       // woff
         256 + 256 + (kMaxSlots + 1) * sizeof(unsigned long long),   // total, base/plan, grow
     };
@@ -1218,41 +1215,67 @@ static void sel_sizes(uint64_t n, size_t* sizes)
         sizes[i] = z[i];
 }
 
-uint64_t select_scratch_bytes(uint64_t n)
+// The last array's size is no multiple of 256: sets and parts start aligned.
+static uint64_t sel_bytes(uint64_t m, BlockShape bs)
 {
     size_t sizes[10], one = 0;
-    sel_sizes(n, sizes);
+    sel_sizes(m, bs, sizes);
     for (size_t z : sizes)
         one += z;
     return one;
 }
 
-static hipError_t sel_buffers(dm_ctx* c, uint64_t n, int par, SelBuf* b)
+uint64_t select_scratch_bytes(uint64_t n) { return sel_bytes(n, block_shape(n, false)); }
+
+// Parts of a batch: the level blocks of a first part of two are those of an
+// unpipelined batch (its walk waits for them), but for the shortest; the
+// second part's level kernel runs beside the first one's walk.
+void select_parts(uint64_t n, bool pipelined, int parts, SelParts* out)
+{
+    out->count = parts;
+    out->bytes = 0;
+    uint64_t r0 = 0;
+    for (int k = 0; k < parts; k++) {
+        const uint64_t end = k + 1 == parts ? n : n / 4 & ~(kSelBlock - 1);
+        SelPart& q = out->part[k];
+        q.r0 = r0;
+        q.m = end - r0;
+        r0 = end;
+        const BlockShape bs = parts == 1 ? block_shape(n, pipelined)
+                              : k == 0   ? block_shape(std::min(q.m, kLargeFrom - 1), false)
+                                         : block_shape(n, true);
+        q.block = bs.block;
+        q.wincap = bs.wincap;
+        q.at = out->bytes;
+        out->bytes += up256(sel_bytes(q.m, bs));
+    }
+}
+
+static hipError_t sel_buffers(dm_ctx* c, const SelParts& ps, const SelPart& q, int par, SelBuf* b)
 {
     hipError_t e = hipSuccess;
-    b->shape = block_shape(n, c->pipelined);
-    b->nblk = (n + b->shape.block - 1) / b->shape.block;
-    b->nslots = b->nblk * b->shape.wincap * kSets * kWave;
+    b->shape = BlockShape{q.block, q.wincap};
+    b->nblk = (q.m + q.block - 1) / q.block;
+    b->nslots = b->nblk * q.wincap * kSets * kWave;
     size_t sizes[10];
-    sel_sizes(n, sizes);
-    const size_t one = select_scratch_bytes(n);
+    sel_sizes(q.m, b->shape, sizes);
     uint8_t* sw = nullptr;
     if (c->arena.on) {
-        // allocation-free call: unpipelined, one set
-        sw = static_cast<uint8_t*>(scratch_get(c, kSelSlot, one, &e));
+        // allocation-free call: unpipelined, one set, one part
+        sw = static_cast<uint8_t*>(scratch_get(c, kSelSlot, sel_bytes(q.m, b->shape), &e));
     } else {
         // The two sets sit sel_stride apart whatever this batch's size: a
         // smaller batch must not move its set into the other parity's, which
         // the batch before it may still be walking.  A larger batch widens
         // the stride only once every stream is idle.
-        if (one > c->sel_stride) {
+        if (ps.bytes > c->sel_stride) {
             if ((e = sync_streams(c)) != hipSuccess)
                 return e;
-            c->sel_stride = one;
+            c->sel_stride = ps.bytes;
         }
         sw = static_cast<uint8_t*>(scratch_get(c, kSelSlot, 2 * c->sel_stride, &e));
         if (sw)
-            sw += par * c->sel_stride;
+            sw += par * c->sel_stride + q.at;
     }
     if (!sw)
         return e;
@@ -1286,34 +1309,51 @@ static uint32_t block_shift(const dm_ctx* c)
     return bshift;
 }
 
-hipError_t select_growth(dm_ctx* c, uint64_t n, int par, unsigned long long** grow)
+hipError_t select_growth(dm_ctx* c, const SelParts& ps, int k, int par, unsigned long long** grow)
 {
     SelBuf b;
-    const hipError_t e = sel_buffers(c, n, par, &b);
+    const hipError_t e = sel_buffers(c, ps, ps.part[k], par, &b);
     *grow = b.grow;
     return e;
 }
 
+// The part's requests as the kernels read them.
+static SelArgs part_args(const dm_ctx* c, const int64_t* offsets, uint64_t n, const SelPart& q,
+                         const dm_route_out* out, int64_t* loads)
+{
+    const dm_config& k = c->cfg;
+    return SelArgs{offsets + q.r0,     q.m,
+                   n,                  block_shift(c),
+                   out->cand + q.r0,   out->match + q.r0,
+                   out->flags + q.r0,  out->chosen + q.r0,
+                   out->ttft_us + q.r0, loads,
+                   c->d_live_ids,      c->n_live,
+                   k.max_slots,        k.ttft_base_us,
+                   k.ttft_per_token_us, c->shift_div,
+                   k.slo_us,           c->policy};
+}
+
 hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uint64_t n,
-                          const dm_route_out* out, int par)
+                          const dm_route_out* out, const SelParts& ps, int part, int par)
 {
     SelBuf b;
-    hipError_t e = sel_buffers(c, n, par, &b);
+    const SelPart& q = ps.part[part];
+    hipError_t e = sel_buffers(c, ps, q, par, &b);
     if (e != hipSuccess)
         return e;
     const uint64_t fill_waves = (b.nblk * b.shape.wincap + 2 * kPrefetch) * kSets;
     if (b.nblk > 0x7FFFFFFFull || fill_waves > 0x7FFFFFFFull)
         return hipErrorInvalidValue;
     const uint32_t NL = c->n_live;
-    const dm_config& k = c->cfg;
+    const SelArgs g = part_args(c, offsets, n, q, out, nullptr);
     // few workgroups: each adds its per-instance growth sums to the global
     // ones with one atomic per instance, and those atomics meet on a few lines
-    sel_prep_kernel<<<grid_for(n, 256, 512), 256, NL * sizeof(unsigned long long), st>>>(
-        offsets, n, block_shift(c), out->cand, out->match, c->d_dense, NL, k.ttft_base_us,
-        k.ttft_per_token_us, c->shift_div, k.slo_us, c->policy, b.prep, b.grow);
+    sel_prep_kernel<<<grid_for(q.m, 256, 512), 256, NL * sizeof(unsigned long long), st>>>(
+        g.offsets, g.n, g.second, g.bshift, g.cand, g.match, c->d_dense, NL, g.tbase, g.per,
+        g.qshift, g.slo, g.policy, b.prep, b.grow);
     if (b.nblk > 0) {
         auto level = [&](auto kernel) {
-            kernel<<<(uint32_t)b.nblk, kWave, 0, st>>>(b.prep, n, b.info, b.slotmap, b.wdepth,
+            kernel<<<(uint32_t)b.nblk, kWave, 0, st>>>(b.prep, q.m, b.info, b.slotmap, b.wdepth,
                                                        b.wcount, c->d_status);
         };
         auto sized = [&](auto live) {
@@ -1334,48 +1374,40 @@ hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uin
     if (scan)
         sel_scan_kernel<<<1, 1024, 0, st>>>(b.wcount, b.nblk, b.woff, b.total);
     sel_fill_kernel<<<(uint32_t)((fill_waves + 3) / 4), 4 * kWave, 0, st>>>(
-        b.prep, n, b.info, b.slotmap, b.wdepth, b.wcount, scan ? b.woff : nullptr, b.total, b.nblk,
-        b.shape, b.rec, b.slot_of);
+        b.prep, q.m, b.info, b.slotmap, b.wdepth, b.wcount, scan ? b.woff : nullptr, b.total,
+        b.nblk, b.shape, b.rec, b.slot_of);
     return hipGetLastError();
 }
 
-hipError_t select_run(dm_ctx* c, hipStream_t ss, hipStream_t os, hipEvent_t sel_done,
-                      const int64_t* offsets, uint64_t n, const dm_route_out* out,
-                      int64_t* loads, int par)
+hipError_t select_walk(dm_ctx* c, hipStream_t ss, const int64_t* offsets, uint64_t n,
+                       const dm_route_out* out, int64_t* loads, const SelParts& ps, int part,
+                       int par)
 {
     SelBuf b;
-    hipError_t e = sel_buffers(c, n, par, &b);
+    hipError_t e = sel_buffers(c, ps, ps.part[part], par, &b);
     if (e != hipSuccess)
         return e;
-    const dm_config& k = c->cfg;
-    const SelArgs g{offsets, n, block_shift(c), out->cand, out->match, out->flags, out->chosen,
-                    out->ttft_us, loads, c->d_live_ids, c->n_live, k.max_slots, k.ttft_base_us,
-                    k.ttft_per_token_us, c->shift_div, k.slo_us, c->policy};
+    const SelArgs g = part_args(c, offsets, n, ps.part[part], out, loads);
     if (c->policy == DM_POLICY_MIN_TTFT)
         select_walk_kernel<true><<<1, kWave, 0, ss>>>(g, b.rec, b.total, b.grow, b.plan, b.base,
                                                       b.lpre);
     else
         select_walk_kernel<false><<<1, kWave, 0, ss>>>(g, b.rec, b.total, b.grow, b.plan, b.base,
                                                        b.lpre);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    if (os != ss) {
-        if ((e = hipEventRecord(sel_done, ss)) != hipSuccess ||
-            (e = hipStreamWaitEvent(os, sel_done, 0)) != hipSuccess)
-            return e;
-    }
-    sel_out_kernel<<<grid_for(n, 256, 8192), 256, 0, os>>>(g, b.lpre, b.slot_of, b.nslots, b.base,
-                                                           b.plan);
     return hipGetLastError();
 }
 
-hipError_t select_batch(dm_ctx* c, hipStream_t st, const int64_t* offsets, uint64_t n,
-                        const dm_route_out* out, int64_t* loads)
+hipError_t select_output(dm_ctx* c, hipStream_t os, const int64_t* offsets, uint64_t n,
+                         const dm_route_out* out, const SelParts& ps, int part, int par)
 {
-    hipError_t e = select_prepare(c, st, offsets, n, out, 0);
-    if (e == hipSuccess)
-        e = select_run(c, st, st, nullptr, offsets, n, out, loads, 0);
-    return e;
+    SelBuf b;
+    hipError_t e = sel_buffers(c, ps, ps.part[part], par, &b);
+    if (e != hipSuccess)
+        return e;
+    const SelArgs g = part_args(c, offsets, n, ps.part[part], out, nullptr);
+    sel_out_kernel<<<grid_for(g.n, 256, 8192), 256, 0, os>>>(g, b.lpre, b.slot_of, b.nslots, b.base,
+                                                             b.plan);
+    return hipGetLastError();
 }
 
 }  // namespace dm

@@ -93,3 +93,45 @@ def test_small_level_blocks(n_inst, n_req):
     wl = workloads.small_random(131 + n_inst, n_inst, 4, 16, n_req, slo_us=3_000)
     wl = dataclasses.replace(wl, n_prior=300)
     _pair(wl, workloads.initial_loads(wl, wl.route.max_slots))
+
+
+@pytest.mark.parametrize("n_req,mean,kl", [(8192, 24_500, False), (20_000, 10_100, True), (33_333, 6100, False)])
+def test_batch_overlapping_itself(n_req, mean, kl):
+    """Unpipelined batches of at least 200 M tokens are selected in two parts beside
+    the hashing: outputs, loads, block keys and the hotness tree's windows
+    against the oracle, twice in a row on the same buffers."""
+    import paper_2602_06502_amd.harness as gh
+    B = 16
+    wl = workloads.small_random(7, 40, 8, B, 64, slo_us=30_000)
+    eng, o = gh.engine_for(wl), oh.oracle_for(wl)
+    rng = np.random.default_rng(n_req)
+    tpl = [rng.integers(0, 1 << 20, size=B * 90, dtype=np.int32) for _ in range(12)]
+    lens = rng.integers(mean // 2, mean * 3 // 2 + 200, size=n_req)
+    off = np.zeros(n_req + 1, np.int64)
+    off[1:] = np.cumsum(lens)
+    tok = rng.integers(0, 1 << 20, size=int(off[-1]), dtype=np.int32)
+    for r in range(n_req):
+        t = tpl[int(rng.integers(0, 12))]
+        k = min(len(t), int(lens[r]))
+        tok[off[r]:off[r] + k] = t[:k]
+    assert len(tok) >= 200_000_000
+    if kl:
+        eng.keylen_enable(4096, int((lens // B).sum()) + n_req)
+        assert o.keylen_enable(4096) == oracle.OK
+    L = workloads.initial_loads(wl, wl.route.max_slots)
+    Ld = gh.to_dev(L, eng.device)
+    td, od = gh.to_dev(tok, eng.device), gh.to_dev(off, eng.device)
+    for step in range(2):
+        print("[case] overlap", n_req, len(tok), step, flush=True)
+        g = eng.route(td, od, Ld, block_keys=True)
+        g2 = {k: v.clone() for k, v in g.items()}  # on the caller's stream, no wait
+        r = o.route(tok, off, L, block_keys=True)
+        for k in ("key", "cand", "match", "chosen", "ttft", "flags", "key_len", "block_keys"):
+            assert np.array_equal(g2[k].cpu().numpy()[:len(r[k])], r[k]), k
+        assert np.array_equal(Ld.cpu().numpy(), r["loads"])
+        L = r["loads"]
+        if kl:
+            eng.keylen_window()
+            assert o.keylen_window() == oracle.OK
+            assert np.array_equal(eng.keylen_tree(), o.keylen_tree())
+    eng.sync()
