@@ -255,6 +255,8 @@ dm_status dm_create(const dm_config* cfg, void* hip_stream, dm_ctx** out)
     if (e == hipSuccess) e = hipMalloc(&c->d_counts, 2 * S * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMalloc(&c->d_status, sizeof(uint32_t));
     if (e == hipSuccess)
+        e = hipHostMalloc(reinterpret_cast<void**>(&c->host_words), 4096, hipHostMallocDefault);
+    if (e == hipSuccess)
         e = hipMemcpyAsync(c->d_hp, &c->hp, sizeof(HashParams), hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
         e = hipMemsetAsync(c->d_tables, 0, table_slots * sizeof(uint64_t), c->stream);
@@ -311,6 +313,7 @@ void dm_destroy(dm_ctx* c)
     (void)hipFree(c->d_tables);
     (void)hipFree(c->d_counts);
     (void)hipFree(c->d_status);
+    (void)hipHostFree(c->host_words);
     delete c;
 }
 
@@ -560,13 +563,9 @@ dm_status dm_rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out,
     DeviceGuard g(c->device);
     if (hipError_t je = join_selection(c); je != hipSuccess)
         return hip_fail(c, je, "dm_rebalance");
-    // The record count sizes the work arrays: read qoff[max_slots].
+    // The record count sizes the work arrays.
     int64_t Qs = 0, q0 = 0;
-    hipError_t e = hipStreamSynchronize(c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpy(&Qs, q->qoff + c->cfg.max_slots, sizeof(int64_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess)
-        e = hipMemcpy(&q0, q->qoff, sizeof(int64_t), hipMemcpyDeviceToHost);
+    hipError_t e = queue_ends(c, q->qoff, &q0, &Qs);
     if (e != hipSuccess)
         return hip_fail(c, e, "dm_rebalance");
     if (q0 != 0 || Qs < 0 || Qs >= (1ll << 32))

@@ -146,6 +146,9 @@ struct dm_ctx {
     uint64_t* d_tables = nullptr;  // [max_slots << log2slots]
     uint64_t* d_counts = nullptr;  // [2 * max_slots] live keys, then occupied slots
     uint32_t* d_status = nullptr;  // device status word
+    // pinned host words that a call's kernels write and the call reads once it
+    // has waited for the stream
+    uint64_t* host_words = nullptr;
     // [max_slots] most slots of each index that can be occupied (dm_index.hip);
     // UINT64_MAX: not known
     std::vector<uint64_t> occ_bound;
@@ -401,6 +404,8 @@ hipError_t route(dm_ctx* c, const int32_t* tokens, uint64_t n_tokens, const int6
                  uint64_t n, int64_t* loads, const dm_route_out* out);
 
 // dm_rebalance.hip
+// qoff[0] and qoff[max_slots], once the stream has come this far.
+hipError_t queue_ends(dm_ctx* c, const int64_t* qoff, int64_t* first, int64_t* last);
 hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm_migrations* out,
                      uint64_t cap, uint64_t Q);
 

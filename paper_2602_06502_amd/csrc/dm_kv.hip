@@ -151,6 +151,16 @@ __global__ __launch_bounds__(1024) void kv_region_kernel(const uint32_t* __restr
         first[S] = (uint32_t)(part[1023] < 0xFFFFFFFFull ? part[1023] : 0xFFFFFFFFull);
 }
 
+// The checks' word, the table's tiles and the batch's blocks, to pinned host
+// memory.
+__global__ void kv_post_kernel(const uint32_t* __restrict__ bad, const uint32_t* __restrict__ tiles,
+                               const uint64_t* __restrict__ blocks, uint64_t* __restrict__ host)
+{
+    host[0] = *bad;
+    host[1] = *tiles;
+    host[2] = blocks ? *blocks : 0;
+}
+
 __global__ void kv_zero_kernel(unsigned long long* __restrict__ p, uint64_t n)
 {
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
@@ -703,13 +713,11 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
         kv_check_kernel<<<grid_for(n, 256, 256), 256, S * sizeof(unsigned long long), st>>>(
             inst, n, S, bstart, bad, touches);
     kv_region_kernel<<<1, 1024, 0, st>>>(rec.count, touches, S, first);
-    uint64_t E = 0;
-    uint32_t badh = 0, tiles = 0;
-    if ((e = hipMemcpyAsync(&badh, bad, 4, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipMemcpyAsync(&tiles, first + S, 4, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (n && (e = hipMemcpyAsync(&E, bstart + n, 8, hipMemcpyDeviceToHost, st)) != hipSuccess) ||
-        (e = hipStreamSynchronize(st)) != hipSuccess)
+    kv_post_kernel<<<1, 1, 0, st>>>(bad, first + S, n ? bstart + n : nullptr, c->host_words);
+    if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
         return failed(e);
+    const uint32_t badh = (uint32_t)c->host_words[0], tiles = (uint32_t)c->host_words[1];
+    const uint64_t E = c->host_words[2];
     if (badh & 2)
         return fail(c, DM_EINVAL, "dm_kv_save: an instance id is >= max_slots");
     if (badh)
@@ -756,6 +764,7 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
     s.same = carve<uint32_t>(w, S);
     o.fits = carve<uint32_t>(w, S);
     o.occ = carve<uint64_t>(w, S);
+    uint8_t* const results = reinterpret_cast<uint8_t*>(o.fits);
     const int a = rec.cur, b = 1 - a;
     const uint64_t room = cap && cap < (1ull << 32) ? std::min<uint64_t>(M, cap * S) : M;
     if ((e = kv_reserve(c, room)) != hipSuccess)
@@ -803,36 +812,39 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
                                                      c->d_counts, log2slots, c->d_status);
     if ((e = hipGetLastError()) != hipSuccess)
         return failed(e);
-    std::vector<uint32_t> ins(S), fits(S);
-    std::vector<uint64_t> occ(S);
-    uint64_t sum[4] = {0, 0, 0, 0};
-    if ((e = hipMemcpyAsync(sum, o.sum, 32, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipMemcpyAsync(ins.data(), o.ins, 4 * (size_t)S, hipMemcpyDeviceToHost, st)) !=
+    // two copies: keys to insert with the totals, room with occupied slots
+    const size_t insb = up256v(4 * (size_t)S), occb = 8 * (size_t)S;
+    std::vector<uint64_t> head_h((insb + 64) / 8), tail_h((insb + occb) / 8);
+    if ((e = hipMemcpyAsync(head_h.data(), o.ins, insb + 64, hipMemcpyDeviceToHost, st)) !=
             hipSuccess ||
-        (e = hipMemcpyAsync(fits.data(), o.fits, 4 * (size_t)S, hipMemcpyDeviceToHost, st)) !=
-            hipSuccess ||
-        (e = hipMemcpyAsync(occ.data(), o.occ, 8 * (size_t)S, hipMemcpyDeviceToHost, st)) !=
+        (e = hipMemcpyAsync(tail_h.data(), results, insb + occb, hipMemcpyDeviceToHost, st)) !=
             hipSuccess ||
         (e = hipStreamSynchronize(st)) != hipSuccess)
         return failed(e);
+    const uint32_t* ins = reinterpret_cast<const uint32_t*>(head_h.data());
+    const uint64_t* sum = head_h.data() + insb / 8;  // record entries, erased, inserted, ~time
+    const uint32_t* fits = reinterpret_cast<const uint32_t*>(tail_h.data());
+    const uint64_t* occ = tail_h.data() + insb / 8;
     rec.n = sum[0];
     rec.cur = b;
     rec.tmin = ~sum[3];
     rec.tmax = tmax;
     // tables without room, one at a time: their keys listed where the hash
     // table was
+    bool listed = false;
     for (uint32_t i = 0; i < S; i++) {
         if (fits[i]) {
             index_note_occupied(c, i, occ[i]);
             continue;
         }
+        listed = true;
         kv_zero_kernel<<<1, 64, 0, st>>>(o.sum, 1);
         kv_list_kernel<<<grid_for(ins[i], 256, 1024), kTileThreads, 0, st>>>(
             first, used, key, word, s, i, h.key, o.sum);
         if ((e = index_insert(c, i, h.key, ins[i])) != hipSuccess)
             return failed(e);
     }
-    if ((e = hipStreamSynchronize(st)) != hipSuccess)
+    if (listed && (e = hipStreamSynchronize(st)) != hipSuccess)
         return failed(e);
     if (added) *added = sum[2];
     if (removed) *removed = sum[1];

@@ -322,6 +322,15 @@ __global__ void zero_u32_kernel(uint32_t* p, uint32_t n)
         p[k] = 0;
 }
 
+// Three words to pinned host memory.
+__global__ void post_words_kernel(const uint64_t* a, const uint64_t* b, const uint64_t* c,
+                                  uint64_t* __restrict__ host)
+{
+    host[0] = *a;
+    host[1] = *b;
+    host[2] = *c;
+}
+
 __global__ void fill_u32_kernel(uint32_t* p, uint64_t n, uint32_t v)
 {
     for (uint64_t k = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; k < n;
@@ -1159,6 +1168,18 @@ T* carve(uint8_t*& p, uint64_t n)
 
 }  // namespace
 
+hipError_t queue_ends(dm_ctx* c, const int64_t* qoff, int64_t* first, int64_t* last)
+{
+    const uint64_t* q = reinterpret_cast<const uint64_t*>(qoff);
+    post_words_kernel<<<1, 1, 0, c->stream>>>(q, q + c->cfg.max_slots, q, c->host_words);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(c->stream);
+    *first = e == hipSuccess ? (int64_t)c->host_words[0] : 0;
+    *last = e == hipSuccess ? (int64_t)c->host_words[1] : 0;
+    return e;
+}
+
 hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm_migrations* out,
                      uint64_t cap, uint64_t Q)
 {
@@ -1188,8 +1209,9 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     uint64_t* base_of = carve<uint64_t>(pi, S);
     int64_t* slice_sum = carve<int64_t>(pi, (uint64_t)S * kQSplit);
     int64_t* slice_max = carve<int64_t>(pi, (uint64_t)S * kQSplit);
-    uint32_t* nsrc = carve<uint32_t>(pi, 1);
-    uint64_t* ctot = carve<uint64_t>(pi, 2);  // candidate count, largest eligible benefit
+    // candidate count, largest eligible benefit, overloaded sources
+    uint64_t* ctot = carve<uint64_t>(pi, 3);
+    uint32_t* nsrc = reinterpret_cast<uint32_t*>(ctot + 2);
     // per-record arrays
     const uint64_t Qa = Q ? Q : 1;
     uint8_t* pr = static_cast<uint8_t*>(scratch_get(c, kSlotProbe, Qa * 48 + 8 * 256, &e));
@@ -1202,8 +1224,7 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     uint64_t* pos = carve<uint64_t>(pr, Qa);
     uint32_t* qkey = carve<uint32_t>(pr, Qa);
 
-    zero_u32_kernel<<<1, 64, 0, st>>>(nsrc, 1);
-    zero_u32_kernel<<<1, 64, 0, st>>>(reinterpret_cast<uint32_t*>(ctot), 4);
+    zero_u32_kernel<<<1, 64, 0, st>>>(reinterpret_cast<uint32_t*>(ctot), 6);
     fill_u32_kernel<<<grid_for(Qa, 256), 256, 0, st>>>(owner, Qa, 0xFFFFFFFFu);
     queue_sum_kernel<<<S * kQSplit, kQThreads, 0, st>>>(q->qoff, Q, q->unc_here, slice_sum,
                                                         c->d_status);
@@ -1226,13 +1247,12 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
         e = exclusive_scan_u64(c, elig, Q, pos, ctot);
         if (e != hipSuccess)
             return e;
-        e = hipMemcpyAsync(hw, ctot, sizeof(hw), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(&nsrc_h, nsrc, sizeof(nsrc_h), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(st);
-        if (e != hipSuccess)
+        post_words_kernel<<<1, 1, 0, st>>>(ctot, ctot + 1, ctot + 2, c->host_words);
+        if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
             return e;
+        hw[0] = c->host_words[0];
+        hw[1] = c->host_words[1];
+        nsrc_h = (uint32_t)c->host_words[2];
     }
     const uint64_t C = hw[0];
     // per-candidate arrays
