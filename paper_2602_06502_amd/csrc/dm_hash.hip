@@ -110,6 +110,8 @@ struct HashArgs {
     unsigned long long* ext_count;
     const unsigned long long* ext_count_in;
     uint32_t* key_len;            // [n] or null
+    // prefix: candidates of the ring keys (look.cand null: not looked up here)
+    LookupArgs look;
     // f1 digests NH(j) of blocks j < min(K, full blocks), [n * key_blocks]:
     // written by the prefix pass so that the members pass need not read
     // those tokens again (null: not kept)
@@ -191,12 +193,27 @@ __global__ __launch_bounds__(kHashThreads) void ring_key_kernel(HashArgs a, uint
             s2 += shfl_xor_u64(s2, (int)d);
         }
         bool down = false;  // the depth-K prefix is extended: go on down the tree
-        if (r < a.n && j == 0) {
-            uint64_t x1 = mix64(H01 ^ seed1), x2 = mix64(H02 ^ seed2);  // empty-prefix keys
-            if (kr > 0) {
-                x1 = mix64(((H01 + s1) * hp->ppow[0][kr - 1]) ^ seed1);
-                x2 = mix64(((H02 + s2) * hp->ppow[1][kr - 1]) ^ seed2);
+        uint64_t x1 = mix64(H01 ^ seed1), x2 = mix64(H02 ^ seed2);  // empty-prefix keys
+        if (kr > 0) {
+            x1 = mix64(((H01 + s1) * hp->ppow[0][kr - 1]) ^ seed1);
+            x2 = mix64(((H02 + s2) * hp->ppow[1][kr - 1]) ^ seed2);
+        }
+        if (a.look.cand) {
+            // a group's first two lanes take a ring each
+            const uint64_t y1 = bad ? 0 : x1, y2 = bad ? 0 : x2;
+            uint32_t c1 = 0, c2 = 0;
+            if (g > 1) {
+                if (r < a.n && j < 2)
+                    c1 = ring_owner(j ? a.look.r2 : a.look.r1, j ? y2 : y1);
+                c2 = (uint32_t)__shfl((int)c1, lane | 1);
+            } else if (r < a.n) {
+                c1 = ring_owner(a.look.r1, y1);
+                c2 = ring_owner(a.look.r2, y2);
             }
+            if (r < a.n && j == 0)
+                lookup_store(a.look, a.n, r, y1, c1, c2);
+        }
+        if (r < a.n && j == 0) {
             a.key_out[r] = bad ? 0 : x1;
             a.key_out[a.n + r] = bad ? 0 : x2;
             if (a.key_len)
@@ -787,9 +804,12 @@ static void tree_args(dm_ctx* c, HashArgs& a)
 
 hipError_t hash_prefix(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                        const uint32_t* bad, uint64_t* key_out, uint32_t* key_len,
-                       uint32_t* ext_list, unsigned long long* ext_count, uint64_t* nh0)
+                       uint32_t* ext_list, unsigned long long* ext_count, uint64_t* nh0,
+                       const LookupArgs* look)
 {
     HashArgs a = base_args(c, tokens, offsets, n, bad);
+    if (look)
+        a.look = *look;
     a.nh0 = nh0;
     a.key_out = key_out;
     a.key_len = key_len;

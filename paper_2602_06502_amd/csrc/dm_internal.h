@@ -256,10 +256,18 @@ size_t noalloc_capacity();
 hipError_t exclusive_scan_u64(dm_ctx* c, const uint64_t* in, uint64_t n, uint64_t* out,
                               uint64_t* total_out);
 // block_starts also checks the offsets (0 <= offsets[0] <= ... <= offsets[n]
-// <= n_tokens) and sets *bad (zeroed beforehand) when they break that rule;
-// such requests count no full block.
+// <= n_tokens): *bad is 1 when they break that rule, else 0 (n > 0); such
+// requests count no full block.  Being a batch's first kernels it also clears
+// the words that later ones add to: the tree's count, and the selection's
+// growth bounds of the parts there are.
+constexpr int kMaxParts = 2;
+struct BatchClear {
+    unsigned long long* count;
+    unsigned long long* grow[kMaxParts];
+    uint32_t n_live;
+};
 hipError_t block_starts(dm_ctx* c, const int64_t* offsets, uint64_t n, uint64_t n_tokens,
-                        uint64_t* starts, uint32_t* bad);
+                        uint64_t* starts, uint32_t* bad, const BatchClear& also = {});
 
 // dm_sort.hip: stable LSD radix sort of (u64 key, u32 value) pairs on the
 // low `bits` bits of the key (bits multiple of 8).  Sorted data ends in
@@ -281,6 +289,18 @@ void index_note_occupied(dm_ctx* c, uint32_t id, uint64_t occupied);
 hipError_t index_clear(dm_ctx* c, uint32_t id);
 // the tables of n instances (host list) emptied by one launch
 hipError_t index_clear_many(dm_ctx* c, const uint32_t* ids_host, uint32_t n);
+
+// What a lookup on the rings reads and writes (dm_probe.hip): candidates and
+// flags, and the ordering's sort input (svals null: the request's number).
+struct LookupArgs {
+    RingView r1, r2;
+    const uint32_t* next_live;
+    uint32_t n_live;
+    uint32_t* cand;    // [2n]
+    uint8_t* flags;    // [n]
+    uint64_t* skeys;   // [n]
+    uint32_t* svals;   // [n] or null
+};
 
 // Requests grouped by equal ring keys (dm_probe.hip): group_of[r] is
 // request r's group, leader[g] is group g's leader request, *groups = G.
@@ -307,11 +327,13 @@ struct GroupView {
 //   nh0 (optional, [n * K]): hash_prefix keeps there the f1 digests of
 //     every request's blocks below min(K, full blocks), and hash_members
 //     takes them instead of reading those tokens again.
+//   look (optional): hash_prefix also looks the ring keys up.
 //   keylen_record: every request's prefixes of depth >= K (its f1 block
 //     keys from block K - 1 on, in hkeys at bstart[r]) join the window.
 hipError_t hash_prefix(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                        const uint32_t* bad, uint64_t* key_out, uint32_t* key_len,
-                       uint32_t* ext_list, unsigned long long* ext_count, uint64_t* nh0);
+                       uint32_t* ext_list, unsigned long long* ext_count, uint64_t* nh0,
+                       const LookupArgs* look);
 hipError_t hash_extend(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                        const uint32_t* bad, uint64_t* key_out, uint32_t* key_len,
                        const uint32_t* ext_list, const unsigned long long* ext_count);
@@ -359,8 +381,10 @@ dm_status queue_reprobe(dm_ctx* c, const dm_queues* q, const int64_t* coff, cons
 
 // dm_probe.hip: candidates on the current rings (cand, fix-up flag bit 3),
 // then requests ordered by their first ring key and grouped (gv).
-hipError_t lookup_group(dm_ctx* c, uint64_t n, const uint64_t* key, const uint64_t* bstart,
-                        const uint32_t* bad, uint32_t* cand, uint8_t* flags, GroupView* gv);
+hipError_t lookup_args(dm_ctx* c, uint64_t n, uint32_t* cand, uint8_t* flags, LookupArgs* a);
+hipError_t lookup_candidates(dm_ctx* c, uint64_t n, const uint64_t* key, const LookupArgs& a);
+hipError_t group_requests(dm_ctx* c, uint64_t n, const uint64_t* bstart, const uint32_t* bad,
+                          GroupView* gv);
 
 // dm_select.hip: the choice in request order; chosen, ttft_us and flags bits
 // 0-2 written, loads updated.  A batch is selected in one part, or in
@@ -370,7 +394,6 @@ hipError_t lookup_group(dm_ctx* c, uint64_t n, const uint64_t* key, const uint64
 // select_prepare packs the part's records (no loads needed), select_walk
 // takes the loads' plan and walks the part, select_output writes its
 // results.  par picks one of two work-array sets.
-constexpr int kMaxParts = 2;
 struct SelPart {
     uint64_t r0, m;          // requests [r0, r0 + m)
     uint32_t block, wincap;  // requests per level block, windows per block
@@ -513,6 +536,29 @@ __device__ __forceinline__ uint32_t ring_owner(const RingView& r, uint64_t x)
     if (i >= r.len)
         i = 0;
     return r.id[i];
+}
+
+// Requests are ordered by the top bits of their first ring key.
+constexpr int kOrderBits = 16;
+
+// Request r with first ring key x and owners c1, c2: its candidates (distinct
+// where two instances live) and flags; the ordering's sort input is the ring key
+// rotated so that its top kOrderBits bits are the low ones that the sort
+// orders by (the sort carries the whole key along), and the request.
+__device__ __forceinline__ void lookup_store(const LookupArgs& a, uint64_t n, uint64_t r,
+                                             uint64_t x, uint32_t c1, uint32_t c2)
+{
+    a.skeys[r] = (x << kOrderBits) | (x >> (64 - kOrderBits));
+    if (a.svals)
+        a.svals[r] = (uint32_t)r;
+    uint8_t f = 0;
+    if (c2 == c1) {
+        f = 8;
+        c2 = a.n_live >= 2 ? a.next_live[c1] : c1;
+    }
+    a.cand[r] = c1;
+    a.cand[n + r] = c2;
+    a.flags[r] = f;
 }
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }

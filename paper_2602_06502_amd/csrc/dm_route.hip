@@ -3,10 +3,10 @@
 //   block_starts   exclusive sum of full blocks per request: where each
 //                  request's block keys go; checks the offsets;
 //   hash_prefix    both ring keys from the first min(K, full blocks)
-//                  blocks (dm_hash.hip);
-//   lookup_group   candidates on the two rings, then requests ordered by
-//                  their first ring key and grouped by equal ring keys,
-//                  with a leader per group (dm_probe.hip);
+//                  blocks, and the candidates on the two rings
+//                  (dm_hash.hip);
+//   group_requests requests ordered by their first ring key and grouped by
+//                  equal ring keys, with a leader per group (dm_probe.hip);
 //   hash_leaders   leaders' full chains and longest cached prefixes;
 //   hash_members   every other request's full chain and longest cached
 //                  prefix, from its leader's keys and its own probes;
@@ -27,33 +27,6 @@ namespace dm {
 namespace {
 
 constexpr int kKeySlot = kSlotKeys;  // block keys when the caller keeps none
-
-// Growth bounds of the selection's parts (those there are).
-struct Growth {
-    unsigned long long* of[kMaxParts];
-};
-
-// Clears the batch's malformed-offsets word, the tree's count and the
-// selection's growth bounds (a kernel rather than a memset, so that a
-// captured graph replays it like the rest of the batch).
-__global__ __launch_bounds__(256) void route_zero_kernel(uint32_t* bad,
-                                                         unsigned long long* ext_count,
-                                                         Growth grow, uint32_t n_live)
-{
-    for (int p = 0; p < kMaxParts; p++) {
-        if (!grow.of[p])
-            break;
-        for (uint32_t k = threadIdx.x; k < n_live; k += blockDim.x)
-            grow.of[p][k] = 0;
-        if (threadIdx.x == 0)
-            grow.of[p][kMaxSlots] = 0;
-    }
-    if (threadIdx.x == 0) {
-        *bad = 0;
-        if (ext_count)
-            *ext_count = 0;
-    }
-}
 
 // An unpipelined batch of at least kSplitTokens tokens (and kSplitFrom
 // requests) is selected in two parts: the walk of the first, one wave on one
@@ -174,12 +147,11 @@ static hipError_t route_parts(dm_ctx* c, const int32_t* tokens, uint64_t n_token
         ext_list = reinterpret_cast<uint32_t*>(w + 256);
         kl_work = reinterpret_cast<uint64_t*>(w + 256 + list_bytes);
     }
-    Growth grow{};
+    BatchClear clear{ext_count, {}, c->n_live};
     for (int k = 0; k < ps.count; k++)
-        if ((e = select_growth(c, ps, k, par, &grow.of[k])) != hipSuccess)
+        if ((e = select_growth(c, ps, k, par, &clear.grow[k])) != hipSuccess)
             return e;
-    route_zero_kernel<<<1, 256, 0, st>>>(bad, ext_count, grow, c->n_live);
-    if ((e = block_starts(c, offsets, n, n_tokens, bstart, bad)) != hipSuccess)
+    if ((e = block_starts(c, offsets, n, n_tokens, bstart, bad, clear)) != hipSuccess)
         return e;
     uint64_t* hkeys = out->block_keys;
     // the hotness tree's window records every request's block keys
@@ -196,13 +168,16 @@ static hipError_t route_parts(dm_ctx* c, const int32_t* tokens, uint64_t n_token
     if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess)
         return e;
     GroupView gv{};
-    if ((e = hash_prefix(c, tokens, offsets, n, bad, out->key, out->key_len, ext_list,
-                         ext_count, nh0)) != hipSuccess)
+    LookupArgs look{};
+    if ((e = lookup_args(c, n, out->cand, out->flags, &look)) != hipSuccess ||
+        (e = hash_prefix(c, tokens, offsets, n, bad, out->key, out->key_len, ext_list,
+                         ext_count, nh0, c->kl.on ? nullptr : &look)) != hipSuccess)
         return e;
-    if (c->kl.on && (e = hash_extend(c, tokens, offsets, n, bad, out->key, out->key_len, ext_list,
-                                     ext_count)) != hipSuccess)
+    if (c->kl.on && ((e = hash_extend(c, tokens, offsets, n, bad, out->key, out->key_len, ext_list,
+                                      ext_count)) != hipSuccess ||
+                     (e = lookup_candidates(c, n, out->key, look)) != hipSuccess))
         return e;
-    if ((e = lookup_group(c, n, out->key, bstart, bad, out->cand, out->flags, &gv)) != hipSuccess)
+    if ((e = group_requests(c, n, bstart, bad, &gv)) != hipSuccess)
         return e;
     if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess)
         return e;
