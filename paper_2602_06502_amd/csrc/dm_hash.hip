@@ -44,6 +44,9 @@ constexpr uint32_t kLeaderBlocks = 2048;    // tree walk, resume walk: at most 8
 constexpr uint32_t kLeaderGrid = 8192;      // leaders: up to 32,768 waves, one leader each
 
 enum : int { kLeaders = 1, kResume = 2 };
+// most requests of a members pass in one launch (member_probe_kernel); at
+// 131,072 the one launch and the four take the same time
+constexpr uint64_t kInlineTo = 1u << 16;
 constexpr uint64_t kPendKeys = 8;  // keys kept per request for the pending probes
 
 typedef int v4i __attribute__((ext_vector_type(4), aligned(4)));
@@ -665,6 +668,129 @@ __global__ __launch_bounds__(kHashThreads) void member_kernel(HashArgs a)
     }
 }
 
+// The members pass of batches of at most kInlineTo requests, which are bound by
+// launches and a chain's latency rather than by bytes: a wave gathers its
+// request's record itself and probes as it hashes, where larger batches take
+// four kernels (records, chains, pending probes, resumed walks).  In four and
+// in one: 1,024 requests 118 and 111 us, 4,096 chat requests 240 and 231,
+// 65,536 on 512 instances 581 and 568, 16,384 agent prompts routed and saved
+// 1,254 and 1,200.
+template <int B>
+__global__ __launch_bounds__(kHashThreads) void member_probe_kernel(HashArgs a)
+{
+    const int lane = lane_id();
+    const HashParams* hp = a.hp;
+    const uint64_t seed1 = hp->seed[0];
+    const uint64_t q1 = hp->qpow[0][lane], p1 = hp->ppow[0][lane];
+    const bool bad = *a.bad != 0;
+    uint32_t k1[B];
+#pragma unroll
+    for (int j = 0; j < B; j++)
+        k1[j] = hp->kk[0][j];
+    const uint64_t r = a.r0 + wave_index();
+    if (r >= a.r1)
+        return;
+    const uint64_t K = a.key_blocks;
+    auto blocks = [&](uint64_t q) -> uint64_t {
+        const uint64_t x = bad ? 0 : (uint64_t)(a.offsets[q + 1] - a.offsets[q]) / B;
+        return x > 0xFFFFFFFFull ? 0 : x;  // reported by the leaders' walk if a leader
+    };
+    const uint64_t nfull = blocks(r), kp = a.nh0 ? (nfull < K ? nfull : K) : 0;
+    const int32_t* tp = a.tokens + a.offsets[r];
+    ChunkTokens<B> nx;
+    load_chunk<B>(nx, tp, (uint64_t)lane, (uint64_t)lane < nfull && (uint64_t)lane >= kp);
+    const uint64_t pre = (uint64_t)lane < kp ? a.nh0[r * K + lane] : 0;
+    // the leader's keys, how far to compare and its matches
+    const uint32_t L = a.gv.leader[a.gv.group_of[r]];
+    const bool lead = L == r;
+    const uint32_t c0 = a.cand[r], c1 = a.cand[a.n + r];
+    uint64_t lim = 0;
+    uint32_t lead0 = 0, lead1 = 0;
+    const uint64_t* lk = a.hkeys;
+    if (!lead) {
+        lk += a.bstart[L];
+        lead0 = a.match[L];
+        lead1 = a.match[a.n + L];
+        const uint64_t M = lead0 > lead1 ? lead0 : lead1, nl = blocks(L);
+        lim = M + 1 < nfull ? M + 1 : nfull;
+        lim = lim < nl ? lim : nl;
+        // other candidates than the leader's (only on a ring-key collision):
+        // probed from block 0
+        if (c0 != a.cand[L] || c1 != a.cand[a.n + L])
+            lim = 0;
+    }
+    const uint32_t ls = a.log2slots;
+    const uint64_t* t0 = a.tables + ((uint64_t)c0 << ls);
+    const uint64_t* t1 = a.tables + ((uint64_t)c1 << ls);
+    uint64_t* hk = a.hkeys + a.bstart[r];
+    uint64_t nlk = (uint64_t)lane < lim ? lk[lane] : 0;
+    bool cmp = lim > 0, pend0 = false, pend1 = false;
+    uint64_t from = 0;  // first block to probe
+    uint32_t m0 = (uint32_t)nfull, m1 = (uint32_t)nfull;
+    // blocks before s hold the leader's keys
+    auto resolve = [&](uint64_t s) {
+        from = s;
+        if (lead0 < s)
+            m0 = lead0;
+        else
+            pend0 = s < nfull;
+        if (lead1 < s)
+            m1 = lead1;
+        else
+            pend1 = s < nfull;
+    };
+    if (!cmp && !lead)
+        resolve(0);
+    uint64_t G = hp->H0[0];
+    for (uint64_t cb = 0; cb < nfull; cb += kWave) {
+        const uint64_t b = cb + lane;
+        const bool valid = b < nfull;
+        const ChunkTokens<B> tc = nx;
+        const uint64_t lkey = nlk;
+        // loads of the following chunk go out before this one is hashed
+        const uint64_t b2 = b + kWave;
+        if (cb + kWave < nfull) {
+            load_chunk<B>(nx, tp, b2, b2 < nfull);
+            nlk = cmp && b2 < lim ? lk[b2] : 0;
+        }
+        const uint64_t nh1 = valid ? (b < kp ? pre : nh_regs<B>(tc, k1)) : 0;
+        const uint64_t S = wave_incl_sum_u64(nh1 * q1, lane);
+        const uint64_t H = (G + S) * p1;
+        const uint64_t h = mix64(H ^ seed1);
+        if (a.write_keys && valid)
+            hk[b] = h;
+        G = readlane_u64(H, kWave - 1);
+        if (cmp) {
+            const uint64_t diff = ballot(b < lim && lkey != h);
+            if (diff) {
+                cmp = false;
+                resolve(cb + (uint64_t)__builtin_ctzll(diff));
+            } else if (cb + kWave >= lim) {
+                cmp = false;
+                resolve(lim);
+            }
+        }
+        if (pend0 || pend1) {
+            const uint64_t hi = nfull < cb + kWave ? nfull : cb + kWave;
+            const uint64_t pb = from > cb ? from : cb;
+            const uint64_t ck = canon_key(h);
+            uint64_t f = 0;
+            if (pend0 && pb < hi && chunk_first_absent(t0, ls, ck, cb, pb, hi, lane, &f)) {
+                m0 = (uint32_t)f;
+                pend0 = false;
+            }
+            if (pend1 && pb < hi && chunk_first_absent(t1, ls, ck, cb, pb, hi, lane, &f)) {
+                m1 = (uint32_t)f;
+                pend1 = false;
+            }
+        }
+    }
+    if (lane == 0 && !lead) {
+        a.match[r] = m0;
+        a.match[a.n + r] = m1;
+    }
+}
+
 // Pending candidates of the members pass, one thread per request: probe
 // its kept keys of blocks [s, s + 8) in order up to the first absent one.
 // If all are present and blocks remain, the (request, candidate) goes to
@@ -741,6 +867,20 @@ hipError_t launch_members(dm_ctx* c, const HashArgs& a)
         case 64: return launch_members_b<64>(c, a);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_member_probe(dm_ctx* c, const HashArgs& a)
+{
+    const uint32_t grid = grid_for(a.r1 - a.r0, kHashThreads / kWave);
+    switch (c->cfg.block_size) {
+        case 4: member_probe_kernel<4><<<grid, kHashThreads, 0, c->stream>>>(a); break;
+        case 8: member_probe_kernel<8><<<grid, kHashThreads, 0, c->stream>>>(a); break;
+        case 16: member_probe_kernel<16><<<grid, kHashThreads, 0, c->stream>>>(a); break;
+        case 32: member_probe_kernel<32><<<grid, kHashThreads, 0, c->stream>>>(a); break;
+        case 64: member_probe_kernel<64><<<grid, kHashThreads, 0, c->stream>>>(a); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 HashArgs base_args(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
@@ -885,16 +1025,6 @@ hipError_t hash_members(dm_ctx* c, const int32_t* tokens, const int64_t* offsets
                         const uint32_t* bad, const GroupView& gv, const uint32_t* cand,
                         uint64_t* hkeys, bool write_keys, uint32_t* match, const uint64_t* nh0)
 {
-    MemberWork mw;
-    hipError_t e = member_work(c, n, &mw);
-    if (e != hipSuccess)
-        return e;
-    uint32_t bshift = 0;
-    while ((1u << bshift) < c->cfg.block_size)
-        bshift++;
-    member_record_kernel<<<grid_for(m, 256, 8192), 256, 0, c->stream>>>(
-        offsets, n, r0, r0 + m, bshift, bstart, bad, gv, cand, match, mw.rec,
-        mw.resume_count + part);
     HashArgs a = base_args(c, tokens, offsets, n, bad);
     a.r0 = r0;
     a.r1 = r0 + m;
@@ -905,6 +1035,18 @@ hipError_t hash_members(dm_ctx* c, const int32_t* tokens, const int64_t* offsets
     a.gv = gv;
     a.cand = cand;
     a.match = match;
+    if (m <= kInlineTo)
+        return launch_member_probe(c, a);
+    MemberWork mw;
+    hipError_t e = member_work(c, n, &mw);
+    if (e != hipSuccess)
+        return e;
+    uint32_t bshift = 0;
+    while ((1u << bshift) < c->cfg.block_size)
+        bshift++;
+    member_record_kernel<<<grid_for(m, 256, 8192), 256, 0, c->stream>>>(
+        offsets, n, r0, r0 + m, bshift, bstart, bad, gv, cand, match, mw.rec,
+        mw.resume_count + part);
     a.rec = mw.rec;
     a.pkeys = mw.pkeys;
     a.pend = mw.pend;
