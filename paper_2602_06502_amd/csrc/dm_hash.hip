@@ -40,13 +40,14 @@ namespace {
 
 constexpr int kHashThreads = 256;
 constexpr uint32_t kHashBlocks = 1u << 20;  // one wave per unit up to 4 Mi units
-constexpr uint32_t kLeaderBlocks = 2048;    // tree walk, resume walk: at most 8,192 waves
+constexpr uint32_t kLeaderBlocks = 2048;    // resume walk: at most 8,192 waves
 constexpr uint32_t kLeaderGrid = 8192;      // leaders: up to 32,768 waves, one leader each
 
 enum : int { kLeaders = 1, kResume = 2 };
 // most requests of a members pass in one launch (member_probe_kernel); at
 // 131,072 the one launch and the four take the same time
 constexpr uint64_t kInlineTo = 1u << 16;
+constexpr uint32_t kExtend = 4;   // requests of one wave of the tree walk
 constexpr uint64_t kPendKeys = 8;  // keys kept per request for the pending probes
 
 typedef int v4i __attribute__((ext_vector_type(4), aligned(4)));
@@ -109,9 +110,9 @@ struct HashArgs {
     uint32_t kl_on;
     uint32_t kl_log2;
     const uint64_t* kl_tab;       // extended prefixes
-    uint32_t* ext_list;           // requests whose depth-K prefix is extended
-    unsigned long long* ext_count;
-    const unsigned long long* ext_count_in;
+    // per wave of the prefix pass: lanes (a request's first) whose request's
+    // depth-K prefix is extended
+    uint64_t* ext;
     uint32_t* key_len;            // [n] or null
     // prefix: candidates of the ring keys (look.cand null: not looked up here)
     LookupArgs look;
@@ -226,16 +227,9 @@ __global__ __launch_bounds__(kHashThreads) void ring_key_kernel(HashArgs a, uint
                 down = table_has(a.kl_tab, a.kl_log2, canon_key(x1));
         }
         if (a.kl_on) {
-            // one append per wave for the requests going down the tree
             const uint64_t m = ballot(down);
-            if (m) {
-                unsigned long long at = 0;
-                if (lane == (int)__builtin_ctzll(m))
-                    at = atomicAdd(a.ext_count, (unsigned long long)__builtin_popcountll(m));
-                at = (unsigned long long)readlane_u64((uint64_t)at, (int)__builtin_ctzll(m));
-                if (down)
-                    a.ext_list[at + __builtin_popcountll(m & ((1ull << lane) - 1))] = (uint32_t)r;
-            }
+            if (lane == 0)
+                a.ext[base / per_wave] = m;
         }
     }
 }
@@ -243,9 +237,12 @@ __global__ __launch_bounds__(kHashThreads) void ring_key_kernel(HashArgs a, uint
 // Requests whose depth-K prefix is extended walk down the tree: both chains
 // 64 blocks at a time from the start; K_r is the first depth d > K whose
 // prefix (f1 key of block d - 1) is not extended, or the full-block count.
-// The ring keys become the depth-K_r keys.
+// The ring keys become the depth-K_r keys.  A wave takes up to kExtend of the
+// prefix pass's requests, those that its mask names.  (A list of them took one
+// atomic per wave on one counter: the prefix pass of 131,072 requests 110 us
+// instead of 19.)
 template <int B>
-__global__ __launch_bounds__(kHashThreads) void extend_kernel(HashArgs a)
+__global__ __launch_bounds__(kHashThreads) void extend_kernel(HashArgs a, uint32_t glog)
 {
     const int lane = lane_id();
     const uint64_t gw = wave_index();
@@ -261,42 +258,49 @@ __global__ __launch_bounds__(kHashThreads) void extend_kernel(HashArgs a)
         k2[t] = hp->kk[1][t];
     }
     const uint64_t K = a.key_blocks;
-    const uint64_t units = *a.ext_count_in;
+    const uint32_t per = kWave >> glog, take = per < kExtend ? per : kExtend;
+    const uint64_t units = (a.n + take - 1) / take;
     for (uint64_t u = gw; u < units; u += nw) {
-        const uint32_t r = a.ext_list[u];
-        const int64_t o0 = a.offsets[r];
-        const uint64_t nfull = (uint64_t)(a.offsets[(uint64_t)r + 1] - o0) / B;
-        const int32_t* tp = a.tokens + o0;
-        uint64_t G1 = hp->H0[0], G2 = hp->H0[1];
-        uint64_t kr = nfull, x1 = 0, x2 = 0;
-        for (uint64_t cb = 0; cb < nfull; cb += kWave) {
-            const uint64_t b = cb + lane, d = b + 1;
-            const bool valid = b < nfull;
-            uint64_t nh1 = 0, nh2 = 0;
-            if (valid)
-                nh_block2<B>(tp + b * B, k1, k2, nh1, nh2);
-            const uint64_t H1 = (G1 + wave_incl_sum_u64(nh1 * q1, lane)) * p1;
-            const uint64_t H2 = (G2 + wave_incl_sum_u64(nh2 * q2, lane)) * p2;
-            G1 = readlane_u64(H1, kWave - 1);
-            G2 = readlane_u64(H2, kWave - 1);
-            const uint64_t h1 = mix64(H1 ^ seed1);
-            // the path ends at the first depth past K that is not extended
-            const bool below = valid && d > K;
-            const uint64_t stop =
-                ballot(below && (d == nfull || !table_has(a.kl_tab, a.kl_log2, canon_key(h1))));
-            if (stop) {
-                const int f = __builtin_ctzll(stop);
-                kr = cb + f + 1;
-                x1 = readlane_u64(h1, f);
-                x2 = readlane_u64(mix64(H2 ^ seed2), f);
-                break;
+        const uint64_t first = u * take, in = first % per;  // in its wave of the prefix pass
+        uint64_t m = a.ext[first / per] >> (in << glog);
+        if (take < per)
+            m &= (1ull << (take << glog)) - 1;
+        for (; m; m &= m - 1) {
+            const uint64_t r = first + ((uint32_t)__builtin_ctzll(m) >> glog);
+            const int64_t o0 = a.offsets[r];
+            const uint64_t nfull = (uint64_t)(a.offsets[(uint64_t)r + 1] - o0) / B;
+            const int32_t* tp = a.tokens + o0;
+            uint64_t G1 = hp->H0[0], G2 = hp->H0[1];
+            uint64_t kr = nfull, x1 = 0, x2 = 0;
+            for (uint64_t cb = 0; cb < nfull; cb += kWave) {
+                const uint64_t b = cb + lane, d = b + 1;
+                const bool valid = b < nfull;
+                uint64_t nh1 = 0, nh2 = 0;
+                if (valid)
+                    nh_block2<B>(tp + b * B, k1, k2, nh1, nh2);
+                const uint64_t H1 = (G1 + wave_incl_sum_u64(nh1 * q1, lane)) * p1;
+                const uint64_t H2 = (G2 + wave_incl_sum_u64(nh2 * q2, lane)) * p2;
+                G1 = readlane_u64(H1, kWave - 1);
+                G2 = readlane_u64(H2, kWave - 1);
+                const uint64_t h1 = mix64(H1 ^ seed1);
+                // the path ends at the first depth past K that is not extended
+                const bool below = valid && d > K;
+                const uint64_t stop =
+                    ballot(below && (d == nfull || !table_has(a.kl_tab, a.kl_log2, canon_key(h1))));
+                if (stop) {
+                    const int f = __builtin_ctzll(stop);
+                    kr = cb + f + 1;
+                    x1 = readlane_u64(h1, f);
+                    x2 = readlane_u64(mix64(H2 ^ seed2), f);
+                    break;
+                }
             }
-        }
-        if (lane == 0) {
-            a.key_out[r] = x1;
-            a.key_out[a.n + r] = x2;
-            if (a.key_len)
-                a.key_len[r] = (uint32_t)kr;
+            if (lane == 0) {
+                a.key_out[r] = x1;
+                a.key_out[a.n + r] = x2;
+                if (a.key_len)
+                    a.key_len[r] = (uint32_t)kr;
+            }
         }
     }
 }
@@ -942,10 +946,24 @@ static void tree_args(dm_ctx* c, HashArgs& a)
     a.kl_tab = k.tab[k.cur];
 }
 
+// log2 of the prefix pass's lanes per request.
+static uint32_t prefix_glog(const dm_ctx* c)
+{
+    uint32_t glog = 0;
+    while ((1u << glog) < c->cfg.key_blocks)
+        glog++;
+    return glog;
+}
+
+uint64_t ext_words(const dm_ctx* c, uint64_t n)
+{
+    const uint64_t per = kWave >> prefix_glog(c);
+    return (n + per - 1) / per;
+}
+
 hipError_t hash_prefix(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                        const uint32_t* bad, uint64_t* key_out, uint32_t* key_len,
-                       uint32_t* ext_list, unsigned long long* ext_count, uint64_t* nh0,
-                       const LookupArgs* look)
+                       uint64_t* ext, uint64_t* nh0, const LookupArgs* look)
 {
     HashArgs a = base_args(c, tokens, offsets, n, bad);
     if (look)
@@ -954,11 +972,8 @@ hipError_t hash_prefix(dm_ctx* c, const int32_t* tokens, const int64_t* offsets,
     a.key_out = key_out;
     a.key_len = key_len;
     tree_args(c, a);
-    a.ext_list = ext_list;
-    a.ext_count = ext_count;
-    uint32_t glog = 0;
-    while ((1u << glog) < c->cfg.key_blocks)
-        glog++;
+    a.ext = ext;
+    const uint32_t glog = prefix_glog(c);
     const uint64_t waves = (n + (kWave >> glog) - 1) / (kWave >> glog);
     const uint32_t grid = grid_for(waves, kHashThreads / kWave, kHashBlocks);
     switch (c->cfg.block_size) {
@@ -974,22 +989,21 @@ hipError_t hash_prefix(dm_ctx* c, const int32_t* tokens, const int64_t* offsets,
 
 hipError_t hash_extend(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                        const uint32_t* bad, uint64_t* key_out, uint32_t* key_len,
-                       const uint32_t* ext_list, const unsigned long long* ext_count)
+                       uint64_t* ext)
 {
     HashArgs a = base_args(c, tokens, offsets, n, bad);
     a.key_out = key_out;
     a.key_len = key_len;
     tree_args(c, a);
-    a.ext_list = const_cast<uint32_t*>(ext_list);
-    a.ext_count_in = ext_count;
-    // the listed count is on the device: a bounded grid strides over it
-    const uint32_t grid = grid_for(n, kHashThreads / kWave, kLeaderBlocks);
+    a.ext = ext;
+    const uint32_t glog = prefix_glog(c), per = kWave >> glog, take = per < kExtend ? per : kExtend;
+    const uint32_t grid = grid_for((n + take - 1) / take, kHashThreads / kWave, kHashBlocks);
     switch (c->cfg.block_size) {
-        case 4: extend_kernel<4><<<grid, kHashThreads, 0, c->stream>>>(a); break;
-        case 8: extend_kernel<8><<<grid, kHashThreads, 0, c->stream>>>(a); break;
-        case 16: extend_kernel<16><<<grid, kHashThreads, 0, c->stream>>>(a); break;
-        case 32: extend_kernel<32><<<grid, kHashThreads, 0, c->stream>>>(a); break;
-        case 64: extend_kernel<64><<<grid, kHashThreads, 0, c->stream>>>(a); break;
+        case 4: extend_kernel<4><<<grid, kHashThreads, 0, c->stream>>>(a, glog); break;
+        case 8: extend_kernel<8><<<grid, kHashThreads, 0, c->stream>>>(a, glog); break;
+        case 16: extend_kernel<16><<<grid, kHashThreads, 0, c->stream>>>(a, glog); break;
+        case 32: extend_kernel<32><<<grid, kHashThreads, 0, c->stream>>>(a, glog); break;
+        case 64: extend_kernel<64><<<grid, kHashThreads, 0, c->stream>>>(a, glog); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

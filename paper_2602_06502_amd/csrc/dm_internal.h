@@ -100,7 +100,8 @@ struct KeyLen {
     uint64_t n_ext = 0;
     uint64_t* log = nullptr;      // [cap] the window's record
     uint32_t* roots = nullptr;    // [cap / 32 + 1] bit i: record entry i is a request's root
-    unsigned long long* log_n = nullptr;  // entries the window produced (may pass cap)
+    // entries the window produced (may pass cap), then its runs
+    unsigned long long* log_n = nullptr;
     uint64_t win = 0;             // requests routed in the current window
 };
 
@@ -258,11 +259,9 @@ hipError_t exclusive_scan_u64(dm_ctx* c, const uint64_t* in, uint64_t n, uint64_
 // block_starts also checks the offsets (0 <= offsets[0] <= ... <= offsets[n]
 // <= n_tokens): *bad is 1 when they break that rule, else 0 (n > 0); such
 // requests count no full block.  Being a batch's first kernels it also clears
-// the words that later ones add to: the tree's count, and the selection's
-// growth bounds of the parts there are.
+// the selection's growth bounds of the parts there are, which later ones add to.
 constexpr int kMaxParts = 2;
 struct BatchClear {
-    unsigned long long* count;
     unsigned long long* grow[kMaxParts];
     uint32_t n_live;
 };
@@ -321,9 +320,9 @@ struct GroupView {
 //     that comparison and probes past the first disagreement; its keys are
 //     stored into hkeys only when write_keys is set.
 //   hash_prefix with the hotness tree on: requests whose depth-K prefix is
-//     extended are listed (ext_list, *ext_count zeroed beforehand) for
-//     hash_extend, which walks them down the tree to K_r and rewrites their
-//     ring keys.  key_len (optional) gets every request's K_r.
+//     extended are marked (ext, [ext_words]) for hash_extend, which walks them
+//     down the tree to K_r and rewrites their ring keys.  key_len (optional)
+//     gets every request's K_r.
 //   nh0 (optional, [n * K]): hash_prefix keeps there the f1 digests of
 //     every request's blocks below min(K, full blocks), and hash_members
 //     takes them instead of reading those tokens again.
@@ -332,11 +331,11 @@ struct GroupView {
 //     keys from block K - 1 on, in hkeys at bstart[r]) join the window.
 hipError_t hash_prefix(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                        const uint32_t* bad, uint64_t* key_out, uint32_t* key_len,
-                       uint32_t* ext_list, unsigned long long* ext_count, uint64_t* nh0,
-                       const LookupArgs* look);
+                       uint64_t* ext, uint64_t* nh0, const LookupArgs* look);
 hipError_t hash_extend(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                        const uint32_t* bad, uint64_t* key_out, uint32_t* key_len,
-                       const uint32_t* ext_list, const unsigned long long* ext_count);
+                       uint64_t* ext);
+uint64_t ext_words(const dm_ctx* c, uint64_t n);
 hipError_t hash_leaders(dm_ctx* c, const int32_t* tokens, const int64_t* offsets, uint64_t n,
                         const uint64_t* bstart, const uint32_t* bad, const GroupView& gv,
                         const uint32_t* cand, uint64_t* hkeys, uint32_t* match);

@@ -14,10 +14,24 @@
 // and n live instances the result is the set of prefixes with count c
 //   extended now:  c * n >= W      (not cold: rho >= 1/n)
 //   a leaf now:    c * n >  2 W    (hot: rho > 2/n)
-// (extended prefixes the window never saw, c = 0, are dropped): the record
-// sorted in place (radix), each run of equal keys counted at its first
-// entry, the kept ones compacted in key order into the next tree (built in
-// the other table).
+// (extended prefixes the window never saw, c = 0, are dropped).
+//
+// Counts come from the record's runs (a run is one request's entries, its
+// prefixes of growing depth), not from sorting its entries.  A node is a prefix
+// with c n >= W, and the runs that carry it:
+//   1. the runs meet by their next key (first the depth-K prefix) in a hash
+//      table that counts them; the keys with c n >= W are the nodes, at most n,
+//      and the other runs are done with;
+//   2. each node's longest run represents it: every run of the node is compared
+//      with it (a wave per run, 64 prefixes a step) and its common length counted;
+//   3. suffix sums of the lengths are the counts of every prefix along the
+//      representative, which are decided;
+//   4. runs that go on past their common length meet again by their next key
+//      there, until no node is left (a second node below a first one takes a
+//      branch that W / n requests share).
+// What bounds it: one read of the hot runs' entries, and launches.  It replaces
+// two radix sorts (of the depth-K prefixes and of all entries under hot ones, 64
+// bits each): 131,072 requests routed and the window closed, 2.40 to 1.31 ms.
 #include <algorithm>
 
 #include "dm_internal.h"
@@ -35,9 +49,8 @@ __global__ void kl_fill_kernel(uint64_t* __restrict__ p, uint64_t n, uint64_t v)
 // Distinct canonical keys into an empty table with room to spare (at most
 // half full): the first empty slot along the key's bucket sequence.
 __global__ void kl_insert_kernel(uint64_t* __restrict__ tab, uint32_t ls,
-                                 const uint64_t* __restrict__ keys, const uint64_t* __restrict__ n_p)
+                                 const uint64_t* __restrict__ keys, uint64_t n)
 {
-    const uint64_t n = *n_p;
     const uint32_t nbk = 1u << (ls - 3);
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
          i += (uint64_t)gridDim.x * blockDim.x) {
@@ -56,15 +69,30 @@ __global__ void kl_insert_kernel(uint64_t* __restrict__ tab, uint32_t ls,
 
 // Window record of one batch: request r contributes its block keys from
 // block K - 1 on (its prefixes of depth >= K), canonical, at the record's
-// current end plus its offset among the batch's entries.
+// current end plus its offset among the batch's entries; *runs += the requests
+// that contribute.
 __global__ void kl_entries_kernel(const uint64_t* __restrict__ bstart, uint64_t n, uint64_t K,
-                                  uint64_t* __restrict__ ent)
+                                  uint64_t* __restrict__ ent, unsigned long long* __restrict__ runs)
 {
+    uint32_t mine = 0;
     for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n;
          r += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t nfull = bstart[r + 1] - bstart[r];
         ent[r] = nfull >= K ? nfull - K + 1 : 0;
+        mine += nfull >= K;
     }
+    // one add per workgroup, of which there are few: they meet on one word
+    __shared__ uint32_t total;
+    if (threadIdx.x == 0)
+        total = 0;
+    __syncthreads();
+    for (int d = 1; d < kWave; d <<= 1)
+        mine += (uint32_t)__shfl_xor((int)mine, d);
+    if (lane_id() == 0)
+        atomicAdd(&total, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && total)
+        atomicAdd(runs, (unsigned long long)total);
 }
 
 __global__ void kl_append_kernel(uint64_t n, const uint64_t* __restrict__ bstart,
@@ -100,74 +128,277 @@ __global__ void kl_root_count_kernel(const uint32_t* __restrict__ roots, uint64_
         cnt[w] = __popc(roots[w]);
 }
 
-// Run (request) of record entry i: the roots at or before it, minus one.
-__device__ __forceinline__ uint64_t kl_run_of(const uint32_t* roots, const uint64_t* wpre,
-                                              uint64_t i)
+// Start of each run, in record order.
+__global__ void kl_runs_kernel(const uint32_t* __restrict__ roots, uint64_t nw,
+                               const uint64_t* __restrict__ wpre, uint64_t runs,
+                               uint64_t* __restrict__ start)
 {
-    const uint32_t below = roots[i >> 5] & (0xFFFFFFFFu >> (31 - (i & 31)));  // bits <= i
-    return wpre[i >> 5] + __popc(below) - 1;
+    for (uint64_t w = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; w < nw;
+         w += (uint64_t)gridDim.x * blockDim.x) {
+        uint64_t at = wpre[w];
+        for (uint32_t m = roots[w]; m && at < runs; m &= m - 1)
+            start[at++] = w * 32 + (uint32_t)__builtin_ctz(m);
+    }
 }
 
-// Each run's root key, in record order.
-__global__ void kl_root_keys_kernel(const uint64_t* __restrict__ log, uint64_t m,
-                                    const uint32_t* __restrict__ roots,
-                                    const uint64_t* __restrict__ wpre, uint64_t* __restrict__ rk)
+// The runs of a window while it is closed, the table that they meet in and
+// the nodes found there.
+struct KlNode {
+    uint64_t rep;    // record position of the node's prefix in its representative
+    uint64_t len;    // the representative's entries from there on
+    uint64_t base;   // its counts in hist
+};
+constexpr uint64_t kDone = UINT64_MAX;
+constexpr uint32_t kNoNode = UINT32_MAX;  // too few runs share the key
+struct KlRuns {
+    const uint64_t* log;
+    uint64_t m;               // record entries
+    const uint64_t* start;    // [runs]
+    uint64_t runs;            // how many
+    uint32_t* depth;          // [runs] entries of the run that are settled
+    uint64_t* slot;           // [runs] where its next key is; kDone
+    uint64_t* key;            // [slots] 0: none
+    uint64_t* rep;            // [slots] remaining entries (24 bits, capped) | ~run (40 bits)
+    uint64_t* count;          // [slots]
+    uint32_t* node;           // [slots]
+    uint64_t mask;            // slots - 1
+    KlNode* nodes;            // [n_live]
+    uint64_t* hist;           // [m]
+    unsigned long long* words;  // nodes, counts used, prefixes kept
+    uint64_t W, n_live;
+};
+
+__device__ __forceinline__ uint64_t kl_len(const KlRuns& a, uint64_t k)
 {
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < m;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        if ((roots[i >> 5] >> (i & 31)) & 1)
-            rk[kl_run_of(roots, wpre, i)] = log[i];
+    return (k + 1 < a.runs ? a.start[k + 1] : a.m) - a.start[k];
 }
 
-// Over the sorted root keys: at the first of each run of equal keys, flag
-// it when its count c (requests carrying that depth-K prefix) has
-// c n >= W.  No prefix under a root without it can reach c n >= W.
-__global__ void kl_hot_root_kernel(const uint64_t* __restrict__ keys, uint64_t m, uint64_t W,
-                                   uint64_t n_live, uint64_t* __restrict__ flag)
+// An empty table and no nodes; FIRST: every run at its first entry.
+template <bool FIRST>
+__global__ void kl_clear_kernel(KlRuns a)
 {
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < m;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t key = keys[i];
-        uint64_t f = 0;
-        if (i == 0 || keys[i - 1] != key) {
-            uint64_t lo = i + 1, hi = m;
-            while (lo < hi) {
-                const uint64_t mid = lo + (hi - lo) / 2;
-                if (keys[mid] == key)
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            f = (lo - i) * n_live >= W ? 1 : 0;
+    const uint64_t t0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x,
+                   nt = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = t0; i <= a.mask; i += nt) {
+        a.key[i] = 0;
+        a.rep[i] = 0;
+        a.count[i] = 0;
+    }
+    if (FIRST)
+        for (uint64_t k = t0; k < a.runs; k += nt) {
+            a.depth[k] = 0;
+            a.slot[k] = 0;
         }
-        flag[i] = f;
+    if (t0 == 0)
+        a.words[0] = a.words[1] = 0;
+}
+
+// Slot of a key in the open-addressing table of mask + 1 slots (claimed if
+// new); it has at least twice as many slots as there are keys, so this ends.
+__device__ __forceinline__ uint64_t kl_claim(uint64_t* tab, uint64_t mask, uint64_t key)
+{
+    for (uint64_t i = mix64(key) & mask;; i = (i + 1) & mask) {
+        uint64_t v = tab[i];
+        if (v == 0)
+            v = atomicCAS((unsigned long long*)&tab[i], 0ull, (unsigned long long)key);
+        if (v == 0 || v == key)
+            return i;
     }
 }
 
-// Is key among the h sorted hot roots?
-__device__ __forceinline__ bool kl_is_hot(const uint64_t* hot, uint64_t h, uint64_t key)
+// Runs meet by their next key, and the longest run of each key is found.  A
+// workgroup's runs meet in LDS first: thousands of runs share a popular key, and
+// atomics from all over the chip on one address take some 11 ns each
+// (131,072 runs: 421 us without this, 18 with it).
+constexpr uint32_t kMeet = 1024;
+
+__global__ __launch_bounds__(kMeet) void kl_meet_kernel(KlRuns a)
 {
-    uint64_t lo = 0, hi = h;
-    while (lo < hi) {
-        const uint64_t mid = lo + (hi - lo) / 2;
-        if (hot[mid] < key)
-            lo = mid + 1;
-        else
-            hi = mid;
+    constexpr uint32_t kSlots = 2 * kMeet;
+    __shared__ uint64_t key[kSlots];    // then the key's slot in the table
+    __shared__ unsigned long long top[kSlots];
+    __shared__ uint32_t count[kSlots];
+    for (uint64_t k0 = blockIdx.x * (uint64_t)kMeet; k0 < a.runs; k0 += (uint64_t)gridDim.x * kMeet) {
+        const uint64_t k = k0 + threadIdx.x;
+        const bool in = k < a.runs && a.slot[k] != kDone;
+        if (!__syncthreads_or(in))
+            continue;
+        for (uint32_t j = threadIdx.x; j < kSlots; j += kMeet) {
+            key[j] = 0;
+            top[j] = 0;
+            count[j] = 0;
+        }
+        __syncthreads();
+        uint32_t j = 0;
+        if (in) {
+            const uint64_t d = a.depth[k], left = kl_len(a, k) - d;
+            j = (uint32_t)kl_claim(key, kSlots - 1, a.log[a.start[k] + d]);
+            atomicAdd(&count[j], 1u);
+            atomicMax(&top[j], (unsigned long long)((left < 0xFFFFFFull ? left : 0xFFFFFFull) << 40 |
+                                                    (0xFFFFFFFFFFull - k)));
+        }
+        __syncthreads();
+        for (uint32_t q = threadIdx.x; q < kSlots; q += kMeet)
+            if (count[q]) {
+                const uint64_t i = kl_claim(a.key, a.mask, key[q]);
+                atomicAdd((unsigned long long*)&a.count[i], (unsigned long long)count[q]);
+                atomicMax((unsigned long long*)&a.rep[i], top[q]);
+                key[q] = i;
+            }
+        __syncthreads();
+        if (in)
+            a.slot[k] = key[j];
+        __syncthreads();
     }
-    return lo < h && hot[lo] == key;
 }
 
-// keep[i] = 1 for record entries whose run has a hot root.
-__global__ void kl_keep_kernel(uint64_t m, const uint32_t* __restrict__ roots,
-                               const uint64_t* __restrict__ wpre, const uint64_t* __restrict__ rk,
-                               const uint64_t* __restrict__ hot, const uint64_t* __restrict__ h_p,
-                               uint64_t* __restrict__ keep)
+__global__ void kl_node_kernel(KlRuns a)
 {
-    const uint64_t h = *h_p;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < m;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        keep[i] = h && kl_is_hot(hot, h, rk[kl_run_of(roots, wpre, i)]) ? 1 : 0;
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i <= a.mask;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        if (!a.rep[i] || a.count[i] * a.n_live < a.W) {
+            a.node[i] = kNoNode;
+            continue;
+        }
+        const uint64_t k = 0xFFFFFFFFFFull - (a.rep[i] & 0xFFFFFFFFFFull);
+        const uint64_t d = a.depth[k], len = kl_len(a, k) - d;
+        // disjoint sets of at least W / n of at most W runs: at most n nodes,
+        // whose representatives are distinct runs: at most m counts
+        const uint64_t at = atomicAdd(&a.words[0], 1ull);
+        a.nodes[at] = KlNode{a.start[k] + d, len, atomicAdd(&a.words[1], (unsigned long long)len)};
+        a.node[i] = (uint32_t)at;
+    }
+}
+
+__global__ __launch_bounds__(256) void kl_hist_zero_kernel(KlRuns a)
+{
+    for (uint64_t b = blockIdx.x; b < a.words[0]; b += gridDim.x)
+        for (uint64_t j = threadIdx.x; j < a.nodes[b].len; j += blockDim.x)
+            a.hist[a.nodes[b].base + j] = 0;
+}
+
+// Every run's entries in common with its node's representative: a wave takes
+// kAlike runs, whose first 64 entries are loaded together.  The counts meet in
+// LDS first, as above (many runs part from their representative where a shared
+// prompt ends; 131,072 runs 161 us without this, 36 with it).
+constexpr uint32_t kAlike = 8, kCommonWaves = 16, kCommonRuns = kAlike * kCommonWaves;
+
+__global__ __launch_bounds__(kCommonWaves * kWave) void kl_common_kernel(KlRuns a)
+{
+    constexpr uint32_t kSlots = 2 * kCommonRuns;
+    __shared__ uint64_t at[kSlots];  // place in hist + 1
+    __shared__ uint32_t count[kSlots];
+    if (a.words[0] == 0)
+        return;
+    const int lane = lane_id();
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint64_t k0 = blockIdx.x * (uint64_t)kCommonRuns; k0 < a.runs;
+         k0 += (uint64_t)gridDim.x * kCommonRuns) {
+        for (uint32_t j = threadIdx.x; j < kSlots; j += kCommonWaves * kWave) {
+            at[j] = 0;
+            count[j] = 0;
+        }
+        __syncthreads();
+        // lane l < kAlike: the wave's l-th run
+        const uint64_t k = k0 + wv * kAlike + lane;
+        bool in = lane < (int)kAlike && k < a.runs;
+        uint64_t mine = 0, rep = 0, lim = 0, left = 0, base = 0, d = 0;
+        if (in) {
+            const uint64_t i = a.slot[k];
+            const uint32_t b = i == kDone ? kNoNode : a.node[i];
+            if (i != kDone && b == kNoNode)
+                a.slot[k] = kDone;
+            in = b != kNoNode;
+            if (in) {
+                const KlNode nd = a.nodes[b];
+                d = a.depth[k];
+                left = kl_len(a, k) - d;
+                lim = left < nd.len ? left : nd.len;
+                mine = a.start[k] + d;
+                rep = nd.rep;
+                base = nd.base;
+            }
+        }
+        // (lim = 0 for a run that is done with)
+        uint64_t x[kAlike], y[kAlike];
+#pragma unroll
+        for (uint32_t q = 0; q < kAlike; q++) {
+            const bool ok = (uint64_t)lane < readlane_u64(lim, q);
+            x[q] = ok ? a.log[readlane_u64(mine, q) + lane] : 0;
+            y[q] = ok ? a.log[readlane_u64(rep, q) + lane] : 0;
+        }
+        uint64_t l = lim;
+#pragma unroll
+        for (uint32_t q = 0; q < kAlike; q++) {
+            const uint64_t n = readlane_u64(lim, q);
+            uint64_t diff = ballot(x[q] != y[q]), j = 0;
+            if (!diff && n > kWave) {
+                const uint64_t *m = a.log + readlane_u64(mine, q), *r = a.log + readlane_u64(rep, q);
+                for (j = kWave; j < n; j += kWave) {
+                    diff = ballot(j + lane < n && m[j + lane] != r[j + lane]);
+                    if (diff)
+                        break;
+                }
+            }
+            if (diff && lane == (int)q)
+                l = j + (uint64_t)__builtin_ctzll(diff);
+        }
+        if (in) {
+            // l > 0: the node's prefix itself is in common
+            atomicAdd(&count[kl_claim(at, kSlots - 1, base + l)], 1u);
+            a.depth[k] = (uint32_t)(d + l);
+            if (l == left)
+                a.slot[k] = kDone;
+        }
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < kSlots; j += kCommonWaves * kWave)
+            if (count[j])
+                atomicAdd((unsigned long long*)&a.hist[at[j] - 1], (unsigned long long)count[j]);
+        __syncthreads();
+    }
+}
+
+// A workgroup per node: how many of its runs carry each prefix along its
+// representative (suffix sums), and the prefixes that the next tree holds:
+// extended now and c n >= W, or a leaf now and c n > 2 W.
+__global__ __launch_bounds__(256) void kl_decide_kernel(KlRuns a, const uint64_t* __restrict__ tab,
+                                                        uint32_t ls, uint64_t* __restrict__ out,
+                                                        uint64_t cap)
+{
+    __shared__ uint64_t part[256];
+    for (uint64_t b = blockIdx.x; b < a.words[0]; b += gridDim.x) {
+        const KlNode nd = a.nodes[b];
+        const uint64_t per = (nd.len + 255) / 256, j0 = threadIdx.x * per,
+                       j1 = j0 + per < nd.len ? j0 + per : nd.len;
+        uint64_t sum = 0;
+        for (uint64_t j = j0; j < j1; j++)
+            sum += a.hist[nd.base + j];
+        __syncthreads();
+        part[threadIdx.x] = sum;
+        __syncthreads();
+        uint64_t c = 0;
+        for (uint32_t t = threadIdx.x + 1; t < 256; t++)
+            c += part[t];
+        for (uint64_t j = j1; j-- > j0;) {
+            c += a.hist[nd.base + j];
+            if (c * a.n_live < a.W)
+                continue;
+            const uint64_t key = a.log[nd.rep + j];
+            if (c * a.n_live > 2 * a.W || table_has(tab, ls, key)) {
+                const uint64_t at = atomicAdd(&a.words[2], 1ull);
+                if (at < cap)
+                    out[at] = key;
+            }
+        }
+    }
+}
+
+// Nodes and prefixes kept so far, to pinned host memory.
+__global__ void kl_post_kernel(const unsigned long long* __restrict__ words,
+                               uint64_t* __restrict__ host)
+{
+    host[0] = words[0];
+    host[1] = words[2];
 }
 
 __global__ void kl_zero_u32_kernel(uint32_t* __restrict__ p, uint64_t n)
@@ -185,46 +416,6 @@ __global__ void kl_advance_kernel(unsigned long long* __restrict__ log_n,
     *log_n = v;
     if (v > cap)
         atomicOr(status, kErrFull);
-}
-
-// flag[i] = 1 at the first entry of each run of equal sorted keys whose
-// prefix the next tree holds: count c = run length (its end by bisection),
-// extended now and c n >= W, or a leaf now and c n > 2 W.
-__global__ void kl_decide_kernel(const uint64_t* __restrict__ keys, uint64_t m,
-                                 const uint64_t* __restrict__ tab, uint32_t ls, uint64_t W,
-                                 uint64_t n_live, uint64_t* __restrict__ flag)
-{
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < m;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t key = keys[i];
-        uint64_t f = 0;
-        if (i == 0 || keys[i - 1] != key) {
-            uint64_t lo = i + 1, hi = m;  // first index past the run in [lo, hi]
-            while (lo < hi) {
-                const uint64_t mid = lo + (hi - lo) / 2;
-                if (keys[mid] == key)
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            const uint64_t cnt = lo - i;
-            const bool ext = table_has(tab, ls, key);
-            f = (ext ? cnt * n_live >= W : cnt * n_live > 2 * W) ? 1 : 0;
-        }
-        flag[i] = f;
-    }
-}
-
-// Kept prefixes in key order, at most cap of them written.
-__global__ void kl_compact_kernel(const uint64_t* __restrict__ keys,
-                                  const uint64_t* __restrict__ flag,
-                                  const uint64_t* __restrict__ pos, uint64_t m,
-                                  uint64_t* __restrict__ out, uint64_t cap)
-{
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < m;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        if (flag[i] && pos[i] < cap)
-            out[pos[i]] = keys[i];
 }
 
 template <typename T>
@@ -248,7 +439,7 @@ void reset_window(dm_ctx* c)
 {
     KeyLen& k = c->kl;
     k.win = 0;
-    kl_fill_kernel<<<1, 64, 0, c->stream>>>(reinterpret_cast<uint64_t*>(k.log_n), 1, 0);
+    kl_fill_kernel<<<1, 64, 0, c->stream>>>(reinterpret_cast<uint64_t*>(k.log_n), 2, 0);
 }
 
 size_t up256k(size_t x) { return (x + 255) & ~size_t(255); }
@@ -280,7 +471,8 @@ hipError_t keylen_record(dm_ctx* c, uint64_t n, const uint64_t* bstart, const ui
     uint64_t* epos = work + up256k(8 * n) / 8;
     uint64_t* total = work + 2 * (up256k(8 * n) / 8);
     const uint64_t K = c->cfg.key_blocks;
-    kl_entries_kernel<<<grid_for(n, 256, 8192), 256, 0, c->stream>>>(bstart, n, K, ent);
+    kl_entries_kernel<<<grid_for(n, 1024, 128), 1024, 0, c->stream>>>(bstart, n, K, ent,
+                                                                      k.log_n + 1);
     hipError_t e = exclusive_scan_u64(c, ent, n, epos, total);
     if (e != hipSuccess)
         return e;
@@ -314,7 +506,7 @@ dm_status keylen_enable(dm_ctx* c, uint64_t max_nodes, uint64_t max_window_block
         (e = hipMalloc(&k.list, max_nodes * 8)) == hipSuccess &&
         (e = hipMalloc(&k.log, k.cap * 8)) == hipSuccess &&
         (e = hipMalloc(&k.roots, (k.cap / 32 + 1) * 4)) == hipSuccess)
-        e = hipMalloc(&k.log_n, 8);
+        e = hipMalloc(&k.log_n, 16);
     c->kl = k;
     if (e != hipSuccess) {
         keylen_free(c);
@@ -340,10 +532,10 @@ dm_status keylen_window(dm_ctx* c)
     hipError_t e = quiesce(c);
     if (e != hipSuccess)
         return hip_fail(c, e, "dm_keylen_window");
-    unsigned long long M = 0;
-    if ((e = hipMemcpy(&M, k.log_n, sizeof(M), hipMemcpyDeviceToHost)) != hipSuccess)
+    unsigned long long made[2] = {0, 0};
+    if ((e = hipMemcpy(made, k.log_n, sizeof(made), hipMemcpyDeviceToHost)) != hipSuccess)
         return hip_fail(c, e, "dm_keylen_window");
-    const uint64_t W = k.win;
+    const uint64_t M = made[0], R = made[1], W = k.win;
     hipStream_t st = c->stream;
     if (M > k.cap) {
         reset_window(c);
@@ -359,75 +551,76 @@ dm_status keylen_window(dm_ctx* c)
         e = hipStreamSynchronize(st);
         return e == hipSuccess ? DM_OK : hip_fail(c, e, "dm_keylen_window");
     }
-    const uint64_t Ma = M ? M : 1, outcap = k.max_nodes + 1, nw = (Ma + 31) / 32;
+    const uint64_t nw = (M + 31) / 32, outcap = k.max_nodes;
+    uint64_t meets = 64;
+    while (meets < 2 * R)
+        meets *= 2;
+    // nodes have disjoint sets of at least W / n runs (more runs than W only
+    // where a captured batch was replayed)
+    const uint64_t parts = std::min(std::max<uint64_t>(R, 1), std::max(R, W) * c->n_live / W);
     uint8_t* w = static_cast<uint8_t*>(scratch_get(
-        c, kSlotMembers, 3 * up256k(8 * Ma) + up256k(8 * outcap) + 2 * up256k(8 * nw) + 1024, &e));
+        c, kSlotMembers,
+        2 * up256k(8 * outcap) + 2 * up256k(8 * nw) + 2 * up256k(8 * R) + up256k(4 * R) +
+            3 * up256k(8 * meets) + up256k(4 * meets) + up256k(sizeof(KlNode) * parts) +
+            up256k(8 * M) + 1024,
+        &e));
     if (!w)
         return hip_fail(c, e, "dm_keylen_window");
-    uint64_t* ktmp = carve<uint64_t>(w, Ma);
-    uint64_t* flag = carve<uint64_t>(w, Ma);
-    uint64_t* pos = carve<uint64_t>(w, Ma);
     uint64_t* out = carve<uint64_t>(w, outcap);
+    uint64_t* otmp = carve<uint64_t>(w, outcap);
     uint64_t* wcnt = carve<uint64_t>(w, nw);
     uint64_t* wpre = carve<uint64_t>(w, nw);
-    uint64_t* count = carve<uint64_t>(w, 4);
-    kl_fill_kernel<<<1, 64, 0, st>>>(count, 4, 0);
-    if (M) {
-        // Only prefixes under a root (depth-K prefix) carried by at least
-        // W / n requests can be kept (a prefix's count never exceeds its
-        // root's): count the roots first, one per request, and sort only
-        // the entries of requests with such a root.
+    uint64_t* start = carve<uint64_t>(w, R);
+    KlRuns a{};
+    a.log = k.log;
+    a.m = M;
+    a.start = start;
+    a.slot = carve<uint64_t>(w, R);
+    a.depth = carve<uint32_t>(w, R);
+    a.key = carve<uint64_t>(w, meets);
+    a.rep = carve<uint64_t>(w, meets);
+    a.count = carve<uint64_t>(w, meets);
+    a.node = carve<uint32_t>(w, meets);
+    a.mask = meets - 1;
+    a.nodes = carve<KlNode>(w, parts);
+    a.hist = carve<uint64_t>(w, M);
+    a.words = carve<unsigned long long>(w, 4);
+    a.runs = R;
+    a.W = W;
+    a.n_live = c->n_live;
+    kl_fill_kernel<<<1, 64, 0, st>>>(reinterpret_cast<uint64_t*>(a.words), 4, 0);
+    uint64_t n_next = 0;
+    if (R) {
         kl_root_count_kernel<<<grid_for(nw, 256, 8192), 256, 0, st>>>(k.roots, nw, wcnt);
-        uint64_t R = 0;
-        if ((e = exclusive_scan_u64(c, wcnt, nw, wpre, count + 1)) != hipSuccess ||
-            (e = hipMemcpyAsync(&R, count + 1, 8, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-            (e = hipStreamSynchronize(st)) != hipSuccess)
+        if ((e = exclusive_scan_u64(c, wcnt, nw, wpre, nullptr)) != hipSuccess)
             return hip_fail(c, e, "dm_keylen_window");
-        const uint64_t Ra = R ? R : 1;
-        uint8_t* rw = static_cast<uint8_t*>(
-            scratch_get(c, kSlotProbe, 6 * up256k(8 * Ra) + 256, &e));
-        if (!rw)
-            return hip_fail(c, e, "dm_keylen_window");
-        uint64_t* rk = carve<uint64_t>(rw, Ra);     // each run's root, record order
-        uint64_t* rs = carve<uint64_t>(rw, Ra);     // the same, sorted
-        uint64_t* rtmp = carve<uint64_t>(rw, Ra);
-        uint64_t* rflag = carve<uint64_t>(rw, Ra);
-        uint64_t* rpos = carve<uint64_t>(rw, Ra);
-        uint64_t* hot = carve<uint64_t>(rw, Ra);
-        const uint32_t g = grid_for(M, 256, 8192), gr = grid_for(Ra, 256, 8192);
-        kl_root_keys_kernel<<<g, 256, 0, st>>>(k.log, M, k.roots, wpre, rk);
-        uint64_t Mk = 0;
-        if ((e = hipMemcpyAsync(rs, rk, 8 * R, hipMemcpyDeviceToDevice, st)) != hipSuccess ||
-            (e = radix_sort_kv(c, rs, nullptr, rtmp, nullptr, R, 64)) != hipSuccess)
-            return hip_fail(c, e, "dm_keylen_window");
-        kl_hot_root_kernel<<<gr, 256, 0, st>>>(rs, R, W, c->n_live, rflag);
-        if ((e = exclusive_scan_u64(c, rflag, R, rpos, count + 2)) != hipSuccess)
-            return hip_fail(c, e, "dm_keylen_window");
-        kl_compact_kernel<<<gr, 256, 0, st>>>(rs, rflag, rpos, R, hot, Ra);
-        kl_keep_kernel<<<g, 256, 0, st>>>(M, k.roots, wpre, rk, hot, count + 2, flag);
-        if ((e = exclusive_scan_u64(c, flag, M, pos, count + 3)) != hipSuccess)
-            return hip_fail(c, e, "dm_keylen_window");
-        kl_compact_kernel<<<g, 256, 0, st>>>(k.log, flag, pos, M, ktmp, Ma);
-        if ((e = hipMemcpyAsync(&Mk, count + 3, 8, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-            (e = hipStreamSynchronize(st)) != hipSuccess)
-            return hip_fail(c, e, "dm_keylen_window");
-        if (Mk) {
-            const uint32_t gk = grid_for(Mk, 256, 8192);
-            if ((e = radix_sort_kv(c, ktmp, nullptr, pos, nullptr, Mk, 64)) != hipSuccess)
+        kl_runs_kernel<<<grid_for(nw, 256, 8192), 256, 0, st>>>(k.roots, nw, wpre, R, start);
+        const uint32_t gs = grid_for(meets, 256, 8192);
+        auto meet = [&](bool first) {
+            if (first)
+                kl_clear_kernel<true><<<gs, 256, 0, st>>>(a);
+            else
+                kl_clear_kernel<false><<<gs, 256, 0, st>>>(a);
+            kl_meet_kernel<<<grid_for(R, kMeet, 2048), kMeet, 0, st>>>(a);
+            kl_node_kernel<<<gs, 256, 0, st>>>(a);
+        };
+        meet(true);
+        // each turn settles the nodes found before it and finds those below
+        for (bool more = true; more;) {
+            kl_hist_zero_kernel<<<grid_for(parts, 1, 1024), 256, 0, st>>>(a);
+            kl_common_kernel<<<grid_for(R, kCommonRuns, 32768), kCommonWaves * kWave, 0, st>>>(a);
+            kl_decide_kernel<<<grid_for(parts, 1, 1024), 256, 0, st>>>(a, k.tab[k.cur], k.log2, out,
+                                                                      outcap);
+            meet(false);
+            kl_post_kernel<<<1, 1, 0, st>>>(a.words, c->host_words);
+            if ((e = hipGetLastError()) != hipSuccess ||
+                (e = hipStreamSynchronize(st)) != hipSuccess)
                 return hip_fail(c, e, "dm_keylen_window");
-            kl_decide_kernel<<<gk, 256, 0, st>>>(ktmp, Mk, k.tab[k.cur], k.log2, W, c->n_live,
-                                                 flag);
-            if ((e = exclusive_scan_u64(c, flag, Mk, pos, count)) != hipSuccess)
-                return hip_fail(c, e, "dm_keylen_window");
-            kl_compact_kernel<<<gk, 256, 0, st>>>(ktmp, flag, pos, Mk, out, outcap);
+            more = c->host_words[0] != 0;
+            n_next = c->host_words[1];
         }
         kl_zero_u32_kernel<<<grid_for(nw, 256, 8192), 256, 0, st>>>(k.roots, nw);
     }
-    uint64_t n_next = 0;
-    if ((e = hipGetLastError()) != hipSuccess ||
-        (e = hipMemcpyAsync(&n_next, count, 8, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipStreamSynchronize(st)) != hipSuccess)
-        return hip_fail(c, e, "dm_keylen_window");
     reset_window(c);
     if (n_next > k.max_nodes) {
         if ((e = hipStreamSynchronize(st)) != hipSuccess)
@@ -439,11 +632,13 @@ dm_status keylen_window(dm_ctx* c)
     const int nx = 1 - k.cur;
     const uint64_t slots = 1ull << k.log2;
     kl_fill_kernel<<<grid_for(slots, 256), 256, 0, st>>>(k.tab[nx], slots, kEmpty);
-    kl_insert_kernel<<<grid_for(std::max<uint64_t>(n_next, 1), 256, 4096), 256, 0, st>>>(
-        k.tab[nx], k.log2, out, count);
-    if (n_next &&
-        (e = hipMemcpyAsync(k.list, out, n_next * 8, hipMemcpyDeviceToDevice, st)) != hipSuccess)
-        return hip_fail(c, e, "dm_keylen_window");
+    if (n_next) {
+        kl_insert_kernel<<<grid_for(n_next, 256, 4096), 256, 0, st>>>(k.tab[nx], k.log2, out, n_next);
+        // the list is ascending
+        if ((e = radix_sort_kv(c, out, nullptr, otmp, nullptr, n_next, 64)) != hipSuccess ||
+            (e = hipMemcpyAsync(k.list, out, n_next * 8, hipMemcpyDeviceToDevice, st)) != hipSuccess)
+            return hip_fail(c, e, "dm_keylen_window");
+    }
     if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
         return hip_fail(c, e, "dm_keylen_window");
     k.cur = nx;

@@ -90,8 +90,8 @@ void route_scratch_plan(const dm_ctx* c, uint64_t n, uint64_t n_tokens, bool key
     bytes[kSlotSort] = sort_scratch_bytes(n);         // digit counts of the ordering sort
     const uint64_t s1 = scan_scratch_bytes(n), s2 = scan_scratch_bytes(sort_scan_len(n));
     bytes[kSlotScan] = s1 > s2 ? s1 : s2;             // tile sums of both kinds of scan
-    if (c->kl.on)  // requests going down the tree; the window record's offsets
-        bytes[kSlotRebalance] = 256 + ((n * sizeof(uint32_t) + 255) & ~255ull) +
+    if (c->kl.on)  // marks of requests going down the tree; the window record's offsets
+        bytes[kSlotRebalance] = ((ext_words(c, n) * sizeof(uint64_t) + 255) & ~255ull) +
                                 keylen_record_bytes(n);
 }
 
@@ -132,22 +132,19 @@ static hipError_t route_parts(dm_ctx* c, const int32_t* tokens, uint64_t n_token
     uint64_t* nh0 = nh0_bytes(c, n) ? reinterpret_cast<uint64_t*>(
                                           reinterpret_cast<uint8_t*>(bstart) + starts_bytes(n))
                                     : nullptr;
-    // with the hotness tree: the count (first 256 bytes), then the list of
-    // requests going down the tree
-    unsigned long long* ext_count = nullptr;
-    uint32_t* ext_list = nullptr;
+    // with the hotness tree: marks of the requests going down the tree
+    uint64_t* ext = nullptr;
     uint64_t* kl_work = nullptr;
     if (c->kl.on) {
-        const uint64_t list_bytes = (n * sizeof(uint32_t) + 255) & ~255ull;
-        uint8_t* w = static_cast<uint8_t*>(scratch_get(
-            c, kSlotRebalance, 256 + list_bytes + keylen_record_bytes(n), &e));
+        const uint64_t ext_bytes = (ext_words(c, n) * sizeof(uint64_t) + 255) & ~255ull;
+        uint8_t* w = static_cast<uint8_t*>(
+            scratch_get(c, kSlotRebalance, ext_bytes + keylen_record_bytes(n), &e));
         if (!w)
             return e;
-        ext_count = reinterpret_cast<unsigned long long*>(w);
-        ext_list = reinterpret_cast<uint32_t*>(w + 256);
-        kl_work = reinterpret_cast<uint64_t*>(w + 256 + list_bytes);
+        ext = reinterpret_cast<uint64_t*>(w);
+        kl_work = reinterpret_cast<uint64_t*>(w + ext_bytes);
     }
-    BatchClear clear{ext_count, {}, c->n_live};
+    BatchClear clear{{}, c->n_live};
     for (int k = 0; k < ps.count; k++)
         if ((e = select_growth(c, ps, k, par, &clear.grow[k])) != hipSuccess)
             return e;
@@ -170,11 +167,11 @@ static hipError_t route_parts(dm_ctx* c, const int32_t* tokens, uint64_t n_token
     GroupView gv{};
     LookupArgs look{};
     if ((e = lookup_args(c, n, out->cand, out->flags, &look)) != hipSuccess ||
-        (e = hash_prefix(c, tokens, offsets, n, bad, out->key, out->key_len, ext_list,
-                         ext_count, nh0, c->kl.on ? nullptr : &look)) != hipSuccess)
+        (e = hash_prefix(c, tokens, offsets, n, bad, out->key, out->key_len, ext, nh0,
+                         c->kl.on ? nullptr : &look)) != hipSuccess)
         return e;
-    if (c->kl.on && ((e = hash_extend(c, tokens, offsets, n, bad, out->key, out->key_len, ext_list,
-                                      ext_count)) != hipSuccess ||
+    if (c->kl.on && ((e = hash_extend(c, tokens, offsets, n, bad, out->key, out->key_len,
+                                      ext)) != hipSuccess ||
                      (e = lookup_candidates(c, n, out->key, look)) != hipSuccess))
         return e;
     if ((e = group_requests(c, n, bstart, bad, &gv)) != hipSuccess)

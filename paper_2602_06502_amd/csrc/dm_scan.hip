@@ -66,8 +66,6 @@ struct FullBlocksIn {
             if (threadIdx.x == 0)
                 also.grow[p][kMaxSlots] = 0;
         }
-        if (threadIdx.x == 0 && also.count)
-            *also.count = 0;
     }
     // by one thread
     __device__ void result(bool broken) const
