@@ -121,14 +121,17 @@ __global__ void zero_u64_kernel(uint64_t* p, uint32_t n)
         p[threadIdx.x] = 0;
 }
 
-__global__ void remap_kernel(RingView o1, RingView o2, RingView n1, RingView n2,
+constexpr int kRemapThreads = 1024;
+
+__global__ __launch_bounds__(kRemapThreads) void remap_kernel(RingView o1, RingView o2, RingView n1, RingView n2,
                              const uint64_t* __restrict__ keys, uint64_t n,
                              const uint8_t* __restrict__ is_add, const uint8_t* __restrict__ is_rm,
                              uint32_t* __restrict__ old_owner, uint32_t* __restrict__ new_owner,
                              uint64_t* __restrict__ moved, uint64_t* __restrict__ violations)
 {
     // counts gather per wave over the grid-stride loop, then per workgroup in
-    // LDS: three device atomics per workgroup, not per wave
+    // LDS: three device atomics per workgroup, not per wave, and few large
+    // workgroups (those that meet on one word take some 11 ns each)
     __shared__ unsigned long long s_cnt[3];
     if (threadIdx.x < 3)
         s_cnt[threadIdx.x] = 0;
@@ -258,7 +261,7 @@ hipError_t ring_remap(dm_ctx* c, const Ring old_r[2], const Ring new_r[2], const
     zero_u64_kernel<<<1, 64, 0, c->stream>>>(moved, 2);
     zero_u64_kernel<<<1, 64, 0, c->stream>>>(violations, 1);
     if (n)
-        remap_kernel<<<grid_for(2 * n, 256, 1024), 256, 0, c->stream>>>(
+        remap_kernel<<<grid_for(2 * n, kRemapThreads, 256), kRemapThreads, 0, c->stream>>>(
             view(old_r[0]), view(old_r[1]), view(new_r[0]), view(new_r[1]), keys, n,
             c->d_flag_add, c->d_flag_rm, old_owner, new_owner, moved, violations);
     return hipGetLastError();
