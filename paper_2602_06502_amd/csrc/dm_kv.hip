@@ -7,7 +7,7 @@
 // The record of saved keys is a flat array of (instance, key, time of the
 // latest touch).  One save:
 //   1. the record's entries and the batch's touches meet in a hash table with
-//      a region per instance (kv_record_kernel, kv_touch_kernel): a slot
+//      a region per instance (kv_home, kv_record and kv_touch_kernel): a slot
 //      holds a key, its latest time and whether the record had it;
 //   2. each region's occupied slots are packed to its front
 //      (kv_pack_kernel);
@@ -22,7 +22,8 @@
 // a time word) and the launches.  It replaces sorting record and touches by
 // key, instance and time (19 radix passes and 14 scans).  Routing and saving
 // 16,384 agent requests, 2.3 M touches on a record of 1 M keys, went from
-// 2.39 to 1.27 ms; 4,096 chat requests, 1.1 M touches, from 1.45 to 0.69 ms.
+// 2.39 to 1.27 ms; 4,096 chat requests, 1.1 M touches, from 1.45 to 0.69 ms
+// (later steps: 1.19 and 0.55).
 #include <algorithm>
 #include <vector>
 
@@ -70,12 +71,17 @@ __device__ __forceinline__ uint32_t tile_instance(const uint32_t* first, uint32_
     return found;
 }
 
+__device__ __forceinline__ uint32_t kv_home(uint32_t size, uint64_t k)
+{
+    return (uint32_t)(((mix64(k) >> 32) * size) >> 32);
+}
+
 // Slot of key k in the region of `size` + 1 slots at base (claimed if new).
 __device__ __forceinline__ uint64_t kv_slot(uint64_t* key, uint64_t base, uint32_t size, uint64_t k)
 {
     if (k == 0)
         return base + size;
-    uint32_t i = (uint32_t)(((mix64(k) >> 32) * size) >> 32);
+    uint32_t i = kv_home(size, k);
     for (uint32_t step = 0; step < size; step++) {
         uint64_t* p = key + base + i;
         const uint64_t v = *p;
@@ -116,6 +122,11 @@ __global__ void kv_check_kernel(const uint32_t* __restrict__ inst, uint64_t n, u
         if (cnt[c])
             atomicAdd(&touches[c], cnt[c]);
 }
+
+// Counters that workgroups of many tiles add to lie a line apart: atomics on one
+// line take some 11 ns each, wherever they come from (1,237 tiles of 16 instances:
+// packing 29 us without this and 18 with it, keeping 36 and 29).
+constexpr uint32_t kApart = 128 / sizeof(uint64_t);
 
 // Regions: 1.5 slots per entry that instance c may hold (its record entries
 // and its touches), first[c] = tiles before it.  One workgroup; tiles are
@@ -173,6 +184,24 @@ __device__ __forceinline__ uint32_t region_size(const KvSlots& h, uint32_t c)
     // slots but key 0's; a region never needs 2^32 slots (entries < 2^32)
     const uint64_t slots = (uint64_t)(h.first[c + 1] - h.first[c]) * kTile - 1;
     return (uint32_t)(slots < 0xFFFFFFFFull ? slots : 0xFFFFFFFFull);
+}
+
+// The record's keys (distinct) into their home slots, before anything else is in
+// the table: where several share one, any of them gets it, and kv_record_kernel
+// claims places for the others.  Random claims go at some 3.3 G/s on the whole
+// chip, plain stores several times faster: 259,000 entries 80 us by claims
+// alone, 14 + 39 us so.
+__global__ void kv_home_kernel(const uint64_t* __restrict__ rkey, const uint32_t* __restrict__ rinst,
+                               uint64_t nrec, KvSlots h)
+{
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < nrec;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t k = rkey[i];
+        const uint32_t c = rinst[i];
+        if (k)
+            __hip_atomic_store(h.key + (uint64_t)h.first[c] * kTile + kv_home(region_size(h, c), k), k,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 __global__ void kv_record_kernel(const uint64_t* __restrict__ rkey, const uint64_t* __restrict__ rt,
@@ -259,11 +288,11 @@ __device__ __forceinline__ uint32_t tile_excl(uint32_t v, uint32_t& total)
 }
 
 // A region's occupied slots to the front of its place in the packed arrays
-// (any order); used[c] = how many.
+// (any order); used[c * kApart] = how many.
 __global__ __launch_bounds__(kTileThreads) void kv_pack_kernel(KvSlots h, uint32_t S,
                                                                uint64_t* __restrict__ key,
                                                                uint64_t* __restrict__ word,
-                                                               uint32_t* __restrict__ used)
+                                                               unsigned long long* __restrict__ used)
 {
     __shared__ uint32_t at0;
     const uint32_t c = tile_instance(h.first, S, blockIdx.x);
@@ -277,7 +306,7 @@ __global__ __launch_bounds__(kTileThreads) void kv_pack_kernel(KvSlots h, uint32
     }
     uint32_t at = tile_excl(mine, total);
     if (threadIdx.x == 0)
-        at0 = total ? atomicAdd(&used[c], total) : 0;
+        at0 = total ? (uint32_t)atomicAdd(&used[c * kApart], (unsigned long long)total) : 0;
     __syncthreads();
     uint64_t out = (uint64_t)h.first[c] * kTile + at0 + at;
 #pragma unroll
@@ -309,14 +338,14 @@ __device__ __forceinline__ uint64_t rel_time(uint64_t word, uint64_t lo) { retur
 template <bool FIRST>
 __global__ __launch_bounds__(kTileThreads) void kv_hist_kernel(const uint32_t* __restrict__ first,
                                                                uint32_t S,
-                                                               const uint32_t* __restrict__ used,
+                                                               const unsigned long long* __restrict__ used,
                                                                const uint64_t* __restrict__ word,
                                                                KvSelect s, uint32_t shift,
                                                                uint32_t bits)
 {
     __shared__ uint32_t cnt[1u << kDigit0];
     const uint32_t c = tile_instance(first, S, blockIdx.x);
-    const uint32_t n = used[c];
+    const uint32_t n = (uint32_t)used[c * kApart];
     const uint64_t i0 = (uint64_t)(blockIdx.x - first[c]) * kTile;
     if (i0 >= n || (FIRST ? n <= s.cap : s.rem[c] == 0))
         return;
@@ -347,11 +376,12 @@ __global__ __launch_bounds__(kTileThreads) void kv_hist_kernel(const uint32_t* _
 // The digit of the last key dropped, a workgroup per instance; clears the
 // counts for the next digit.
 template <bool FIRST>
-__global__ __launch_bounds__(kTileThreads) void kv_pick_kernel(const uint32_t* __restrict__ used,
+__global__ __launch_bounds__(kTileThreads) void kv_pick_kernel(const unsigned long long* __restrict__ used,
                                                                KvSelect s, uint32_t bits)
 {
     const uint32_t c = blockIdx.x;
-    const uint32_t rem = FIRST ? (used[c] > s.cap ? (uint32_t)(used[c] - s.cap) : 0) : s.rem[c];
+    const uint64_t held = used[c * kApart];
+    const uint32_t rem = FIRST ? (held > s.cap ? (uint32_t)(held - s.cap) : 0) : s.rem[c];
     if (rem == 0) {
         if (FIRST && threadIdx.x == 0)
             s.rem[c] = 0;
@@ -378,7 +408,7 @@ __global__ __launch_bounds__(kTileThreads) void kv_pick_kernel(const uint32_t* _
 // Of an instance's keys with the time of the last one dropped, the smallest
 // go first: the largest of them to drop, bit by bit (all of them: any key).
 __global__ __launch_bounds__(kTileThreads) void kv_tie_kernel(const uint32_t* __restrict__ first,
-                                                              const uint32_t* __restrict__ used,
+                                                              const unsigned long long* __restrict__ used,
                                                               const uint64_t* __restrict__ key,
                                                               const uint64_t* __restrict__ word,
                                                               KvSelect s)
@@ -391,10 +421,11 @@ __global__ __launch_bounds__(kTileThreads) void kv_tie_kernel(const uint32_t* __
         return;
     }
     const uint64_t base = (uint64_t)first[c] * kTile, T = s.prefix[c];
+    const uint32_t n = (uint32_t)used[c * kApart];
     uint64_t last = 0;
     for (int bit = 63; bit >= 0; bit--) {
         uint32_t low = 0;
-        for (uint32_t i = threadIdx.x; i < used[c]; i += kTileThreads)
+        for (uint32_t i = threadIdx.x; i < n; i += kTileThreads)
             low += rel_time(word[base + i], s.lo) == T && key[base + i] >> bit == last << 1;
         low = tile_sum(low);
         last <<= 1;
@@ -409,13 +440,52 @@ __global__ __launch_bounds__(kTileThreads) void kv_tie_kernel(const uint32_t* __
 
 // Results of a save: per instance the keys to insert and whether its table
 // has room for them, its occupied slots afterwards; record entries, erased
-// and inserted keys, the smallest time kept.
+// and inserted keys, ~the smallest time kept.  While the tiles are gone through,
+// each in a counter of its own per instance (kTallies a line apart).
+enum { kPlace, kErased, kInserted, kTime, kTallies };
 struct KvOut {
     uint32_t* ins;
     uint32_t* fits;
     uint64_t* occ;
-    unsigned long long* sum;  // record entries, erased, inserted, ~smallest time
+    uint64_t* sum;              // record entries, erased, inserted, ~smallest time
+    unsigned long long* tally;  // [S * kTallies * kApart]
 };
+
+__device__ __forceinline__ unsigned long long* kv_tally(const KvOut& o, uint32_t c, uint32_t which)
+{
+    return o.tally + ((uint64_t)c * kTallies + which) * kApart;
+}
+
+// Record entries per instance (an instance keeps its cap, or what it has) and
+// where they go.
+__global__ __launch_bounds__(1024) void kv_place_kernel(const unsigned long long* __restrict__ used,
+                                                        uint32_t S, uint64_t cap, KvOut o,
+                                                        uint32_t* __restrict__ rcount)
+{
+    __shared__ uint64_t part[1024];
+    const uint32_t per = (S + 1023) / 1024, c0 = threadIdx.x * per;
+    uint64_t sum = 0;
+    for (uint32_t c = c0; c < c0 + per && c < S; c++) {
+        const uint64_t kept = used[c * kApart] < cap ? used[c * kApart] : cap;
+        rcount[c] = (uint32_t)kept;
+        sum += kept;
+    }
+    part[threadIdx.x] = sum;
+    __syncthreads();
+    for (uint32_t d = 1; d < 1024; d <<= 1) {
+        const uint64_t x = threadIdx.x >= d ? part[threadIdx.x - d] : 0;
+        __syncthreads();
+        part[threadIdx.x] += x;
+        __syncthreads();
+    }
+    uint64_t at = part[threadIdx.x] - sum;
+    for (uint32_t c = c0; c < c0 + per && c < S; c++) {
+        *kv_tally(o, c, kPlace) = at;
+        at += rcount[c];
+    }
+    if (threadIdx.x == 1023)
+        o.sum[0] = part[1023];
+}
 
 __device__ __forceinline__ bool kv_dropped(const KvSelect& s, uint32_t c, uint32_t rem, uint64_t k,
                                            uint64_t w)
@@ -429,15 +499,14 @@ __device__ __forceinline__ bool kv_dropped(const KvSelect& s, uint32_t c, uint32
 // The kept keys into the new record, the dropped ones that were cached out
 // of their index.
 __global__ __launch_bounds__(kTileThreads) void kv_keep_kernel(
-    const uint32_t* __restrict__ first, uint32_t S, const uint32_t* __restrict__ used,
+    const uint32_t* __restrict__ first, uint32_t S, const unsigned long long* __restrict__ used,
     const uint64_t* __restrict__ key, const uint64_t* __restrict__ word, KvSelect s, KvOut o,
     uint64_t* __restrict__ tables, uint64_t* __restrict__ live, uint32_t log2slots,
-    uint64_t* __restrict__ rkey, uint64_t* __restrict__ rt, uint32_t* __restrict__ rinst,
-    uint32_t* __restrict__ rcount)
+    uint64_t* __restrict__ rkey, uint64_t* __restrict__ rt, uint32_t* __restrict__ rinst)
 {
     __shared__ unsigned long long at0, tmin;
     const uint32_t c = tile_instance(first, S, blockIdx.x);
-    const uint32_t n = used[c];
+    const uint32_t n = (uint32_t)used[c * kApart];
     const uint64_t i0 = (uint64_t)(blockIdx.x - first[c]) * kTile;
     if (i0 >= n)
         return;
@@ -476,19 +545,15 @@ __global__ __launch_bounds__(kTileThreads) void kv_keep_kernel(
         atomicMin(&tmin, (unsigned long long)mn);
     __syncthreads();
     if (threadIdx.x == 0) {
-        at0 = total ? atomicAdd(&o.sum[0], (unsigned long long)total) : 0;
-        if (total)
-            atomicAdd(&rcount[c], total);
+        at0 = total ? atomicAdd(kv_tally(o, c, kPlace), (unsigned long long)total) : 0;
         if (erase)
-            atomicAdd(&o.sum[1], (unsigned long long)erase);
+            atomicAdd(kv_tally(o, c, kErased), (unsigned long long)erase);
         if (gone)
             atomicAdd((unsigned long long*)&live[c], 0ull - gone);
-        if (add) {
-            atomicAdd(&o.sum[2], (unsigned long long)add);
-            atomicAdd(&o.ins[c], add);
-        }
+        if (add)
+            atomicAdd(kv_tally(o, c, kInserted), (unsigned long long)add);
         if (tmin != UINT64_MAX)
-            atomicMax(&o.sum[3], ~tmin);
+            atomicMax(kv_tally(o, c, kTime), ~tmin);
     }
     __syncthreads();
     uint64_t out = at0 + at;
@@ -504,13 +569,13 @@ __global__ __launch_bounds__(kTileThreads) void kv_keep_kernel(
 // The kept keys that were not cached into the indexes that have room for
 // all of theirs (the count words grow once per workgroup).
 __global__ __launch_bounds__(kTileThreads) void kv_insert_kernel(
-    const uint32_t* __restrict__ first, uint32_t S, const uint32_t* __restrict__ used,
+    const uint32_t* __restrict__ first, uint32_t S, const unsigned long long* __restrict__ used,
     const uint64_t* __restrict__ key, const uint64_t* __restrict__ word, KvSelect s, KvOut o,
     uint64_t* __restrict__ tables, uint64_t* __restrict__ counts, uint32_t log2slots,
     uint32_t* __restrict__ status)
 {
     const uint32_t c = tile_instance(first, S, blockIdx.x);
-    const uint32_t n = used[c];
+    const uint32_t n = (uint32_t)used[c * kApart];
     const uint64_t i0 = (uint64_t)(blockIdx.x - first[c]) * kTile;
     if (i0 >= n || o.ins[c] == 0 || !o.fits[c])
         return;
@@ -534,25 +599,38 @@ __global__ __launch_bounds__(kTileThreads) void kv_insert_kernel(
 }
 
 // Which tables have room for their keys without a rebuild (the others are
-// left to index_insert, with its rebuild and overflow handling).
-__global__ void kv_fits_kernel(const uint64_t* __restrict__ counts, uint32_t S, uint64_t limit,
-                               KvOut o)
+// left to index_insert, with its rebuild and overflow handling), and the
+// tallies together.  One workgroup.
+__global__ __launch_bounds__(256) void kv_fits_kernel(const uint64_t* __restrict__ counts,
+                                                      uint32_t S, uint64_t limit, KvOut o)
 {
-    for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < S; c += gridDim.x * blockDim.x) {
-        o.fits[c] = counts[S + c] + o.ins[c] <= limit;
-        o.occ[c] = counts[S + c] + o.ins[c];
+    __shared__ unsigned long long sum[3];
+    if (threadIdx.x < 3)
+        sum[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t c = threadIdx.x; c < S; c += 256) {
+        const uint64_t add = *kv_tally(o, c, kInserted);
+        o.ins[c] = (uint32_t)add;
+        o.fits[c] = counts[S + c] + add <= limit;
+        o.occ[c] = counts[S + c] + add;
+        atomicAdd(&sum[0], *kv_tally(o, c, kErased));
+        atomicAdd(&sum[1], (unsigned long long)add);
+        atomicMax(&sum[2], *kv_tally(o, c, kTime));
     }
+    __syncthreads();
+    if (threadIdx.x < 3)
+        o.sum[1 + threadIdx.x] = sum[threadIdx.x];
 }
 
 // Instance c's keys to insert, as a list (any order).
 __global__ __launch_bounds__(kTileThreads) void kv_list_kernel(
-    const uint32_t* __restrict__ first, const uint32_t* __restrict__ used,
+    const uint32_t* __restrict__ first, const unsigned long long* __restrict__ used,
     const uint64_t* __restrict__ key, const uint64_t* __restrict__ word, KvSelect s, uint32_t c,
     uint64_t* __restrict__ list, unsigned long long* __restrict__ len)
 {
     const uint32_t rem = s.rem[c];
     const uint64_t base = (uint64_t)first[c] * kTile;
-    const uint32_t n = used[c];
+    const uint32_t n = (uint32_t)used[c * kApart];
     for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {
         const uint32_t i = i0 + threadIdx.x;
         const uint64_t k = i < n ? key[base + i] : 0, w = i < n ? word[base + i] : 1;
@@ -736,11 +814,12 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
     }
     // the hash table and its packed form, the select's state, the results
     const uint64_t slots = (uint64_t)tiles * kTile;
-    const uint64_t zeroed = 8 * slots * 2 + up256v((4ull * S) << kDigit) + up256v(4 * (size_t)S) +
-                            up256v(4 * (size_t)S) + 256;
+    const size_t apart = 8 * (size_t)kApart * S;  // a counter per instance
+    const uint64_t zeroed = 8 * slots * 2 + up256v((4ull * S) << kDigit) + up256v(apart) +
+                            up256v(kTallies * apart);
     uint8_t* w = static_cast<uint8_t*>(scratch_get(
         c, kSlotMembers,
-        zeroed + 16 * slots + 2 * up256v(8 * (size_t)S) + 3 * up256v(4 * (size_t)S) +
+        zeroed + 16 * slots + 2 * up256v(8 * (size_t)S) + 4 * up256v(4 * (size_t)S) +
             up256v(8 * (size_t)S) + 4096,
         &e));
     if (!w)
@@ -752,10 +831,11 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
     h.first = first;
     KvSelect s{};
     s.hist = carve<uint32_t>(w, (uint64_t)S << kDigit);
-    uint32_t* used = carve<uint32_t>(w, S);
+    unsigned long long* used = carve<unsigned long long>(w, (uint64_t)S * kApart);
     KvOut o{};
+    o.tally = carve<unsigned long long>(w, (uint64_t)S * kApart * kTallies);  // cleared up to here
     o.ins = carve<uint32_t>(w, S);
-    o.sum = carve<unsigned long long>(w, 8);  // cleared up to here
+    o.sum = carve<uint64_t>(w, 8);
     uint64_t* key = carve<uint64_t>(w, slots);
     uint64_t* word = carve<uint64_t>(w, slots);
     s.prefix = carve<uint64_t>(w, S);
@@ -774,9 +854,11 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
     const uint64_t tmax = std::max(rec.n ? rec.tmax : 0, clock + (E ? E - 1 : 0));
     kv_zero_kernel<<<grid_for(zeroed / 8, 256, 4096), 256, 0, st>>>(
         reinterpret_cast<unsigned long long*>(w1), zeroed / 8);
-    if (rec.n)
+    if (rec.n) {
+        kv_home_kernel<<<grid_for(rec.n, 256, 8192), 256, 0, st>>>(rec.key[a], rec.inst[a], rec.n, h);
         kv_record_kernel<<<grid_for(rec.n, 256, 8192), 256, 0, st>>>(rec.key[a], rec.t[a],
                                                                      rec.inst[a], rec.n, h);
+    }
     if (E)
         kv_touch_kernel<<<grid_for(n, 4, 8192), 256, 0, st>>>(n, bstart, block_keys, inst, clock,
                                                               h);
@@ -802,12 +884,11 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
         }
         kv_tie_kernel<<<S, kTileThreads, 0, st>>>(first, used, key, word, s);
     }
-    kv_zero_kernel<<<grid_for(S, 256), 256, 0, st>>>(
-        reinterpret_cast<unsigned long long*>(rec.count), (S + 1) / 2);
+    kv_place_kernel<<<1, 1024, 0, st>>>(used, S, s.cap, o, rec.count);
     kv_keep_kernel<<<tiles, kTileThreads, 0, st>>>(first, S, used, key, word, s, o, c->d_tables,
                                                    c->d_counts, log2slots, rec.key[b], rec.t[b],
-                                                   rec.inst[b], rec.count);
-    kv_fits_kernel<<<grid_for(S, 256), 256, 0, st>>>(c->d_counts, S, 1ull << (log2slots - 1), o);
+                                                   rec.inst[b]);
+    kv_fits_kernel<<<1, 256, 0, st>>>(c->d_counts, S, 1ull << (log2slots - 1), o);
     kv_insert_kernel<<<tiles, kTileThreads, 0, st>>>(first, S, used, key, word, s, o, c->d_tables,
                                                      c->d_counts, log2slots, c->d_status);
     if ((e = hipGetLastError()) != hipSuccess)
@@ -838,9 +919,9 @@ dm_status kv_save(dm_ctx* c, const int64_t* offsets, uint64_t n, const uint64_t*
             continue;
         }
         listed = true;
-        kv_zero_kernel<<<1, 64, 0, st>>>(o.sum, 1);
+        kv_zero_kernel<<<1, 64, 0, st>>>(reinterpret_cast<unsigned long long*>(o.sum), 1);
         kv_list_kernel<<<grid_for(ins[i], 256, 1024), kTileThreads, 0, st>>>(
-            first, used, key, word, s, i, h.key, o.sum);
+            first, used, key, word, s, i, h.key, reinterpret_cast<unsigned long long*>(o.sum));
         if ((e = index_insert(c, i, h.key, ins[i])) != hipSuccess)
             return failed(e);
     }
