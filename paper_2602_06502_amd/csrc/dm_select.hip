@@ -19,8 +19,8 @@
 //                     their uncached tokens, and th such that the rule reads
 //                     "take a iff L_a <= max(th, L_o)" (clamped to 32 bits;
 //                     the 64-bit walk recomputes it exactly);
-//   sel_level_kernel  one wave per block of requests (1024, or 2048 in
-//                     batches of at least 512 Ki requests): the dependency
+//   sel_level_kernel  one wave per block of requests (64 to 2048 by the
+//                     batch's size): the dependency
 //                     level of every request inside its block (runs of up
 //                     to three same-pair requests sharing a level), and the
 //                     packing of whole levels into windows of two sets of
@@ -348,15 +348,19 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
 // 8 instances) for a walk some 5% longer.  Whole calls, 1024 against 256:
 // 1,024 requests 245 and 142 us, 4,096 chat requests 333 and 267, 32,768 on
 // 512 instances 417 and 374, 65,536 chat requests 1,804 and 1,780; at 131,072
-// the two meet.  Pipelined, the kernel runs beside the previous walk, which is
-// what the batches wait for.
+// the two meet.  Blocks of 64 for at most kTinyTo: 1,024 requests 106 us with
+// blocks of 256, 92 with 128, 83 with 64; 4,096 chat requests 236, 223 and 224;
+// at 16,384 the three meet, and 65,536 on 512 instances take 561, 595 and 598.
+// Pipelined, the kernel runs beside the previous walk, which is what the
+// batches wait for.
 template <uint32_t LB>
 struct LevelShape {
     static constexpr uint32_t block = LB;
-    static constexpr uint32_t wincap = LB == 256 ? 9u : LB == 1024 ? 36u : 66u;  // windows per block
+    // windows per block
+    static constexpr uint32_t wincap = LB == 64 ? 5u : LB == 256 ? 9u : LB == 1024 ? 36u : 66u;
     static_assert(wincap >= 2 * ((LB + 64) / 65) + 1, "room for the windows of a block");
 };
-constexpr uint64_t kLargeFrom = 1u << 19, kSmallTo = 1u << 16;
+constexpr uint64_t kLargeFrom = 1u << 19, kSmallTo = 1u << 16, kTinyTo = 1u << 12;
 // The batch limit follows the large layout; the others only serve
 // batches whose slots stay far inside 32 bits.
 static_assert(LevelShape<2048>::block == kSelBlock &&
@@ -372,6 +376,8 @@ static BlockShape block_shape(uint64_t n, bool hidden)
 {
     if (n >= kLargeFrom)
         return BlockShape{LevelShape<2048>::block, LevelShape<2048>::wincap};
+    if (n <= kTinyTo && !hidden)
+        return BlockShape{LevelShape<64>::block, LevelShape<64>::wincap};
     if (n <= kSmallTo && !hidden)
         return BlockShape{LevelShape<256>::block, LevelShape<256>::wincap};
     return BlockShape{LevelShape<1024>::block, LevelShape<1024>::wincap};
@@ -1362,8 +1368,10 @@ hipError_t select_prepare(dm_ctx* c, hipStream_t st, const int64_t* offsets, uin
                 level(sel_level_kernel<2048, LIVE>);
             else if (b.shape.block == LevelShape<1024>::block)
                 level(sel_level_kernel<1024, LIVE>);
-            else
+            else if (b.shape.block == LevelShape<256>::block)
                 level(sel_level_kernel<256, LIVE>);
+            else
+                level(sel_level_kernel<64, LIVE>);
         };
         if (NL <= kByteLive)
             sized(std::integral_constant<uint32_t, kByteLive>{});

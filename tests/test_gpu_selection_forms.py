@@ -95,6 +95,16 @@ def test_small_level_blocks(n_inst, n_req):
     _pair(wl, workloads.initial_loads(wl, wl.route.max_slots))
 
 
+@pytest.mark.parametrize("policy", ["slo_aware", "min_ttft"])
+@pytest.mark.parametrize("n_inst,n_req", [(1, 63), (2, 64), (3, 65), (8, 127), (64, 1025), (200, 4095), (300, 4096),
+                                          (1, 4097), (2, 4351), (3, 4352), (8, 4353), (64, 4609), (300, 4700)])
+def test_tiny_level_blocks(n_inst, n_req, policy):
+    """Blocks of 64 requests at their edges, and both sides of the line to blocks of 256."""
+    wl = workloads.small_random(171 + n_inst, n_inst, 4, 16, n_req, slo_us=3_000)
+    wl = dataclasses.replace(wl, n_prior=300)
+    _pair(wl, workloads.initial_loads(wl, wl.route.max_slots), policy)
+
+
 @pytest.mark.parametrize("n_req,mean,kl", [(8192, 24_500, False), (20_000, 10_100, True), (33_333, 6100, False)])
 def test_batch_overlapping_itself(n_req, mean, kl):
     """Unpipelined batches of at least 200 M tokens are selected in two parts beside
