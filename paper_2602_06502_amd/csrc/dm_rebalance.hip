@@ -298,28 +298,31 @@ __global__ __launch_bounds__(256) void rank_kernel(const int64_t* __restrict__ L
                                                    uint32_t* __restrict__ src,
                                                    uint32_t* __restrict__ nsrc)
 {
+    // the overloaded instances only (in any order): a few, where going through
+    // all S of them took 15 us at S = 256
     __shared__ int64_t sl[kMaxSlots];
-    __shared__ uint8_t so[kMaxSlots];
-    for (uint32_t k = threadIdx.x; k < S; k += blockDim.x) {
-        sl[k] = L0[k];
-        so[k] = over[k];
-    }
+    __shared__ uint32_t si[kMaxSlots];
+    __shared__ uint32_t m;
+    if (threadIdx.x == 0)
+        m = 0;
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < S; k += blockDim.x)
+        if (over[k]) {
+            const uint32_t at = atomicAdd(&m, 1u);
+            sl[at] = L0[k];
+            si[at] = k;
+        }
     __syncthreads();
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= S || !so[i])
+    if (i >= S || !over[i])
         return;
+    const int64_t mine = L0[i];
     uint32_t r = 0;
-    for (uint32_t k = 0; k < S; k++)
-        r += so[k] && (sl[k] > sl[i] || (sl[k] == sl[i] && k < i));
+    for (uint32_t k = 0; k < m; k++)
+        r += sl[k] > mine || (sl[k] == mine && si[k] < i);
     rank[i] = r;
     src[r] = i;
     atomicAdd(nsrc, 1u);
-}
-
-__global__ void zero_u32_kernel(uint32_t* p, uint32_t n)
-{
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
-        p[k] = 0;
 }
 
 // Three words to pinned host memory.
@@ -331,11 +334,14 @@ __global__ void post_words_kernel(const uint64_t* a, const uint64_t* b, const ui
     host[2] = *c;
 }
 
-__global__ void fill_u32_kernel(uint32_t* p, uint64_t n, uint32_t v)
+// Before a pass: no record has an owner; the pass's counters.
+__global__ void begin_kernel(uint32_t* __restrict__ owner, uint64_t n, uint64_t* __restrict__ ctot)
 {
     for (uint64_t k = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; k < n;
          k += (uint64_t)gridDim.x * blockDim.x)
-        p[k] = v;
+        owner[k] = 0xFFFFFFFFu;
+    if (blockIdx.x == 0 && threadIdx.x < 3)
+        ctot[threadIdx.x] = 0;
 }
 
 // Eligible records in record order (queue order within each source).
@@ -352,17 +358,21 @@ __global__ void compact_kernel(uint64_t Q, const uint64_t* __restrict__ elig,
 // kByRankBenefit: (source rank, benefit descending in its low `sh` bits) of
 // record vals[t]; kByRankTarget: (source rank, target in `sh` bits) of
 // candidate vals[t]; kByBenefitDesc / kBySourceRank: the two halves of the
-// first, for benefits too wide to share a key with the rank.
+// first, for benefits too wide to share a key with the rank.  self: vals are
+// 0, 1, 2, ... and are written there.
 enum KeyKind { kByRankBenefit, kByRankTarget, kByBenefitDesc, kBySourceRank };
 
 __global__ void rekey_kernel(uint64_t C, int kind, uint32_t sh, const uint32_t* __restrict__ vals,
                              const uint32_t* __restrict__ cand_q, const int64_t* __restrict__ benefit,
                              const uint32_t* __restrict__ owner, const uint32_t* __restrict__ rank,
-                             const uint32_t* __restrict__ alt, uint64_t* __restrict__ keys)
+                             const uint32_t* __restrict__ alt, uint64_t* __restrict__ keys,
+                             uint32_t* __restrict__ self = nullptr)
 {
     for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < C;
          t += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t v = vals[t];
+        const uint32_t v = self ? (uint32_t)t : vals[t];
+        if (self)
+            self[t] = v;
         uint64_t k = 0;
         switch (kind) {
             case kByRankBenefit:
@@ -391,77 +401,59 @@ inline int bit_length(uint64_t x)
     return n;
 }
 
-__global__ void iota_kernel(uint64_t C, uint32_t* __restrict__ v)
-{
-    for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < C;
-         t += (uint64_t)gridDim.x * blockDim.x)
-        v[t] = (uint32_t)t;
-}
+// Everything that follows from the two orders, in one pass over the candidates
+// (as kernels of their own: seven launches, some 4 us each):
+struct Ordered {
+    uint64_t C;
+    uint32_t S, rb;               // target bits of a grouped key
+    const uint32_t* cand_q;       // [C] record of candidate t
+    const uint64_t* gkey;         // [C] (source rank, target), ascending
+    const uint32_t* grp;          // [C] candidate of grouped position u
+    const uint32_t *owner, *rank, *nsrc;
+    const uint64_t* rec_id;       // the records
+    const uint32_t *alt, *unc_alt, *unc_here;
+    const int64_t *benefit, *L0;
+    uint32_t *g_alt, *g_unc;      // per grouped position: target, its uncached tokens
+    uint64_t* head;               //   1 where it starts a (source, target) segment
+    uint64_t* c_rec;              // per candidate: the record's fields a commit writes
+    uint32_t *c_alt, *c_ua, *c_uh;
+    int64_t* c_ben;
+    uint32_t* start;              // [nsrc + 1] first candidate of each source rank
+    int64_t* loads;               // [S] the loads before the pass
+    uint32_t* gbits;              // [C / 32 + 1] no acceptance bit
+    unsigned long long* run;      // no migration yet
+};
 
-// start[r] = first candidate of source rank r (r = 0..nsrc).
-__global__ void bounds_kernel(uint64_t C, const uint32_t* __restrict__ cand_q,
-                              const uint32_t* __restrict__ owner, const uint32_t* __restrict__ rank,
-                              const uint32_t* __restrict__ nsrc_p, uint32_t* __restrict__ start)
+__global__ void ordered_kernel(Ordered a)
 {
-    const uint32_t nsrc = *nsrc_p;
-    for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t <= C;
-         t += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t lo = t == 0 ? 0 : rank[owner[cand_q[t - 1]]] + 1;
-        const uint32_t hi = t == C ? nsrc : rank[owner[cand_q[t]]];
+    const uint32_t nsrc = *a.nsrc;
+    const uint64_t end = a.C > a.S ? a.C : a.S;
+    for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u <= end;
+         u += (uint64_t)gridDim.x * blockDim.x) {
+        if (u < a.S)
+            a.loads[u] = a.L0[u];
+        if (u <= a.C / 32)
+            a.gbits[u] = 0;
+        if (u == 0)
+            *a.run = 0;
+        if (u > a.C)
+            continue;
+        const uint32_t q = u < a.C ? a.cand_q[u] : 0u;
+        const uint32_t lo = u == 0 ? 0 : a.rank[a.owner[a.cand_q[u - 1]]] + 1;
+        const uint32_t hi = u == a.C ? nsrc : a.rank[a.owner[q]];
         for (uint32_t r = lo; r <= hi; r++)
-            start[r] = (uint32_t)t;
-    }
-}
-
-// Per grouped position u: target, its uncached tokens, candidate index.
-__global__ void gather_groups_kernel(uint64_t C, const uint32_t* __restrict__ grp,
-                                     const uint32_t* __restrict__ cand_q,
-                                     const uint32_t* __restrict__ alt,
-                                     const uint32_t* __restrict__ unc_alt,
-                                     uint32_t* __restrict__ g_alt, uint32_t* __restrict__ g_unc)
-{
-    for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u < C;
-         u += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t q = cand_q[grp[u]];
-        g_alt[u] = alt[q];
-        g_unc[u] = unc_alt[q];
-    }
-}
-
-// Per candidate t (candidate order): the record's fields a commit writes.
-__global__ void gather_cand_kernel(uint64_t C, const uint32_t* __restrict__ cand_q,
-                                   const uint64_t* __restrict__ rec_id,
-                                   const uint32_t* __restrict__ alt,
-                                   const uint32_t* __restrict__ unc_alt,
-                                   const uint32_t* __restrict__ unc_here,
-                                   const int64_t* __restrict__ benefit, uint64_t* __restrict__ c_rec,
-                                   uint32_t* __restrict__ c_alt, uint32_t* __restrict__ c_ua,
-                                   uint32_t* __restrict__ c_uh, int64_t* __restrict__ c_ben)
-{
-    for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < C;
-         t += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t q = cand_q[t];
-        c_rec[t] = rec_id[q];
-        c_alt[t] = alt[q];
-        c_ua[t] = unc_alt[q];
-        c_uh[t] = unc_here[q];
-        c_ben[t] = benefit[q];
-    }
-}
-
-// head[u] = 1 where grouped position u starts a (source, target) segment.
-__global__ void seg_head_kernel(uint64_t C, const uint32_t* __restrict__ grp,
-                                const uint32_t* __restrict__ cand_q,
-                                const uint32_t* __restrict__ owner,
-                                const uint32_t* __restrict__ rank,
-                                const uint32_t* __restrict__ g_alt, uint64_t* __restrict__ head)
-{
-    for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u < C;
-         u += (uint64_t)gridDim.x * blockDim.x) {
-        bool h = u == 0 || g_alt[u] != g_alt[u - 1];
-        if (!h)
-            h = rank[owner[cand_q[grp[u]]]] != rank[owner[cand_q[grp[u - 1]]]];
-        head[u] = h ? 1 : 0;
+            a.start[r] = (uint32_t)u;
+        if (u == a.C)
+            continue;
+        const uint64_t k = a.gkey[u];
+        a.g_alt[u] = (uint32_t)(k & ((1ull << a.rb) - 1));
+        a.g_unc[u] = a.unc_alt[a.cand_q[a.grp[u]]];
+        a.head[u] = u == 0 || k != a.gkey[u - 1] ? 1 : 0;
+        a.c_rec[u] = a.rec_id[q];
+        a.c_alt[u] = a.alt[q];
+        a.c_ua[u] = a.unc_alt[q];
+        a.c_uh[u] = a.unc_here[q];
+        a.c_ben[u] = a.benefit[q];
     }
 }
 
@@ -484,12 +476,6 @@ __global__ void seg_pos_kernel(uint64_t C, uint32_t S, const uint64_t* __restric
         if (u <= nsrc)
             sseg[u] = start[u] < C ? (uint32_t)sid[start[u]] : nseg;
     }
-}
-
-__global__ void copy_i64_kernel(const int64_t* __restrict__ a, int64_t* __restrict__ b, uint32_t n)
-{
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
-        b[k] = a[k];
 }
 
 struct CommitArgs {
@@ -1224,8 +1210,7 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     uint64_t* pos = carve<uint64_t>(pr, Qa);
     uint32_t* qkey = carve<uint32_t>(pr, Qa);
 
-    zero_u32_kernel<<<1, 64, 0, st>>>(reinterpret_cast<uint32_t*>(ctot), 6);
-    fill_u32_kernel<<<grid_for(Qa, 256), 256, 0, st>>>(owner, Qa, 0xFFFFFFFFu);
+    begin_kernel<<<grid_for(Qa, 256), 256, 0, st>>>(owner, Qa, ctot);
     queue_sum_kernel<<<S * kQSplit, kQThreads, 0, st>>>(q->qoff, Q, q->unc_here, slice_sum,
                                                         c->d_status);
     queue_ttft_kernel<<<S * kQSplit, kQThreads, 0, st>>>(q->qoff, Q, q->unc_here, q->alt,
@@ -1257,10 +1242,10 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     const uint64_t C = hw[0];
     // per-candidate arrays
     const uint64_t Ca = C ? C : 1;
-    uint8_t* pc = static_cast<uint8_t*>(scratch_get(c, kSlotRebalance, Ca * 64 + 16 * 256, &e));
-    // per candidate: keys, ktmp 8 B; vals, vtmp, grp, g_alt, g_unc, seg_pos,
-    // c_ua, c_uh, arank 4 B; tto 8 B; three bit-word arrays 1/8 B -- 60.4 B
-    // and 15 carves of at most 256 B padding each
+    uint8_t* pc = static_cast<uint8_t*>(scratch_get(c, kSlotRebalance, Ca * 88 + 19 * 256, &e));
+    // per candidate: keys, ktmp, head, c_rec, c_ben, tto 8 B; vals, vtmp, grp,
+    // g_alt, g_unc, seg_pos, c_ua, c_uh, arank 4 B; three bit-word arrays 1/8 B
+    // -- 84.4 B and 18 carves of at most 256 B padding each
     if (!pc)
         return e;
     uint64_t* keys = carve<uint64_t>(pc, Ca);
@@ -1278,7 +1263,12 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     uint32_t* c_ua = carve<uint32_t>(pc, Ca);
     uint32_t* c_uh = carve<uint32_t>(pc, Ca);
     uint32_t* arank = carve<uint32_t>(pc, Ca);
+    uint64_t* head = carve<uint64_t>(pc, Ca);
+    uint64_t* c_rec = carve<uint64_t>(pc, Ca);
+    int64_t* c_ben = carve<int64_t>(pc, Ca);
+    uint32_t* c_alt = vtmp;   // free once both orders are final
     uint32_t* cand_q = vals;  // the candidate order lands in vals
+    const int rb = std::max(1, bit_length(S - 1));
 
     if (C) {
         const uint32_t gc = grid_for(C, 256);
@@ -1287,7 +1277,6 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
         // so equal benefits keep queue order; grouped order (source rank,
         // target), stable over candidate order.  Keys take only the bits the
         // ranks, targets and largest benefit need.
-        const int rb = std::max(1, bit_length(S - 1));
         const int nb = bit_length(hw[1]);
         if (rb + nb <= 64) {
             rekey_kernel<<<gc, 256, 0, st>>>(C, kByRankBenefit, (uint32_t)nb, vals, nullptr, benefit,
@@ -1304,35 +1293,50 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
             e = radix_sort_kv(c, keys, vals, ktmp, vtmp, C, rb);
             if (e != hipSuccess) return e;
         }
-        iota_kernel<<<gc, 256, 0, st>>>(C, grp);
-        rekey_kernel<<<gc, 256, 0, st>>>(C, kByRankTarget, (uint32_t)rb, grp, cand_q, benefit,
-                                         owner, rank, q->alt, ktmp);
+        rekey_kernel<<<gc, 256, 0, st>>>(C, kByRankTarget, (uint32_t)rb, nullptr, cand_q, benefit,
+                                         owner, rank, q->alt, ktmp, grp);
         // sort (ktmp, grp) using (keys, vtmp) as work arrays: keys is free once cand_q is final
         e = radix_sort_kv(c, ktmp, grp, keys, vtmp, C, 2 * rb);
         if (e != hipSuccess) return e;
-        gather_groups_kernel<<<gc, 256, 0, st>>>(C, grp, cand_q, q->alt, q->unc_alt, g_alt, g_unc);
     }
-    bounds_kernel<<<grid_for(C + 1, 256), 256, 0, st>>>(C, cand_q, owner, rank, nsrc, start);
-    // (source, target) segments of the grouped order; keys and ktmp are free
-    uint64_t* head = ktmp;
+    // (source, target) segments of the grouped order (keys is free)
     uint64_t* sid = keys;
+    Ordered o{};
+    o.C = C;
+    o.S = S;
+    o.rb = (uint32_t)rb;
+    o.cand_q = cand_q;
+    o.gkey = ktmp;
+    o.grp = grp;
+    o.owner = owner;
+    o.rank = rank;
+    o.nsrc = nsrc;
+    o.rec_id = q->rec_id;
+    o.alt = q->alt;
+    o.unc_alt = q->unc_alt;
+    o.unc_here = q->unc_here;
+    o.benefit = benefit;
+    o.L0 = L0;
+    o.g_alt = g_alt;
+    o.g_unc = g_unc;
+    o.head = head;
+    o.c_rec = c_rec;
+    o.c_alt = c_alt;
+    o.c_ua = c_ua;
+    o.c_uh = c_uh;
+    o.c_ben = c_ben;
+    o.start = start;
+    o.loads = loads_out;
+    o.gbits = gbits;
+    o.run = run;
+    ordered_kernel<<<grid_for(std::max<uint64_t>(C, S) + 1, 256), 256, 0, st>>>(o);
     if (C) {
-        seg_head_kernel<<<grid_for(C, 256), 256, 0, st>>>(C, grp, cand_q, owner, rank, g_alt, head);
         e = exclusive_scan_u64(c, head, C, sid, ctot);
         if (e != hipSuccess)
             return e;
     }
     seg_pos_kernel<<<grid_for(std::max<uint64_t>(C, S) + 1, 256), 256, 0, st>>>(
         C, S, head, sid, ctot, start, nsrc, seg_pos, sseg);
-    // the commit's record fields in candidate order (head and sid are spent)
-    uint64_t* c_rec = ktmp;
-    int64_t* c_ben = reinterpret_cast<int64_t*>(keys);
-    uint32_t* c_alt = vtmp;
-    if (C)
-        gather_cand_kernel<<<grid_for(C, 256), 256, 0, st>>>(C, cand_q, q->rec_id, q->alt,
-                                                            q->unc_alt, q->unc_here, benefit,
-                                                            c_rec, c_alt, c_ua, c_uh, c_ben);
-    copy_i64_kernel<<<grid_for(S, 256), 256, 0, st>>>(L0, loads_out, S);
     CommitArgs a;
     a.qoff = q->qoff;
     a.rec_id = q->rec_id;
@@ -1380,9 +1384,6 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     a.status = c->d_status;
     if (nsrc_h <= kSpreadSources) {
         // few sources: each source's phases as kernels over the whole GPU
-        zero_u32_kernel<<<1, 64, 0, st>>>(reinterpret_cast<uint32_t*>(run), 2);
-        zero_u32_kernel<<<grid_for(Ca / 32 + 1, 256, 1024), 256, 0, st>>>(gbits,
-                                                                       (uint32_t)(Ca / 32 + 1));
         const uint32_t gw = (uint32_t)std::min<uint64_t>((S + 3) / 4, 1024);
         const uint32_t gm = grid_for(C, 256, 512);
         for (uint32_t sr = 0; sr < nsrc_h; sr++) {
