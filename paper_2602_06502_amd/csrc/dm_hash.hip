@@ -11,7 +11,8 @@
 //   - block key mix64(H xor seed).
 // Three passes use this walk (dm_route.hip runs them in this order):
 //   prefix   both chains over the first min(K, full blocks) blocks only:
-//            the two ring keys (ring_key_kernel: several requests per wave);
+//            the two ring keys (ring_key_kernel: several requests per wave)
+//            and, with the tree off, their candidates on the rings;
 //            with the prefix hotness tree on, requests whose depth-K prefix
 //            is extended go on down the tree (extend_kernel) to their key
 //            length K_r, both chains, and take the ring keys of depth K_r;
@@ -28,6 +29,8 @@
 //            the leader's match ends before s the request's match is the
 //            leader's; elsewhere the request's first s blocks are present
 //            and its keys are probed from block s on, chunk by chunk.
+//            (Up to kInlineTo requests one kernel does all of that, probing as
+//            it hashes: member_probe_kernel.)
 // The comparison is of keys and the probes are of keys, so every match is
 // the definition's (leading blocks whose f1 keys are all in the candidate's
 // index) whatever the keys are.  Requests that share a prefix with their
@@ -875,7 +878,8 @@ hipError_t launch_members(dm_ctx* c, const HashArgs& a)
 
 hipError_t launch_member_probe(dm_ctx* c, const HashArgs& a)
 {
-    const uint32_t grid = grid_for(a.r1 - a.r0, kHashThreads / kWave);
+    static_assert(kInlineTo <= (uint64_t)kHashBlocks * (kHashThreads / kWave), "a wave per request");
+    const uint32_t grid = grid_for(a.r1 - a.r0, kHashThreads / kWave, kHashBlocks);
     switch (c->cfg.block_size) {
         case 4: member_probe_kernel<4><<<grid, kHashThreads, 0, c->stream>>>(a); break;
         case 8: member_probe_kernel<8><<<grid, kHashThreads, 0, c->stream>>>(a); break;
