@@ -494,20 +494,25 @@ __global__ void q_copy_offsets_kernel(const int64_t* __restrict__ qoff,
 }
 
 // The checks' word and the record count of a queue set, once the stream has
-// come this far (hipErrorInvalidValue for a malformed count).
-hipError_t q_checked(dm_ctx* c, const uint32_t* bad, const int64_t* qoff, int64_t* Q,
-                     uint32_t* badh)
+// come this far: DM_EINVAL for a malformed count, and DM_EDEVICE for any error
+// of the runtime (which may be hipErrorInvalidValue just as well), after which
+// neither word was written.
+dm_status q_checked(dm_ctx* c, const char* what, const uint32_t* bad, const int64_t* qoff,
+                    int64_t* Q, uint32_t* badh)
 {
     q_post_kernel<<<1, 1, 0, c->stream>>>(bad, qoff, c->cfg.max_slots, c->host_words);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess)
         e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess)
-        return e;
+        return hip_fail(c, e, what);
     const int64_t q0 = (int64_t)c->host_words[1];
     *badh = (uint32_t)c->host_words[0];
     *Q = (int64_t)c->host_words[2];
-    return q0 != 0 || *Q < 0 || *Q >= (1ll << 32) ? hipErrorInvalidValue : hipSuccess;
+    if (q0 != 0 || *Q < 0 || *Q >= (1ll << 32))
+        return fail(c, DM_EINVAL,
+                    std::string(what) + ": qoff[0] must be 0, fewer than 2^32 records");
+    return DM_OK;
 }
 
 }  // namespace
@@ -541,10 +546,8 @@ dm_status queue_append(dm_ctx* c, const dm_queues* q, const int64_t* offsets, ui
         q_hist_kernel<<<grid_for(n, 256, 1024), 256, 4 * S, st>>>(routed->chosen, n, S, cnt, bad);
     int64_t Q = 0;
     uint32_t badh = 0;
-    if ((e = q_checked(c, bad, q->qoff, &Q, &badh)) == hipErrorInvalidValue)
-        return fail(c, DM_EINVAL, "dm_queue_append: qoff[0] must be 0, fewer than 2^32 records");
-    if (e != hipSuccess)
-        return hip_fail(c, e, "dm_queue_append");
+    if (dm_status s = q_checked(c, "dm_queue_append", bad, q->qoff, &Q, &badh); s != DM_OK)
+        return s;
     if ((uint64_t)Q + n > out->cap)
         return fail(c, DM_EFULL, "dm_queue_append: the output holds fewer records than the result");
     if (badh & 4)
@@ -592,10 +595,8 @@ dm_status queue_migrate(dm_ctx* c, const dm_queues* q, const uint64_t* mrec,
     q_check_kernel<<<grid_for(S + 1, 256), 256, 0, st>>>(q->qoff, S, nullptr, nullptr, bad0);
     int64_t Q = 0;
     uint32_t badh = 0;
-    if ((e = q_checked(c, bad0, q->qoff, &Q, &badh)) == hipErrorInvalidValue)
-        return fail(c, DM_EINVAL, "dm_queue_migrate: qoff[0] must be 0, fewer than 2^32 records");
-    if (e != hipSuccess)
-        return hip_fail(c, e, "dm_queue_migrate");
+    if (dm_status s = q_checked(c, "dm_queue_migrate", bad0, q->qoff, &Q, &badh); s != DM_OK)
+        return s;
     if ((uint64_t)Q > out->cap)
         return fail(c, DM_EFULL, "dm_queue_migrate: the output holds fewer records than the result");
     if (m > (uint64_t)Q)
@@ -661,8 +662,8 @@ dm_status queue_migrate(dm_ctx* c, const dm_queues* q, const uint64_t* mrec,
         q_mig_in_kernel<<<grid_for(m, 256, 1024), 256, 0, st>>>(a, order, m, S, bad, msrc, mdst, at,
                                                                in_ex, in_cnt, b);
     }
-    if ((e = q_checked(c, bad, q->qoff, &Q, &badh)) != hipSuccess && e != hipErrorInvalidValue)
-        return hip_fail(c, e, "dm_queue_migrate");
+    if (dm_status s = q_checked(c, "dm_queue_migrate", bad, q->qoff, &Q, &badh); s != DM_OK)
+        return s;
     if (badh)
         return fail(c, DM_EINVAL, "dm_queue_migrate: a migration names an instance >= max_slots, "
                                   "a record not queued on its source, a record twice, or the "
@@ -685,10 +686,8 @@ dm_status queue_drain(dm_ctx* c, const dm_queues* q, const int64_t* units,
     q_check_kernel<<<grid_for(S + 1, 256), 256, 0, st>>>(q->qoff, S, q->base_work, units, bad0);
     int64_t Q = 0;
     uint32_t badh = 0;
-    if ((e = q_checked(c, bad0, q->qoff, &Q, &badh)) == hipErrorInvalidValue)
-        return fail(c, DM_EINVAL, "dm_queue_drain: qoff[0] must be 0, fewer than 2^32 records");
-    if (e != hipSuccess)
-        return hip_fail(c, e, "dm_queue_drain");
+    if (dm_status s = q_checked(c, "dm_queue_drain", bad0, q->qoff, &Q, &badh); s != DM_OK)
+        return s;
     if ((uint64_t)Q > out->cap)
         return fail(c, DM_EFULL, "dm_queue_drain: the output holds fewer records than the result");
     if (badh & 4)
@@ -760,10 +759,8 @@ dm_status queue_reprobe(dm_ctx* c, const dm_queues* q, const int64_t* coff, cons
             a, S, out->cap, n_ids, coff, n_keys, plen, bshift, bad);
     int64_t Q = 0;
     uint32_t badh = 0;
-    if ((e = q_checked(c, bad, q->qoff, &Q, &badh)) == hipErrorInvalidValue)
-        return fail(c, DM_EINVAL, "dm_queue_reprobe: qoff[0] must be 0, fewer than 2^32 records");
-    if (e != hipSuccess)
-        return hip_fail(c, e, "dm_queue_reprobe");
+    if (dm_status s = q_checked(c, "dm_queue_reprobe", bad, q->qoff, &Q, &badh); s != DM_OK)
+        return s;
     if ((uint64_t)Q > out->cap)
         return fail(c, DM_EFULL, "dm_queue_reprobe: the output holds fewer records than the input");
     if (Q && !chains)

@@ -1,0 +1,122 @@
+"""What the entry points allocate, wait for and report on the host, against
+the counted stand-in for the runtime in fake_hip.c (kernels do not run; the
+words they would post to pinned memory are set here).  Every scenario runs in
+a child process, which loads the stand-in in front of the runtime."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.check_call(["gcc", "-O1", "-std=c11", "-Wall", "-Wextra", "-shared", "-fPIC", "-o", so,
+                           os.path.join(ROOT, "tests", "fake_hip.c")])
+    import paper_2602_06502_amd as pk
+    if not os.path.exists(pk.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    return so
+
+
+def _child(fake, scenario):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, scenario], cwd=ROOT, capture_output=True,
+                       text=True, timeout=120)
+    assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+
+
+class Host:
+    """A context on the stand-in, and its queues."""
+
+    def __init__(self, fake, lib=None):
+        self.fk = C.CDLL(fake, mode=C.RTLD_GLOBAL)
+        sys.path.insert(0, ROOT)
+        import paper_2602_06502_amd as pk
+        self.pk, self.L = pk, pk.load_library(lib or pk.LIB_PATH)
+        self.keep = []
+        self.S = 8
+
+    def word(self, name, t=C.c_uint64):
+        return t.in_dll(self.fk, name)
+
+    def create(self, **cfg):
+        h = C.c_void_p()
+        cfg = dict(dict(block=16, key_blocks=4, seeds=(1, 2), vnodes=8, max_slots=self.S, index_log2_slots=10), **cfg)
+        assert self.L.dm_create(C.byref(self.pk.make_config(cfg)), None, C.byref(h)) == self.pk.DM_OK
+        ids = (C.c_uint32 * self.S)(*range(self.S))
+        assert self.L.dm_build_rings(h, ids, self.S) == self.pk.DM_OK
+        return h
+
+    def buf(self, nbytes):
+        b = C.create_string_buffer(max(nbytes, 8))
+        self.keep.append(b)
+        return C.addressof(b)
+
+    def queues(self, n):
+        q = self.pk.dm_queues(self.buf(8 * self.S + 8), *(self.buf(8 * n) for _ in range(4)), self.buf(8 * self.S))
+        o = self.pk.dm_queue_out(self.buf(8 * self.S + 8), *(self.buf(8 * n) for _ in range(4)), self.buf(8 * self.S), n)
+        return q, o
+
+    def on_sync(self, f):
+        """f(words) at every wait: sets the posted words, returns the runtime's result."""
+        t = C.CFUNCTYPE(C.c_int)
+        cb = t(lambda: f((C.c_uint64 * 512).from_address(self.word("fake_host", C.c_void_p).value)))
+        self.keep.append(cb)
+        self.word("fake_on_sync", C.c_void_p).value = C.cast(cb, C.c_void_p).value
+
+
+INVALID_VALUE = 1  # hipErrorInvalidValue
+
+
+def scenario_queue_errors(x):
+    """An error of the runtime is DM_EDEVICE at every wait, hipErrorInvalidValue too; a malformed count is DM_EINVAL."""
+    Q, h = 3, x.create()
+    q, o = x.queues(Q)
+    p, u64s = x.buf(64), x.buf(8 * x.S)
+    calls = {
+        "append": lambda: x.L.dm_queue_append(h, C.byref(q), p, 0, None, 0, C.byref(o)),
+        "migrate": lambda: x.L.dm_queue_migrate(h, C.byref(q), p, p, p, 1, C.byref(o)),
+        "drain": lambda: x.L.dm_queue_drain(h, C.byref(q), u64s, C.byref(o)),
+        "reprobe": lambda: x.L.dm_queue_reprobe(h, C.byref(q), u64s, p, 1, u64s, 4, C.byref(o)),
+    }
+    for name, call in calls.items():
+        turn = [0]
+
+        def posted(words, err=0, at=0, count=Q, first=0):
+            turn[0] += 1
+            words[0], words[1], words[2] = 0, first, count
+            return err if turn[0] == at else 0
+
+        x.on_sync(posted)
+        assert call() == x.pk.DM_OK, name
+        turn[0] = 0
+        assert call() == x.pk.DM_OK, name
+        waits = turn[0]  # with the work areas grown
+        for at in range(1, waits + 1):
+            for err in (INVALID_VALUE, 709):
+                turn[0] = 0
+                x.on_sync(lambda w: posted(w, err, at))
+                assert call() == x.pk.DM_EDEVICE, (name, at, err)
+        for bad in (dict(count=1 << 32), dict(count=2**64 - 1), dict(first=1)):
+            turn[0] = 0
+            x.on_sync(lambda w: posted(w, **bad))
+            assert call() == x.pk.DM_EINVAL, (name, bad)
+        assert b"qoff[0] must be 0" in x.L.dm_last_error(h)
+        turn[0] = 0
+        x.on_sync(posted)
+        x.word("fake_last_error", C.c_int).value = INVALID_VALUE  # a launch that failed
+        assert call() == x.pk.DM_EDEVICE, name
+        x.word("fake_last_error", C.c_int).value = 0
+
+
+def test_queue_calls_report_runtime_errors(fake):
+    _child(fake, "queue_errors")
+
+
+if __name__ == "__main__":
+    globals()["scenario_" + sys.argv[2]](Host(sys.argv[1], *sys.argv[3:]))
