@@ -1053,12 +1053,15 @@ hipError_t hash_members(dm_ctx* c, const int32_t* tokens, const int64_t* offsets
     a.gv = gv;
     a.cand = cand;
     a.match = match;
+    // (a batch whose parts are all short gets the room too: routed in one part,
+    // under capture for instance, it would need it)
+    MemberWork mw{};
+    if (n > kInlineTo)
+        if (const hipError_t we = member_work(c, n, &mw); we != hipSuccess)
+            return we;
     if (m <= kInlineTo)
         return launch_member_probe(c, a);
-    MemberWork mw;
-    hipError_t e = member_work(c, n, &mw);
-    if (e != hipSuccess)
-        return e;
+    hipError_t e = hipSuccess;
     uint32_t bshift = 0;
     while ((1u << bshift) < c->cfg.block_size)
         bshift++;

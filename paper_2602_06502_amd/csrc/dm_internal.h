@@ -261,6 +261,9 @@ hipError_t exclusive_scan_u64(dm_ctx* c, const uint64_t* in, uint64_t n, uint64_
 // requests count no full block.  Being a batch's first kernels it also clears
 // the selection's growth bounds of the parts there are, which later ones add to.
 constexpr int kMaxParts = 2;
+// An unpipelined batch of at least so many tokens and requests is selected in
+// two parts (dm_route.hip).
+constexpr uint64_t kSplitTokens = 200000000, kSplitFrom = 1u << 13;
 struct BatchClear {
     unsigned long long* grow[kMaxParts];
     uint32_t n_live;
@@ -400,7 +403,8 @@ struct SelPart {
 };
 struct SelParts {
     int count = 1;
-    size_t bytes = 0;
+    size_t bytes = 0;    // of this batch's parts
+    size_t reserve = 0;  // what its set of work arrays is given (grows with n alone)
     SelPart part[kMaxParts];
 };
 void select_parts(uint64_t n, bool pipelined, int parts, SelParts* out);

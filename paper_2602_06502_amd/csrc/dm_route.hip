@@ -40,7 +40,6 @@ constexpr int kKeySlot = kSlotKeys;  // block keys when the caller keeps none
 // and in two: 1,048,576 requests (1.75 G tokens) 7.58 and 6.51 ms, 262,144
 // (438 M) 2.03 and 1.80 ms, 131,072 with the hotness tree (219 M) 2.55 and
 // 2.49 ms, 65,536 (109 M) 0.61 and 0.67 ms.
-constexpr uint64_t kSplitTokens = 200000000, kSplitFrom = 1u << 13;
 
 }  // namespace
 

@@ -1233,6 +1233,37 @@ static uint64_t sel_bytes(uint64_t m, BlockShape bs)
 
 uint64_t select_scratch_bytes(uint64_t n) { return sel_bytes(n, block_shape(n, false)); }
 
+// What one set of work arrays is given: the most that any batch of at most n
+// requests takes, in one part or in two, pipelined or not.  A form changes with
+// the size, the tokens and the streams, and smaller blocks need more room per
+// request (4,096 requests take 3.6 MB, 4,097 take 1.9): sized by the form of the
+// call, a context warmed by one batch would wait, free and allocate again for a
+// smaller one, which a graph under capture cannot do and a captured one does
+// not survive.
+static uint64_t sel_reserve(uint64_t n)
+{
+    const BlockShape tiny{LevelShape<64>::block, LevelShape<64>::wincap},
+        small{LevelShape<256>::block, LevelShape<256>::wincap},
+        mid{LevelShape<1024>::block, LevelShape<1024>::wincap},
+        large{LevelShape<2048>::block, LevelShape<2048>::wincap};
+    auto early = [&](uint64_t m) -> uint64_t {  // parts whose walk waits for their blocks
+        return std::max(sel_bytes(std::min(m, kTinyTo), tiny),
+                        sel_bytes(std::min(m, kSmallTo), small));
+    };
+    const uint64_t below = std::min(n, kLargeFrom - 1);  // the most before the large blocks
+    uint64_t one = std::max(early(n), sel_bytes(below, mid));
+    if (n >= kLargeFrom)
+        one = std::max(one, sel_bytes(n, large));
+    if (n < kSplitFrom)
+        return up256(one);
+    const uint64_t first = n / 4, rest = n - first + kSelBlock;
+    uint64_t second = sel_bytes(std::min(rest, below), mid);
+    if (n >= kLargeFrom)
+        second = std::max(second, sel_bytes(rest, large));
+    const uint64_t two = up256(std::max(early(first), sel_bytes(first, mid))) + up256(second);
+    return std::max(up256(one), two);
+}
+
 // Parts of a batch: the level blocks of a first part of two are those of an
 // unpipelined batch (its walk waits for them), but for the shortest; the
 // second part's level kernel runs beside the first one's walk.
@@ -1240,6 +1271,7 @@ void select_parts(uint64_t n, bool pipelined, int parts, SelParts* out)
 {
     out->count = parts;
     out->bytes = 0;
+    out->reserve = sel_reserve(n);
     uint64_t r0 = 0;
     for (int k = 0; k < parts; k++) {
         const uint64_t end = k + 1 == parts ? n : n / 4 & ~(kSelBlock - 1);
@@ -1274,10 +1306,10 @@ static hipError_t sel_buffers(dm_ctx* c, const SelParts& ps, const SelPart& q, i
         // smaller batch must not move its set into the other parity's, which
         // the batch before it may still be walking.  A larger batch widens
         // the stride only once every stream is idle.
-        if (ps.bytes > c->sel_stride) {
+        if (ps.reserve > c->sel_stride) {
             if ((e = sync_streams(c)) != hipSuccess)
                 return e;
-            c->sel_stride = ps.bytes;
+            c->sel_stride = ps.reserve;
         }
         sw = static_cast<uint8_t*>(scratch_get(c, kSelSlot, 2 * c->sel_stride, &e));
         if (sw)

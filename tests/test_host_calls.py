@@ -114,6 +114,48 @@ def scenario_queue_errors(x):
         x.word("fake_last_error", C.c_int).value = 0
 
 
+def scenario_route_areas(x):
+    """A context that has routed n requests routes fewer without a wait or an allocation: under capture too, and
+    whatever the form of either batch (pipelined, in two parts, blocks of any size)."""
+    tok, big = x.buf(64), 4_000_000_000
+    out = x.pk.dm_route_out(*(x.buf(64) for _ in range(8)))
+    x.keep.append(out)
+    plain, split = 1_000_000, big  # tokens
+    sizes = [1, 63, 64, 1000, 2047, 2048, 3000, 4095, 4096, 4097, 5000, 8192, 8704, 12_000, 16_384, 32_768, 60_000,
+             65_536, 65_537, 70_000, 80_000, 87_382, 100_000, 131_072, 262_144, 400_000, 524_287, 524_288, 600_000,
+             1_048_576, 2_100_000]
+    count = lambda: (x.word("fake_mallocs").value, x.word("fake_frees").value, x.word("fake_syncs").value)
+    capturing = x.word("fake_capturing", C.c_int)
+
+    def route(h, n, tokens):
+        return x.L.dm_route_batch(h, tok, tokens, tok, n, tok, C.byref(out))
+
+    for k in range(1, len(sizes)):
+        for tokens, pipe in ((plain, 0), (plain, 1), (split, 0)):
+            h = x.create()
+            assert x.L.dm_set_pipelining(h, pipe) == x.pk.DM_OK
+            for _ in range(2):
+                assert route(h, sizes[k], tokens) == x.pk.DM_OK
+            assert x.L.dm_set_pipelining(h, 0) == x.pk.DM_OK
+            capturing.value = 1
+            for n in sizes[:k + 1]:
+                assert route(h, n, tokens) == x.pk.DM_OK, ("capture", sizes[k], n, tokens, pipe)
+            capturing.value = 0
+            route(h, 1, split)  # the streams of a batch in two parts, and of pipelining
+            for p in (0, 1):
+                assert x.L.dm_set_pipelining(h, p) == x.pk.DM_OK
+                before = count()
+                for n in sizes[:k + 1]:
+                    for tk in {tokens, plain}:
+                        assert route(h, n, tk) == x.pk.DM_OK
+                assert count() == before, ("eager", sizes[k], tokens, pipe, p)
+            x.L.dm_destroy(h)
+
+
+def test_work_areas_grow_with_the_batch_alone(fake):
+    _child(fake, "route_areas")
+
+
 def test_queue_calls_report_runtime_errors(fake):
     _child(fake, "queue_errors")
 
