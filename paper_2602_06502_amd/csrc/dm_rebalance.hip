@@ -1242,10 +1242,10 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     const uint64_t C = hw[0];
     // per-candidate arrays
     const uint64_t Ca = C ? C : 1;
-    uint8_t* pc = static_cast<uint8_t*>(scratch_get(c, kSlotRebalance, Ca * 88 + 19 * 256, &e));
-    // per candidate: keys, ktmp, head, c_rec, c_ben, tto 8 B; vals, vtmp, grp,
-    // g_alt, g_unc, seg_pos, c_ua, c_uh, arank 4 B; three bit-word arrays 1/8 B
-    // -- 84.4 B and 18 carves of at most 256 B padding each
+    uint8_t* pc = static_cast<uint8_t*>(scratch_get(c, kSlotRebalance, Ca * 64 + 16 * 256, &e));
+    // per candidate: keys, ktmp 8 B; vals, vtmp, grp, g_alt, g_unc, seg_pos,
+    // c_ua, c_uh, arank 4 B; tto 8 B; three bit-word arrays 1/8 B -- 60.4 B
+    // and 15 carves of at most 256 B padding each
     if (!pc)
         return e;
     uint64_t* keys = carve<uint64_t>(pc, Ca);
@@ -1263,10 +1263,12 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
     uint32_t* c_ua = carve<uint32_t>(pc, Ca);
     uint32_t* c_uh = carve<uint32_t>(pc, Ca);
     uint32_t* arank = carve<uint32_t>(pc, Ca);
-    uint64_t* head = carve<uint64_t>(pc, Ca);
-    uint64_t* c_rec = carve<uint64_t>(pc, Ca);
-    int64_t* c_ben = carve<int64_t>(pc, Ca);
-    uint32_t* c_alt = vtmp;   // free once both orders are final
+    // a candidate is a record: two of the records' arrays are free once the
+    // candidates are listed, and two of the sorts' once both orders are final
+    uint64_t* head = elig;
+    uint64_t* c_rec = pos;
+    int64_t* c_ben = reinterpret_cast<int64_t*>(keys);
+    uint32_t* c_alt = vtmp;
     uint32_t* cand_q = vals;  // the candidate order lands in vals
     const int rb = std::max(1, bit_length(S - 1));
 
@@ -1299,8 +1301,9 @@ hipError_t rebalance(dm_ctx* c, const dm_queues* q, int64_t* loads_out, const dm
         e = radix_sort_kv(c, ktmp, grp, keys, vtmp, C, 2 * rb);
         if (e != hipSuccess) return e;
     }
-    // (source, target) segments of the grouped order (keys is free)
-    uint64_t* sid = keys;
+    // (source, target) segments of the grouped order, numbered where its keys
+    // were (ordered_kernel has read them)
+    uint64_t* sid = ktmp;
     Ordered o{};
     o.C = C;
     o.S = S;

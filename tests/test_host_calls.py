@@ -156,6 +156,40 @@ def test_work_areas_grow_with_the_batch_alone(fake):
     _child(fake, "route_areas")
 
 
+def scenario_rebalance_area(x):
+    """A rebalancing pass takes 64 bytes a candidate on top of what its records take."""
+    Q = 100_000
+    q, _ = x.queues(8)
+    p = x.buf(64)
+    mig = x.pk.dm_migrations(*(x.buf(64) for _ in range(6)))
+    frees, held = x.word("fake_frees"), x.word("fake_bytes")
+
+    def used(candidates):
+        h, turn = x.create(), [0]
+
+        def words(w):
+            turn[0] += 1
+            w[0], w[1], w[2] = (0, Q, 0) if turn[0] == 1 else (candidates, 1000, 2)
+            return 0
+
+        before, had = frees.value, held.value
+        x.on_sync(words)
+        assert x.L.dm_rebalance(h, C.byref(q), p, C.byref(mig), 8) == x.pk.DM_OK
+        x.word("fake_on_sync", C.c_void_p).value = None
+        assert frees.value == before
+        size = held.value - had
+        x.L.dm_destroy(h)
+        return size
+
+    few = used(1)
+    assert used(4096) - few <= 4096 * 64 + 8192
+    assert used(Q) - few <= Q * (64 + 8) + 8192  # and the digit counts of its sorts
+
+
+def test_rebalancing_takes_64_bytes_a_candidate(fake):
+    _child(fake, "rebalance_area")
+
+
 def test_queue_calls_report_runtime_errors(fake):
     _child(fake, "queue_errors")
 
