@@ -253,7 +253,8 @@ dm_status dm_create(const dm_config* cfg, void* hip_stream, dm_ctx** out)
     if (e == hipSuccess) e = hipMalloc(&c->d_flag_rm, S);
     if (e == hipSuccess) e = hipMalloc(&c->d_tables, table_slots * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMalloc(&c->d_counts, 2 * S * sizeof(uint64_t));
-    if (e == hipSuccess) e = hipMalloc(&c->d_status, sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMalloc(&c->d_status, 256);
+    if (e == hipSuccess) c->d_check = c->d_status + 32;  // on a line of its own
     if (e == hipSuccess)
         e = hipHostMalloc(reinterpret_cast<void**>(&c->host_words), 4096, hipHostMallocDefault);
     if (e == hipSuccess)

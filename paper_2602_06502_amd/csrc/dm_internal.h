@@ -147,6 +147,7 @@ struct dm_ctx {
     uint64_t* d_tables = nullptr;  // [max_slots << log2slots]
     uint64_t* d_counts = nullptr;  // [2 * max_slots] live keys, then occupied slots
     uint32_t* d_status = nullptr;  // device status word
+    uint32_t* d_check = nullptr;   // a call's checks (8 bytes; d_status's allocation)
     // pinned host words that a call's kernels write and the call reads once it
     // has waited for the stream
     uint64_t* host_words = nullptr;

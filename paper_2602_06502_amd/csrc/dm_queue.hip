@@ -588,9 +588,8 @@ dm_status queue_migrate(dm_ctx* c, const dm_queues* q, const uint64_t* mrec,
     if (e != hipSuccess)
         return hip_fail(c, e, "dm_queue_migrate");
     hipStream_t st = c->stream;
-    uint32_t* bad0 = static_cast<uint32_t*>(scratch_get(c, kSlotMembers, 256, &e));
-    if (!bad0)
-        return hip_fail(c, e, "dm_queue_migrate");
+    // the first check's word is not in the work area, whose size it decides
+    uint32_t* bad0 = c->d_check;
     q_zero_kernel<<<1, 64, 0, st>>>(reinterpret_cast<unsigned long long*>(bad0), 1);
     q_check_kernel<<<grid_for(S + 1, 256), 256, 0, st>>>(q->qoff, S, nullptr, nullptr, bad0);
     int64_t Q = 0;
@@ -679,9 +678,7 @@ dm_status queue_drain(dm_ctx* c, const dm_queues* q, const int64_t* units,
     if (e != hipSuccess)
         return hip_fail(c, e, "dm_queue_drain");
     hipStream_t st = c->stream;
-    uint32_t* bad0 = static_cast<uint32_t*>(scratch_get(c, kSlotMembers, 256, &e));
-    if (!bad0)
-        return hip_fail(c, e, "dm_queue_drain");
+    uint32_t* bad0 = c->d_check;
     q_zero_kernel<<<1, 64, 0, st>>>(reinterpret_cast<unsigned long long*>(bad0), 1);
     q_check_kernel<<<grid_for(S + 1, 256), 256, 0, st>>>(q->qoff, S, q->base_work, units, bad0);
     int64_t Q = 0;
@@ -743,9 +740,7 @@ dm_status queue_reprobe(dm_ctx* c, const dm_queues* q, const int64_t* coff, cons
     if (e != hipSuccess)
         return hip_fail(c, e, "dm_queue_reprobe");
     hipStream_t st = c->stream;
-    uint32_t* bad = static_cast<uint32_t*>(scratch_get(c, kSlotMembers, 256, &e));
-    if (!bad)
-        return hip_fail(c, e, "dm_queue_reprobe");
+    uint32_t* bad = c->d_check;
     uint32_t bshift = 0;
     while ((1u << bshift) < c->cfg.block_size)
         bshift++;

@@ -190,6 +190,39 @@ def test_rebalancing_takes_64_bytes_a_candidate(fake):
     _child(fake, "rebalance_area")
 
 
+def scenario_first_calls(x):
+    """On a new context no queue operation frees what it has itself allocated (an area that it outgrows is waited for,
+    freed and allocated again)."""
+    Q = 100_000
+    q, o = x.queues(8)
+    o.cap = Q
+    p = x.buf(64)
+
+    def posted(w):
+        w[0], w[1], w[2] = 0, 0, Q  # the queues' checks and ends
+        return 0
+
+    calls = {
+        "append": lambda h: x.L.dm_queue_append(h, C.byref(q), p, 0, None, 0, C.byref(o)),
+        "migrate": lambda h: x.L.dm_queue_migrate(h, C.byref(q), p, p, p, 1000, C.byref(o)),
+        "drain": lambda h: x.L.dm_queue_drain(h, C.byref(q), p, C.byref(o)),
+        "reprobe": lambda h: x.L.dm_queue_reprobe(h, C.byref(q), p, p, 1, p, 4, C.byref(o)),
+    }
+    frees = x.word("fake_frees")
+    for name, call in calls.items():
+        h = x.create()
+        x.on_sync(posted)
+        before = frees.value
+        assert call(h) == x.pk.DM_OK, name
+        assert frees.value == before, name
+        x.word("fake_on_sync", C.c_void_p).value = None
+        x.L.dm_destroy(h)
+
+
+def test_first_queue_call_on_a_new_context(fake):
+    _child(fake, "first_calls")
+
+
 def test_queue_calls_report_runtime_errors(fake):
     _child(fake, "queue_errors")
 
