@@ -264,7 +264,7 @@ hipError_t exclusive_scan_u64(dm_ctx* c, const uint64_t* in, uint64_t n, uint64_
 constexpr int kMaxParts = 2;
 // An unpipelined batch of at least so many tokens and requests is selected in
 // two parts (dm_route.hip).
-constexpr uint64_t kSplitTokens = 200000000, kSplitFrom = 1u << 13;
+constexpr uint64_t kSplitTokens = 200000000, kSplitFrom = (1u << 16) + 1;
 struct BatchClear {
     unsigned long long* grow[kMaxParts];
     uint32_t n_live;

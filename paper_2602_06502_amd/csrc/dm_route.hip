@@ -28,19 +28,27 @@ namespace {
 
 constexpr int kKeySlot = kSlotKeys;  // block keys when the caller keeps none
 
-// An unpipelined batch of at least kSplitTokens tokens (and kSplitFrom
-// requests) is selected in two parts: the walk of the first, one wave on one
+// An unpipelined batch of at least kSplitTokens tokens and kSplitFrom requests
+// is selected in two parts: the walk of the first, one wave on one
 // SIMD, runs on a side stream beside the hashing of the second.  The walk
 // claims a whole SIMD's registers, so it starts only on an empty one: its
 // records are ready before the second part's member records are written, and
 // in the gap between that kernel and the hashing it finds one.  A first part
 // of a quarter walks about as long as the rest hashes (a fifth and three
-// tenths measured 2 and 1% longer).  The two streams' events cost some 130 us,
-// the time in which three quarters of 200 M tokens are hashed.  In one part
-// and in two: 1,048,576 requests (1.75 G tokens) 7.58 and 6.51 ms, 262,144
-// (438 M) 2.03 and 1.80 ms, 131,072 with the hotness tree (219 M) 2.55 and
-// 2.49 ms, 65,536 (109 M) 0.61 and 0.67 ms.
-
+// tenths measured 2 and 1% longer).  The second set of packing kernels and the
+// two streams' events cost 40 to 70 us, so both lines are needed: a walk whose
+// quarter is worth that, and hashing to run it beside.  In one part and in two
+// (us):
+//   200 M tokens            128 instances   8              1,000
+//   8,192 requests          369    430      586    641     402    471
+//   32,768                  512    554      1,332  1,338   533    606
+//   65,536                  717    718
+//   66,000                  788    730      2,462  2,351   806    742
+//   100,000 (305 M)         1,069  982      3,571  3,325   1,073  1,005
+//   262,144                 3,495  3,326    7,565  7,381   1,930  1,769
+// and with more tokens 262,144 (438 M) 2,030 and 1,800, 1,048,576 (1.75 G) 7,580
+// and 6,510, 131,072 with the hotness tree (219 M) 2,550 and 2,490; with fewer,
+// 65,536 (109 M) 610 and 670.
 }  // namespace
 
 namespace {

@@ -105,15 +105,21 @@ def test_tiny_level_blocks(n_inst, n_req, policy):
     _pair(wl, workloads.initial_loads(wl, wl.route.max_slots), policy)
 
 
-@pytest.mark.parametrize("n_req,mean,kl", [(8192, 24_500, False), (20_000, 10_100, True), (33_333, 6100, False)])
-def test_batch_overlapping_itself(n_req, mean, kl):
-    """Unpipelined batches of at least 200 M tokens are selected in two parts beside
-    the hashing: outputs, loads, block keys and the hotness tree's windows
-    against the oracle, twice in a row on the same buffers."""
+@pytest.mark.parametrize("n_req,mean,kl,n_inst,policy", [
+    (8192, 24_500, False, 40, "slo_aware"), (20_000, 10_100, True, 40, "slo_aware"), (33_333, 6100, False, 40, "slo_aware"),
+    (65_537, 3100, False, 40, "slo_aware"), (70_001, 2900, True, 300, "slo_aware"), (90_000, 2250, False, 40, "min_ttft"),
+    (131_072, 1550, False, 1000, "cache_affinity")])
+def test_batch_overlapping_itself(n_req, mean, kl, n_inst, policy):
+    """Unpipelined batches of at least 200 M tokens, those of more than 65,536
+    requests selected in two parts beside the hashing: outputs, loads, block keys
+    and the hotness tree's windows against the oracle, twice in a row on the same
+    buffers, then pipelined."""
     import paper_2602_06502_amd.harness as gh
     B = 16
-    wl = workloads.small_random(7, 40, 8, B, 64, slo_us=30_000)
+    wl = workloads.small_random(7, n_inst, 8, B, 64, slo_us=30_000)
     eng, o = gh.engine_for(wl), oh.oracle_for(wl)
+    eng.set_policy(policy)
+    assert o.set_policy(policy) == oracle.OK
     rng = np.random.default_rng(n_req)
     tpl = [rng.integers(0, 1 << 20, size=B * 90, dtype=np.int32) for _ in range(12)]
     lens = rng.integers(mean // 2, mean * 3 // 2 + 200, size=n_req)
@@ -131,10 +137,13 @@ def test_batch_overlapping_itself(n_req, mean, kl):
     L = workloads.initial_loads(wl, wl.route.max_slots)
     Ld = gh.to_dev(L, eng.device)
     td, od = gh.to_dev(tok, eng.device), gh.to_dev(off, eng.device)
-    for step in range(2):
-        print("[case] overlap", n_req, len(tok), step, flush=True)
+    for step in range(3):
+        print("[case] overlap", n_req, len(tok), n_inst, policy, step, flush=True)
+        eng.set_pipelining(step == 2)
         g = eng.route(td, od, Ld, block_keys=True)
-        g2 = {k: v.clone() for k, v in g.items()}  # on the caller's stream, no wait
+        if step == 2:
+            eng.sync()
+        g2 = {k: v.clone() for k, v in g.items()}  # unpipelined: on the caller's stream, no wait
         r = o.route(tok, off, L, block_keys=True)
         for k in ("key", "cand", "match", "chosen", "ttft", "flags", "key_len", "block_keys"):
             assert np.array_equal(g2[k].cpu().numpy()[:len(r[k])], r[k]), k

@@ -223,6 +223,25 @@ def test_first_queue_call_on_a_new_context(fake):
     _child(fake, "first_calls")
 
 
+def scenario_two_parts(x):
+    """A batch goes in two parts (a second set of launches) from 65,537 requests and 200 M tokens on."""
+    tok = x.buf(64)
+    out = x.pk.dm_route_out(*(x.buf(64) for _ in range(8)))
+    h, runs = x.create(), x.word("fake_launches")
+
+    def launches(n, tokens):
+        a = runs.value
+        assert x.L.dm_route_batch(h, tok, tokens, tok, n, tok, C.byref(out)) == x.pk.DM_OK
+        return runs.value - a
+
+    for n in (8192, 16_384, 32_768, 65_536, 65_537, 100_000):
+        assert (launches(n, 200_000_000) > launches(n, 199_999_999)) == (n > 65_536), n
+
+
+def test_batches_worth_two_parts(fake):
+    _child(fake, "two_parts")
+
+
 def test_queue_calls_report_runtime_errors(fake):
     _child(fake, "queue_errors")
 
