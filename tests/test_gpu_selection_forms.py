@@ -105,6 +105,48 @@ def test_tiny_level_blocks(n_inst, n_req, policy):
     _pair(wl, workloads.initial_loads(wl, wl.route.max_slots), policy)
 
 
+@pytest.mark.parametrize("n_inst,n_req,policy", [(300, 65_537, "slo_aware"), (4093, 66_000, "min_ttft"),
+                                                 (300, 524_287, "slo_aware"), (300, 524_288, "slo_aware"),
+                                                 (1000, 526_500, "min_ttft")])
+def test_large_level_blocks_on_many_instances(n_inst, n_req, policy):
+    """Blocks of 1024 and of 2048 requests with two bytes an instance."""
+    wl = workloads.small_random(311 + n_inst, n_inst, 2, 16, n_req, slo_us=3_000)
+    wl = dataclasses.replace(wl, n_prior=3000)
+    _pair(wl, workloads.initial_loads(wl, wl.route.max_slots), policy)
+
+
+@pytest.mark.parametrize("n_inst,n_req,policy", [(257, 63, "slo_aware"), (300, 5000, "min_ttft"), (4093, 4097, "slo_aware"),
+                                                 (300, 70_000, "slo_aware"), (700, 525_000, "slo_aware")])
+def test_pipelined_on_many_instances(n_inst, n_req, policy):
+    """Consecutive pipelined batches (blocks of 1024 at every size below the
+    largest) on more than 256 instances, the loads carried on."""
+    import paper_2602_06502_amd.harness as gh
+    wl = workloads.small_random(331 + n_inst, n_inst, 2, 16, n_req, slo_us=3_000)
+    wl = dataclasses.replace(wl, n_prior=3000)
+    eng, o = gh.engine_for(wl), oh.oracle_for(wl)
+    gh.prefill_from_prior(eng, wl)
+    oh.prefill_from_prior(o, wl)
+    eng.set_policy(policy)
+    assert o.set_policy(policy) == oracle.OK
+    L = workloads.initial_loads(wl, wl.route.max_slots)
+    Ld = gh.to_dev(L, eng.device)
+    data = [workloads.prompts(wl, n_req, sub=k) for k in (0, 2, 3)]
+    dev = [(gh.to_dev(tok, eng.device), gh.to_dev(off, eng.device)) for tok, off in data]
+    outs = [eng.alloc_route_out(n_req) for _ in data]
+    print("[case] pipelined", n_inst, n_req, policy, flush=True)
+    eng.set_pipelining(True)
+    for (tok, off), out in zip(dev, outs):
+        eng.route_into(tok, off, Ld, out)
+    eng.sync()
+    eng.set_pipelining(False)
+    for (tok, off), out in zip(data, outs):
+        r = o.route(tok, off, L)
+        L = r["loads"]
+        for k in ("key", "cand", "match", "chosen", "ttft", "flags"):
+            assert np.array_equal(out[k].cpu().numpy()[:len(r[k])], r[k]), k
+    assert np.array_equal(Ld.cpu().numpy(), L)
+
+
 @pytest.mark.parametrize("n_req,mean,kl,n_inst,policy", [
     (8192, 24_500, False, 40, "slo_aware"), (20_000, 10_100, True, 40, "slo_aware"), (33_333, 6100, False, 40, "slo_aware"),
     (65_537, 3100, False, 40, "slo_aware"), (70_001, 2900, True, 300, "slo_aware"), (90_000, 2250, False, 40, "min_ttft"),
