@@ -76,3 +76,76 @@ def test_kv_save_matches_lru_dicts(slots, log2, steps):
         if i == 1:
             eng.index_clear(1)
             model.pop(1, None)
+
+
+def test_many_equal_times_at_the_cut():
+    """More entries of one time than a workgroup has threads: lower caps drop
+    the smallest keys first."""
+    import paper_2602_06502_amd as pk
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B, saves = 16, 1300
+    cfg = dict(workloads.small_random(5, 2, 2, B, 10).route.as_dict(), max_slots=3, index_log2_slots=13)
+    eng = pk.DualMap(cfg, device="cuda:0")
+    eng.build_rings(range(2))
+    rng = np.random.default_rng(3)
+    keys = rng.integers(2, 2**63, size=(saves, 2), dtype=np.uint64)
+    keys[5, 0], keys[6, 0], keys[7, 1] = 0, 2**64 - 1, 0
+    keys[100:160, 0] = keys[100, 0] + np.arange(60, dtype=np.uint64)  # alike but for the last digit
+    off, inst = np.array([0, B, 2 * B], np.int64), np.array([0, 1], np.uint32)
+    od, idd, kd = _dev(off), _dev(inst), _dev(keys.reshape(-1))
+    model = {}
+    print("[case] equal times", flush=True)
+    for i in range(saves):
+        eng.kv_save(od, kd[2 * i:2 * i + 2].contiguous(), idd, 7, 0)
+        _save(model, off, keys[i], inst, 7, 0, B)
+    seen = np.unique(keys)
+    for cap in (1200, 1199, 500, 129, 2, 1):
+        print("[case] cap", cap, flush=True)
+        got = eng.kv_save(od[:1].contiguous(), kd[:1].contiguous(), idd[:1].contiguous(), 7, cap)
+        eng.sync()
+        assert got == _save(model, off[:1], keys[0][:0], inst[:0], 7, cap, B), cap
+        for c in (0, 1):
+            assert set(seen[_held(eng, c, seen)].tolist()) == set(model[c]), (cap, c)
+
+
+def _median_us(f, reps=7):
+    import time
+    t = []
+    for i in range(reps + 2):
+        torch.cuda.synchronize()
+        a = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        t.append((time.perf_counter() - a) * 1e6)
+    return sorted(t[2:])[reps // 2]
+
+
+def test_equal_times_cost_little():
+    """65,536 blocks an instance over a cap of as many and one: the clock not
+    advanced (the cut falls between two entries of one time) against advanced.
+    One read of the entries more, not one for each bit of a key (8.8 times)."""
+    import paper_2602_06502_amd as pk
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    S, per, B = 4, 65_536, 16
+    cfg = dict(workloads.small_random(5, S, 2, B, 10).route.as_dict(), index_log2_slots=20)
+    n = S * 256
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda:0") * (B * (per // 256))
+    inst = (torch.arange(n, device="cuda:0") % S).to(torch.int32).view(torch.uint32)
+    us = {}
+    for ahead in (0, 1):
+        eng = pk.DualMap(cfg, device="cuda:0")
+        eng.build_rings(range(S))
+        g, clock = torch.Generator(device="cuda:0").manual_seed(5), [0]
+        batch = [torch.randint(-2**63, 2**63 - 1, (S * per,), dtype=torch.int64, device="cuda:0", generator=g).view(torch.uint64)
+                 for _ in range(3)]
+
+        def save():
+            batch.insert(0, batch.pop())  # other keys every time
+            eng.kv_save(off, batch[0], inst, clock[0], per + 1)
+            clock[0] += ahead * S * per
+        print("[case] ahead", ahead, flush=True)
+        us[ahead] = _median_us(save)
+    print(us)
+    assert us[0] < 3 * us[1], us
