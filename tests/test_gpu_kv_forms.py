@@ -149,3 +149,40 @@ def test_equal_times_cost_little():
         us[ahead] = _median_us(save)
     print(us)
     assert us[0] < 3 * us[1], us
+
+
+def _saves(S, per, blocks, old, reps=7):
+    """Median time of saving `per` fresh blocks on each of S instances over a
+    cap of as many, in requests of `blocks`, with or without an old entry on
+    one more instance."""
+    import paper_2602_06502_amd as pk
+    B = 16
+    cfg = dict(workloads.small_random(5, S + 1, 2, B, 10).route.as_dict(), index_log2_slots=20)
+    eng = pk.DualMap(cfg, device="cuda:0")
+    eng.build_rings(range(S + 1))
+    n = S * (per // blocks)
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda:0") * (B * blocks)
+    inst = (torch.arange(n, device="cuda:0") % S).to(torch.int32).view(torch.uint32)
+    g, clock = torch.Generator(device="cuda:0").manual_seed(5), [0]
+    batch = [torch.randint(-2**63, 2**63 - 1, (n * blocks,), dtype=torch.int64, device="cuda:0", generator=g)
+             .view(torch.uint64) for _ in range(3)]
+    if old:
+        eng.kv_save(off[:2] // blocks, batch[0][:1].contiguous(), (inst[:1].to(torch.int32) + S).view(torch.uint32), 0, per)
+        clock[0] = 1 << 38
+
+    def save():
+        batch.insert(0, batch.pop())
+        eng.kv_save(off, batch[0], inst, clock[0], per)
+        clock[0] += n * blocks
+    print("[case] saves", S, per, blocks, old, flush=True)
+    us = _median_us(save, reps)
+    print(us)
+    return us
+
+
+def test_long_requests_cost_little():
+    """As many blocks in 16 requests as in 2,048 (5 times the time with a wave
+    for each request)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    assert _saves(2, 1 << 18, 1 << 15, False) < 2.5 * _saves(2, 1 << 18, 256, False)
