@@ -186,3 +186,42 @@ def test_long_requests_cost_little():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     assert _saves(2, 1 << 18, 1 << 15, False) < 2.5 * _saves(2, 1 << 18, 256, False)
+
+
+@pytest.mark.parametrize("log2", [10, 13])
+def test_times_far_apart(log2):
+    """Every digit of the select with many entries and with few: an idle
+    instance's old entry, then batches long after it, then spread ones."""
+    import paper_2602_06502_amd as pk
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    S, B = 3, 16
+    cfg = dict(workloads.small_random(5, S, 2, B, 10).route.as_dict(), max_slots=S, index_log2_slots=log2)
+    eng = pk.DualMap(cfg, device="cuda:0")
+    eng.build_rings(range(S))
+    rng = np.random.default_rng(log2)
+    cap, model, seen = 1 << (log2 - 2), {}, np.zeros(0, np.uint64)
+    clock = 0
+    for i, (n, ahead) in enumerate([(1, 1 << 38), (700, 0), (700, 1 << 12), (700, 1 << 20), (700, 1 << 24), (3, 1),
+                                    (700, 1 << 30), (40, 1 << 33), (700, 1)]):
+        f = rng.integers(1, 2 if n == 1 else 12, size=n)
+        off = np.zeros(n + 1, np.int64)
+        off[1:] = np.cumsum(f) * B
+        keys = rng.integers(2, 2**63, size=int(f.sum()), dtype=np.uint64)
+        inst = np.full(n, 2, np.uint32) if n == 1 else rng.integers(0, 2, size=n).astype(np.uint32)
+        print("[case] far", log2, i, n, clock, flush=True)
+        got = eng.kv_save(_dev(off), _dev(keys), _dev(inst), clock, cap)
+        eng.sync()
+        assert got == _save(model, off, keys, inst, clock, cap, B), i
+        seen = np.concatenate([seen, keys])
+        for c in range(S):
+            assert set(seen[_held(eng, c, seen)].tolist()) == set(model.get(c, {})), (i, c)
+        clock += len(keys) + ahead
+
+
+def test_an_old_entry_costs_little():
+    """An idle instance's old entry makes all other times share their leading
+    digits (12 times the time with the counts straight to memory)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    assert _saves(1, 1 << 19, 256, True) < 2.5 * _saves(1, 1 << 19, 256, False)
