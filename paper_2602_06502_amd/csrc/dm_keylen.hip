@@ -22,13 +22,21 @@
 //   1. the runs meet by their next key (first the depth-K prefix) in a hash
 //      table that counts them; the keys with c n >= W are the nodes, at most n,
 //      and the other runs are done with;
-//   2. each node's longest run represents it: every run of the node is compared
+//   2. one run of each node represents it: every run of the node is compared
 //      with it (a wave per run, 64 prefixes a step) and its common length counted;
 //   3. suffix sums of the lengths are the counts of every prefix along the
 //      representative, which are decided;
 //   4. runs that go on past their common length meet again by their next key
 //      there, until no node is left (a second node below a first one takes a
 //      branch that W / n requests share).
+// In the first turns a node's longest run represents it, which settles all runs
+// that are cut from one prompt at once (drawn from the second turn on, a window of
+// 1,024 chat requests took four turns instead of two).  Past kLongestTurns it is
+// drawn: the runs that go on together with a given run are those that share more
+// with it than the drawn one does, on average half, so however the branches nest
+// the turns are about the logarithm of n.  (Longest every time, a spine whose
+// longest runs part first takes a turn a run: 512 requests of 512 to 1,024 blocks
+// on 256 instances 22.5 ms instead of 0.6.)
 // What bounds it: one read of the hot runs' entries, and launches.  It replaces
 // two radix sorts (of the depth-K prefixes and of all entries under hot ones, 64
 // bits each): 131,072 requests routed and the window closed, 2.40 to 1.31 ms.
@@ -150,6 +158,7 @@ struct KlNode {
 };
 constexpr uint64_t kDone = UINT64_MAX;
 constexpr uint32_t kNoNode = UINT32_MAX;  // too few runs share the key
+constexpr uint64_t kLongestTurns = 4;
 struct KlRuns {
     const uint64_t* log;
     uint64_t m;               // record entries
@@ -158,7 +167,7 @@ struct KlRuns {
     uint32_t* depth;          // [runs] entries of the run that are settled
     uint64_t* slot;           // [runs] where its next key is; kDone
     uint64_t* key;            // [slots] 0: none
-    uint64_t* rep;            // [slots] remaining entries (24 bits, capped) | ~run (40 bits)
+    uint64_t* rep;            // [slots] rank among the runs (24 bits, from 1) | ~run (40 bits)
     uint64_t* count;          // [slots]
     uint32_t* node;           // [slots]
     uint64_t mask;            // slots - 1
@@ -166,6 +175,7 @@ struct KlRuns {
     uint64_t* hist;           // [m]
     unsigned long long* words;  // nodes, counts used, prefixes kept
     uint64_t W, n_live;
+    uint64_t turn;            // from kLongestTurns on a drawn run represents a node
 };
 
 __device__ __forceinline__ uint64_t kl_len(const KlRuns& a, uint64_t k)
@@ -206,7 +216,7 @@ __device__ __forceinline__ uint64_t kl_claim(uint64_t* tab, uint64_t mask, uint6
     }
 }
 
-// Runs meet by their next key, and the longest run of each key is found.  A
+// Runs meet by their next key, and the run that represents each key is found.  A
 // workgroup's runs meet in LDS first: thousands of runs share a popular key, and
 // atomics from all over the chip on one address take some 11 ns each
 // (131,072 runs: 421 us without this, 18 with it).
@@ -234,8 +244,10 @@ __global__ __launch_bounds__(kMeet) void kl_meet_kernel(KlRuns a)
             const uint64_t d = a.depth[k], left = kl_len(a, k) - d;
             j = (uint32_t)kl_claim(key, kSlots - 1, a.log[a.start[k] + d]);
             atomicAdd(&count[j], 1u);
-            atomicMax(&top[j], (unsigned long long)((left < 0xFFFFFFull ? left : 0xFFFFFFull) << 40 |
-                                                    (0xFFFFFFFFFFull - k)));
+            const uint64_t rank = a.turn >= kLongestTurns ? mix64(k | a.turn << 40) >> 40 | 1
+                                  : left < 0xFFFFFFull    ? left
+                                                          : 0xFFFFFFull;
+            atomicMax(&top[j], (unsigned long long)(rank << 40 | (0xFFFFFFFFFFull - k)));
         }
         __syncthreads();
         for (uint32_t q = threadIdx.x; q < kSlots; q += kMeet)
@@ -597,6 +609,7 @@ dm_status keylen_window(dm_ctx* c)
         kl_runs_kernel<<<grid_for(nw, 256, 8192), 256, 0, st>>>(k.roots, nw, wpre, R, start);
         const uint32_t gs = grid_for(meets, 256, 8192);
         auto meet = [&](bool first) {
+            a.turn = first ? 0 : a.turn + 1;
             if (first)
                 kl_clear_kernel<true><<<gs, 256, 0, st>>>(a);
             else
@@ -605,18 +618,22 @@ dm_status keylen_window(dm_ctx* c)
             kl_node_kernel<<<gs, 256, 0, st>>>(a);
         };
         meet(true);
-        // each turn settles the nodes found before it and finds those below
-        for (bool more = true; more;) {
+        // each turn settles the nodes found before it and finds those below; a
+        // wait after each of the first, then after every fourth (a turn without
+        // nodes does nothing)
+        for (uint64_t more = 1; more;) {
             kl_hist_zero_kernel<<<grid_for(parts, 1, 1024), 256, 0, st>>>(a);
             kl_common_kernel<<<grid_for(R, kCommonRuns, 32768), kCommonWaves * kWave, 0, st>>>(a);
             kl_decide_kernel<<<grid_for(parts, 1, 1024), 256, 0, st>>>(a, k.tab[k.cur], k.log2, out,
                                                                       outcap);
             meet(false);
+            if (a.turn > kLongestTurns && a.turn % 4)
+                continue;
             kl_post_kernel<<<1, 1, 0, st>>>(a.words, c->host_words);
             if ((e = hipGetLastError()) != hipSuccess ||
                 (e = hipStreamSynchronize(st)) != hipSuccess)
                 return hip_fail(c, e, "dm_keylen_window");
-            more = c->host_words[0] != 0;
+            more = c->host_words[0];
             n_next = c->host_words[1];
         }
         kl_zero_u32_kernel<<<grid_for(nw, 256, 8192), 256, 0, st>>>(k.roots, nw);

@@ -78,3 +78,80 @@ def test_branching_windows(n, n_inst, B, K, depth):
         assert np.array_equal(eng.keylen_tree(), tree)
         most = max(most, len(tree))
     assert most > 0 or n_inst == 1 or n == 1
+
+
+def _route(eng, prompts):
+    import paper_2602_06502_amd.harness as gh
+    off = np.zeros(len(prompts) + 1, np.int64)
+    off[1:] = np.cumsum([len(p) for p in prompts])
+    tok = np.concatenate(prompts).astype(np.int32)
+    return tok, off, gh.to_dev(tok, eng.device), gh.to_dev(off, eng.device)
+
+
+def _spine(rng, W, B):
+    """Run i shares i + 1 blocks with every later one; the longest part first."""
+    spine = rng.integers(0, 1000, size=(W + 1) * B, dtype=np.int32)
+    return [np.concatenate([spine[:(i + 1) * B], rng.integers(1000, 2000, size=(2 * W - 2 * i) * B, dtype=np.int32)])
+            for i in range(W)]
+
+
+@pytest.mark.parametrize("n,n_inst,K,shuffle", [(300, 200, 1, False), (301, 64, 2, True), (65, 1000, 1, True)])
+def test_nested_branches(n, n_inst, K, shuffle):
+    """A branch at every block of a spine: a node below a node, hundreds deep."""
+    import paper_2602_06502_amd.harness as gh
+    B = 4
+    wl = dataclasses.replace(workloads.small_random(17 + n, n_inst, 4, B, 64, slo_us=30_000, key_blocks=K), n_prior=0)
+    eng, o = gh.engine_for(wl), oh.oracle_for(wl)
+    eng.keylen_enable(20_000, 1 << 20)
+    assert o.keylen_enable(20_000) == oracle.OK
+    L = workloads.initial_loads(wl, wl.route.max_slots)
+    Ld = gh.to_dev(L, eng.device)
+    rng = np.random.default_rng(n)
+    prompts = _spine(rng, n, B)
+    if shuffle:
+        prompts = [prompts[i] for i in rng.permutation(n)] + prompts[:5]
+    tok, off, td, od = _route(eng, prompts)
+    for w in range(2):
+        print("[case] nested", n, n_inst, w, flush=True)
+        g = eng.route(td, od, Ld)
+        eng.keylen_window()
+        r = o.route(tok, off, L)
+        L = r["loads"]
+        assert o.keylen_window() == oracle.OK
+        assert np.array_equal(g["key_len"].cpu().numpy()[:len(r["key_len"])], r["key_len"])
+        tree = o.keylen_tree()
+        assert len(tree) > 0 and np.array_equal(eng.keylen_tree(), tree)
+
+
+def _close_us(prompts, n_inst, B=4, K=1, reps=5):
+    """Median time of closing a window of these prompts."""
+    import time
+
+    import paper_2602_06502_amd.harness as gh
+    wl = dataclasses.replace(workloads.small_random(3, n_inst, 4, B, 64, key_blocks=K), n_prior=0)
+    eng = gh.engine_for(wl)
+    _, _, td, od = _route(eng, prompts)
+    eng.keylen_enable(100_000, int(od[-1]) // B + len(prompts))
+    Ld = torch.zeros(wl.route.max_slots, dtype=torch.int64, device=eng.device)
+    t = []
+    for _ in range(reps + 1):
+        eng.route(td, od, Ld)
+        eng.sync()
+        torch.cuda.synchronize()
+        a = time.perf_counter()
+        eng.keylen_window()
+        t.append((time.perf_counter() - a) * 1e6)
+    us = sorted(t[1:])[reps // 2]
+    print("[case] close", len(prompts), n_inst, us, flush=True)
+    return us
+
+
+def test_nested_branches_cost_little():
+    """A spine of 512 branches against as many prompts that part in one place
+    (some 90 times the time with a turn for every branch)."""
+    rng = np.random.default_rng(1)
+    spine = _spine(rng, 512, 4)
+    flat = [np.concatenate([spine[0][:4], p[4:] + 2000]) for p in spine]
+    for i, p in enumerate(flat):
+        p[4:8] = 5000 + i
+    assert _close_us(spine, 256) < 12 * _close_us(flat, 256)
