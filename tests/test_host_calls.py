@@ -242,6 +242,24 @@ def test_batches_worth_two_parts(fake):
     _child(fake, "two_parts")
 
 
+def scenario_tree_walk_waves(x):
+    """The walk down the hotness tree has a wave for every request of a batch that fits the chip at once."""
+    tok = x.buf(64)
+    out = x.pk.dm_route_out(*(x.buf(64) for _ in range(8)))
+    x.fk.fake_waves.restype = C.c_uint64
+    for blocks in (1, 4, 64):
+        h = x.create(key_blocks=blocks)
+        assert x.L.dm_keylen_enable(h, 1000, 10_000) == x.pk.DM_OK
+        for n in (1, 3, 8, 64, 1000, 8192, 8193, 16_384, 100_000):
+            assert x.L.dm_route_batch(h, tok, 1000, tok, n, tok, C.byref(out)) == x.pk.DM_OK
+            waves = x.fk.fake_waves(b"extend_kernel")
+            assert waves >= min(n, 8192), (blocks, n, waves)
+
+
+def test_tree_walk_waves(fake):
+    _child(fake, "tree_walk_waves")
+
+
 def test_queue_calls_report_runtime_errors(fake):
     _child(fake, "queue_errors")
 
