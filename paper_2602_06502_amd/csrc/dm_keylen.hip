@@ -292,11 +292,17 @@ __global__ __launch_bounds__(256) void kl_hist_zero_kernel(KlRuns a)
 // Every run's entries in common with its node's representative: a wave takes
 // kAlike runs, whose first 64 entries are loaded together.  The counts meet in
 // LDS first, as above (many runs part from their representative where a shared
-// prompt ends; 131,072 runs 161 us without this, 36 with it).
-constexpr uint32_t kAlike = 8, kCommonWaves = 16, kCommonRuns = kAlike * kCommonWaves;
+// prompt ends; 131,072 runs 161 us without this, 36 with it).  A run goes on
+// alone, 64 entries a step and after kStep1 of them kAhead steps at once, and few
+// runs (kAloneTo) take a wave each, for they may be long: 64 prompts of 7,000
+// blocks 195 us with neither, 40 with both.
+constexpr uint32_t kCommonWaves = 16, kManyAlike = 8, kAhead = 8;
+constexpr uint64_t kAloneTo = 2048, kStep1 = 512;
 
+template <uint32_t kAlike>
 __global__ __launch_bounds__(kCommonWaves * kWave) void kl_common_kernel(KlRuns a)
 {
+    constexpr uint32_t kCommonRuns = kAlike * kCommonWaves;
     constexpr uint32_t kSlots = 2 * kCommonRuns;
     __shared__ uint64_t at[kSlots];  // place in hist + 1
     __shared__ uint32_t count[kSlots];
@@ -346,10 +352,25 @@ __global__ __launch_bounds__(kCommonWaves * kWave) void kl_common_kernel(KlRuns 
             uint64_t diff = ballot(x[q] != y[q]), j = 0;
             if (!diff && n > kWave) {
                 const uint64_t *m = a.log + readlane_u64(mine, q), *r = a.log + readlane_u64(rep, q);
-                for (j = kWave; j < n; j += kWave) {
+                for (j = kWave; j < n && j < kStep1; j += kWave) {
                     diff = ballot(j + lane < n && m[j + lane] != r[j + lane]);
                     if (diff)
                         break;
+                }
+                while (!diff && j < n) {
+                    uint64_t u[kAhead], v[kAhead];
+#pragma unroll
+                    for (uint32_t h = 0; h < kAhead; h++) {
+                        const uint64_t p = j + h * kWave + lane;
+                        u[h] = p < n ? m[p] : 0;
+                        v[h] = p < n ? r[p] : 0;
+                    }
+#pragma unroll
+                    for (uint32_t h = 0; h < kAhead; h++)
+                        if (!diff) {
+                            diff = ballot(u[h] != v[h]);
+                            j += diff ? 0 : kWave;
+                        }
                 }
             }
             if (diff && lane == (int)q)
@@ -371,35 +392,53 @@ __global__ __launch_bounds__(kCommonWaves * kWave) void kl_common_kernel(KlRuns 
 }
 
 // A workgroup per node: how many of its runs carry each prefix along its
-// representative (suffix sums), and the prefixes that the next tree holds:
-// extended now and c n >= W, or a leaf now and c n > 2 W.
+// representative (suffix sums, from its end up to 2,048 prefixes at a time), and
+// the prefixes that the next tree holds: extended now and c n >= W, or a leaf now
+// and c n > 2 W.
 __global__ __launch_bounds__(256) void kl_decide_kernel(KlRuns a, const uint64_t* __restrict__ tab,
                                                         uint32_t ls, uint64_t* __restrict__ out,
                                                         uint64_t cap)
 {
-    __shared__ uint64_t part[256];
+    constexpr uint32_t kMost = 8;  // prefixes of a thread at a time
+    __shared__ uint64_t part[256 / kWave];
+    const uint32_t wv = threadIdx.x >> 6;
     for (uint64_t b = blockIdx.x; b < a.words[0]; b += gridDim.x) {
         const KlNode nd = a.nodes[b];
-        const uint64_t per = (nd.len + 255) / 256, j0 = threadIdx.x * per,
-                       j1 = j0 + per < nd.len ? j0 + per : nd.len;
-        uint64_t sum = 0;
-        for (uint64_t j = j0; j < j1; j++)
-            sum += a.hist[nd.base + j];
-        __syncthreads();
-        part[threadIdx.x] = sum;
-        __syncthreads();
-        uint64_t c = 0;
-        for (uint32_t t = threadIdx.x + 1; t < 256; t++)
-            c += part[t];
-        for (uint64_t j = j1; j-- > j0;) {
-            c += a.hist[nd.base + j];
-            if (c * a.n_live < a.W)
-                continue;
-            const uint64_t key = a.log[nd.rep + j];
-            if (c * a.n_live > 2 * a.W || table_has(tab, ls, key)) {
-                const uint64_t at = atomicAdd(&a.words[2], 1ull);
-                if (at < cap)
-                    out[at] = key;
+        const uint32_t per = nd.len < 256 * kMost ? (uint32_t)((nd.len + 255) / 256) : kMost;
+        const uint64_t tile = 256 * per;
+        uint64_t after = 0;  // runs that go past the tile
+        for (uint64_t t = (nd.len + tile - 1) / tile; t-- > 0;) {
+            const uint64_t j0 = t * tile + threadIdx.x * per;
+            uint64_t h[kMost], sum = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < kMost; q++) {
+                h[q] = q < per && j0 + q < nd.len ? a.hist[nd.base + j0 + q] : 0;
+                sum += h[q];
+            }
+            const uint64_t upto = wave_incl_sum_u64(sum, lane_id());
+            if (lane_id() == kWave - 1)
+                part[wv] = upto;
+            __syncthreads();
+            uint64_t all = 0, before = upto;
+#pragma unroll
+            for (uint32_t k = 0; k < 256 / kWave; k++) {
+                all += part[k];
+                before += k < wv ? part[k] : 0;
+            }
+            __syncthreads();
+            uint64_t c = after + all - before;
+            after += all;
+#pragma unroll
+            for (uint32_t q = kMost; q-- > 0;) {
+                c += h[q];
+                if (q >= per || j0 + q >= nd.len || c * a.n_live < a.W)
+                    continue;
+                const uint64_t key = a.log[nd.rep + j0 + q];
+                if (c * a.n_live > 2 * a.W || table_has(tab, ls, key)) {
+                    const uint64_t at = atomicAdd(&a.words[2], 1ull);
+                    if (at < cap)
+                        out[at] = key;
+                }
             }
         }
     }
@@ -623,7 +662,12 @@ dm_status keylen_window(dm_ctx* c)
         // nodes does nothing)
         for (uint64_t more = 1; more;) {
             kl_hist_zero_kernel<<<grid_for(parts, 1, 1024), 256, 0, st>>>(a);
-            kl_common_kernel<<<grid_for(R, kCommonRuns, 32768), kCommonWaves * kWave, 0, st>>>(a);
+            if (R <= kAloneTo)
+                kl_common_kernel<1><<<grid_for(R, kCommonWaves, 32768), kCommonWaves * kWave, 0,
+                                      st>>>(a);
+            else
+                kl_common_kernel<kManyAlike><<<grid_for(R, kManyAlike * kCommonWaves, 32768),
+                                               kCommonWaves * kWave, 0, st>>>(a);
             kl_decide_kernel<<<grid_for(parts, 1, 1024), 256, 0, st>>>(a, k.tab[k.cur], k.log2, out,
                                                                       outcap);
             meet(false);

@@ -155,3 +155,45 @@ def test_nested_branches_cost_little():
     for i, p in enumerate(flat):
         p[4:8] = 5000 + i
     assert _close_us(spine, 256) < 12 * _close_us(flat, 256)
+
+
+@pytest.mark.parametrize("n,blocks,n_inst", [(3, 2600, 16), (2047, 70, 64), (2049, 70, 64), (40, 1300, 3), (12, 513, 8), (12, 2049, 8)])
+def test_long_runs(n, blocks, n_inst):
+    """Runs that go on past what a step compares and past what a workgroup sums at
+    a time, parting anywhere; few runs (a wave each) and many."""
+    import paper_2602_06502_amd.harness as gh
+    B = 4
+    wl = dataclasses.replace(workloads.small_random(29 + n, n_inst, 4, B, 64, slo_us=30_000, key_blocks=1), n_prior=0)
+    eng, o = gh.engine_for(wl), oh.oracle_for(wl)
+    eng.keylen_enable(50_000, 1 << 20)
+    assert o.keylen_enable(50_000) == oracle.OK
+    L = workloads.initial_loads(wl, wl.route.max_slots)
+    Ld = gh.to_dev(L, eng.device)
+    rng = np.random.default_rng(n + blocks)
+    spine = rng.integers(0, 1000, size=blocks * B, dtype=np.int32)
+    for w in range(2):
+        prompts = []
+        for i in range(n):
+            k = int(rng.integers(0, blocks + 1)) if i % 3 else blocks
+            more = int(rng.integers(0, blocks)) if i % 2 else 0
+            prompts.append(np.concatenate([spine[:k * B], rng.integers(1000, 2000, size=more, dtype=np.int32)]))
+        tok, off, td, od = _route(eng, prompts)
+        print("[case] long", n, blocks, n_inst, w, flush=True)
+        g = eng.route(td, od, Ld)
+        eng.keylen_window()
+        r = o.route(tok, off, L)
+        L = r["loads"]
+        assert o.keylen_window() == oracle.OK
+        assert np.array_equal(g["key_len"].cpu().numpy()[:len(r["key_len"])], r["key_len"])
+        tree = o.keylen_tree()
+        assert len(tree) > 0 and np.array_equal(eng.keylen_tree(), tree)
+
+
+def test_long_runs_cost_little():
+    """As many blocks in 32 prompts alike but for their ends as in 1,024 (6.7
+    times the time with 8 runs a wave and 64 blocks a step; 2.4 now, the deeper
+    tree included)."""
+    rng = np.random.default_rng(1)
+    spine = rng.integers(0, 1000, size=4 * 16_384, dtype=np.int32)
+    ends = lambda n, b: [np.concatenate([spine[:4 * (b - 1)], np.full(4, 5000 + i, np.int32)]) for i in range(n)]
+    assert _close_us(ends(32, 16_384), 8) < 4 * _close_us(ends(1024, 512), 8)
