@@ -6,8 +6,8 @@
 // slot seen during a lookup proves the key absent.
 //
 // Capacity: a table never holds more than 2^(k-1) occupied slots.  A
-// workgroup reserves a unit of the occupied count per key before its threads
-// claim empty slots and gives back what they did not use; when that is
+// workgroup reserves a unit of the occupied count per key that is not there
+// before its threads claim empty slots and gives back what they did not use; when that is
 // refused at the limit, each of its threads reserves a unit for itself before
 // a claim and gives it back if the claim loses (another thread stored the
 // same or a different key there).  A single reservation refused is not final,
@@ -86,42 +86,71 @@ __device__ __forceinline__ void insert_one(const TableRef& t, uint64_t k, uint32
 
 // Reserving per workgroup instead of per key took 32,768 keys into an empty
 // 2^17-slot table from 54 us to 8.6 us: every key met the others on the two
-// count words.
+// count words, where atomics take some 11 ns each.  So a workgroup reserves only
+// for its keys that are not there (found before the claims, which go on from
+// where the search stopped), and nothing where the host knows that there is room
+// for all (ROOM): 1,048,576 keys that are all there, whole call 150 us with a
+// reservation for each workgroup and 66 without.
+template <bool ROOM>
 __global__ __launch_bounds__(256) void insert_kernel(TableRef t, const uint64_t* __restrict__ keys,
                                                      uint64_t n, uint32_t* __restrict__ status,
                                                      Overflow ovf)
 {
     __shared__ bool room;
-    __shared__ uint32_t stored;
+    __shared__ uint32_t absent, stored;
     unsigned long long* const occupied = (unsigned long long*)t.occupied;
     for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < n;
          base += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t i = base + threadIdx.x;
         const uint64_t k = i < n ? canon_key(keys[i]) : kEmpty;
-        const unsigned long long want = std::min<uint64_t>(blockDim.x, n - base);
-        if (threadIdx.x == 0) {
-            room = atomicAdd(occupied, want) + want <= t.limit;
-            if (!room)
-                atomicAdd(occupied, 0ull - want);  // give back
-            stored = 0;
-        }
+        if (threadIdx.x == 0)
+            absent = stored = 0;
         __syncthreads();
-        const bool grouped = room;
+        PutAt at{home_bucket(k, t.log2slots), 0, 0};
+        Put p = i < n ? find_key(t.slots, t.log2slots, k, at) : Put::kThere;
+        // a key that many lanes hold is left to one of them (whole wavefronts of one
+        // key would meet on its slot: 65,536 copies 782 us instead of 50)
+        uint64_t left = ballot(p != Put::kThere);
+#pragma unroll
+        for (int r = 0; r < 4 && left; r++) {
+            const int lead = __builtin_ctzll(left);
+            const uint64_t same = ballot(k == readlane_u64(k, lead)) & left;
+            if ((same >> lane_id()) & 1 && lane_id() != lead)
+                p = Put::kThere;
+            left &= ~same;
+        }
+        const uint64_t m = ballot(p != Put::kThere);
+        if (lane_id() == 0 && m)
+            atomicAdd(&absent, (uint32_t)__popcll(m));
+        __syncthreads();
+        const unsigned long long want = absent;
+        if (want == 0)
+            continue;
+        if (!ROOM) {
+            if (threadIdx.x == 0) {
+                room = atomicAdd(occupied, want) + want <= t.limit;
+                if (!room)
+                    atomicAdd(occupied, 0ull - want);  // give back
+            }
+            __syncthreads();
+        }
+        const bool grouped = ROOM || room;
         if (grouped) {
-            const Put p = i < n ? put_key(t.slots, t.log2slots, k) : Put::kThere;
+            if (p == Put::kStored)
+                p = claim_key(t.slots, t.log2slots, k, at);
             if (p == Put::kNoRoom)
                 atomicOr(status, kErrFull);
-            const uint64_t m = ballot(p == Put::kStored);
-            if (lane_id() == 0 && m)
-                atomicAdd(&stored, (uint32_t)__popcll(m));
-        } else if (i < n) {
-            insert_one(t, k, status, ovf.count ? &ovf : nullptr);
+            const uint64_t s = ballot(p == Put::kStored);
+            if (lane_id() == 0 && s)
+                atomicAdd(&stored, (uint32_t)__popcll(s));
+        } else if (p != Put::kThere) {
+            insert_one(t, k, status, &ovf);
         }
         __syncthreads();
         if (grouped && threadIdx.x == 0) {
-            const unsigned long long kept = stored;
-            if (kept != want)
-                atomicAdd(occupied, kept - want);  // give back
+            const unsigned long long kept = stored, held = ROOM ? 0 : want;
+            if (kept != held)
+                atomicAdd(occupied, kept - held);  // give back, or add
             if (kept)
                 atomicAdd((unsigned long long*)t.live, kept);
         }
@@ -337,8 +366,8 @@ hipError_t index_insert(dm_ctx* c, uint32_t id, const uint64_t* keys, uint64_t n
     // nor an overflow list can be needed) instead of six.
     if (surely_fits(c, id, n)) {
         if (n)
-            insert_kernel<<<grid_for(n, 256), 256, 0, c->stream>>>(t, keys, n, c->d_status,
-                                                                   Overflow{nullptr, nullptr});
+            insert_kernel<true><<<grid_for(n, 256), 256, 0, c->stream>>>(
+                t, keys, n, c->d_status, Overflow{nullptr, nullptr});
         return hipGetLastError();
     }
     hipError_t e = hipSuccess;
@@ -356,7 +385,7 @@ hipError_t index_insert(dm_ctx* c, uint32_t id, const uint64_t* keys, uint64_t n
     purge_clear_kernel<<<grid_for(nslots, 256, 4096), 256, 0, c->stream>>>(t, w);
     purge_insert_kernel<<<grid_for(t.limit, 256, 4096), 256, 0, c->stream>>>(t, w, gathered,
                                                                             c->d_status);
-    insert_kernel<<<grid_for(n, 256), 256, 0, c->stream>>>(t, keys, n, c->d_status, ovf);
+    insert_kernel<false><<<grid_for(n, 256), 256, 0, c->stream>>>(t, keys, n, c->d_status, ovf);
     overflow_kernel<<<1, kWave, 0, c->stream>>>(t, ovf, c->d_status);
     return hipGetLastError();
 }

@@ -621,17 +621,37 @@ __device__ __forceinline__ BucketView bucket_view(const uint64_t* line64, uint64
 // there; every slot scanned otherwise.
 enum class Put { kStored, kThere, kNoRoom };
 
-__device__ __forceinline__ Put put_key(uint64_t* slots, uint32_t log2slots, uint64_t k)
+// Where the walk along a key's sequence stands.
+struct PutAt {
+    uint64_t b, step;  // bucket, buckets gone past
+    uint32_t empty;    // its empty slots
+};
+
+// Up to the first bucket that holds k (kThere) or has an empty slot (kStored:
+// k is not there yet).
+__device__ __forceinline__ Put find_key(const uint64_t* slots, uint32_t log2slots, uint64_t k,
+                                        PutAt& at)
 {
     const uint64_t nbk = 1ull << (log2slots - 3);
-    uint64_t b = home_bucket(k, log2slots);
-    for (uint64_t step = 0; step < nbk; step++, b = (b + 1) & (nbk - 1)) {
-        uint64_t* line = slots + b * kBucket;
-        const BucketView v = bucket_view(line, k);
+    for (; at.step < nbk; at.step++, at.b = (at.b + 1) & (nbk - 1)) {
+        const BucketView v = bucket_view(slots + at.b * kBucket, k);
         if (v.hit)
             return Put::kThere;
+        at.empty = v.empty;
+        if (v.empty)
+            return Put::kStored;
+    }
+    return Put::kNoRoom;
+}
+
+// Claims a slot for k from where find_key stopped.
+__device__ __forceinline__ Put claim_key(uint64_t* slots, uint32_t log2slots, uint64_t k, PutAt at)
+{
+    const uint64_t nbk = 1ull << (log2slots - 3);
+    for (;;) {
+        uint64_t* line = slots + at.b * kBucket;
         // from the first empty slot on: others may have taken slots since
-        for (uint32_t q = v.empty ? __builtin_ctz(v.empty) : kBucket; q < kBucket; q++) {
+        for (uint32_t q = __builtin_ctz(at.empty); q < kBucket; q++) {
             const unsigned long long prev = atomicCAS((unsigned long long*)(line + q),
                                                       (unsigned long long)kEmpty,
                                                       (unsigned long long)k);
@@ -640,8 +660,19 @@ __device__ __forceinline__ Put put_key(uint64_t* slots, uint32_t log2slots, uint
             if (prev == k)
                 return Put::kThere;
         }
+        at.step++;
+        at.b = (at.b + 1) & (nbk - 1);
+        const Put p = find_key(slots, log2slots, k, at);
+        if (p != Put::kStored)
+            return p;
     }
-    return Put::kNoRoom;
+}
+
+__device__ __forceinline__ Put put_key(uint64_t* slots, uint32_t log2slots, uint64_t k)
+{
+    PutAt at{home_bucket(k, log2slots), 0, 0};
+    const Put p = find_key(slots, log2slots, k, at);
+    return p == Put::kStored ? claim_key(slots, log2slots, k, at) : p;
 }
 
 // Canonical key k erased; true if this thread did it.

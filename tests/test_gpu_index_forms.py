@@ -91,3 +91,48 @@ def test_rebuild_after_erases_and_clear():
             eng.sync()
     every = np.unique(keys)
     assert set(every[_held(eng, 0, every)].tolist()) == live
+
+
+@pytest.mark.parametrize("log2,n", [(4, 3), (10, 200), (12, 1100), (17, 40_000)])
+def test_keys_already_there(log2, n):
+    """Batches of keys that are there, new ones or both, while the host still
+    knows that they fit (first) and once it no longer does, up to the limit."""
+    eng, pk = _engine(log2)
+    rng = np.random.default_rng(n)
+    limit = 1 << (log2 - 1)
+    keys = rng.integers(2, 2**63, size=limit + 1, dtype=np.uint64)
+    have = 0
+    for upto in (n, n, n + 1, n + 1, limit, limit):
+        for rep in range(3):
+            part = keys[:upto][rng.permutation(upto)]
+            eng.index_insert(1, _dev(part))
+            have = max(have, upto)
+            eng.sync()
+            assert eng.index_size(1) == have
+    eng.index_insert(1, _dev(keys))
+    with pytest.raises(pk.DMError) as ei:
+        eng.sync()
+    assert ei.value.status == pk.DM_EFULL and eng.index_size(1) == limit
+    assert _held(eng, 1, keys)[:limit].all()
+
+
+def test_keys_already_there_cost_little():
+    """4 Mi keys that are all there against 1,024 (8 times the time with a
+    reservation on the table's count for every workgroup; reading their buckets
+    takes twice)."""
+    import time
+    eng, _ = _engine(24)
+    us = {}
+    for n in (1 << 10, 1 << 22):
+        k = torch.randint(2, 2**63 - 1, (n,), dtype=torch.int64, device="cuda:0").view(torch.uint64)
+        eng.index_insert(2, k)
+        t = []
+        for _ in range(12):
+            eng.sync()
+            a = time.perf_counter()
+            eng.index_insert(2, k)
+            eng.sync()
+            t.append((time.perf_counter() - a) * 1e6)
+        us[n] = sorted(t[4:])[4]
+    print("[case] there", us, flush=True)
+    assert us[1 << 22] < 5 * us[1 << 10], us
