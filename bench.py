@@ -425,8 +425,7 @@ def policy_rows(eng, wl, st, L0):
                     "hit_rate: cached prompt tokens on the chosen instances / prompt tokens; "
                     "final_load_cv: std / mean of the live instances' queued work after the "
                     "batch; fewer_blocks_frac: requests sent to the candidate with fewer cached "
-                    "blocks; min_ttft takes the serial selection path; ms: host wall time of "
-                    "the call and its sync")
+                    "blocks; ms: host wall time of the call and its sync")
     return rows
 
 
@@ -492,8 +491,8 @@ def adaptive_leg(eng, wl, st, L0, base_out, base_loads, reps=3):
             "note": "each window is one route of the whole batch from the same loads, closed "
                     "after it; route_ms: unpipelined dm_route_batch with the settled tree (the "
                     "window record of every prefix of depth >= K included), host wall clock; "
-                    "window_close_ms: dm_keylen_window (sort and count of the record, tree "
-                    "rebuild); fixed_K: the timed steps' route"}
+                    "window_close_ms: dm_keylen_window (prefixes counted along representative "
+                    "requests, tree rebuild); fixed_K: the timed steps' route"}
 
 
 def elastic_leg(eng, wl, st, keys, L0, reps):
@@ -751,20 +750,26 @@ def main():
         "select_bound": {"kernel": "select_walk_kernel", "bound": "latency",
                          "depth_steps": depth_steps, "windows": walk_windows,
                          "depth_steps_without_runs": depth_steps_no_runs,
-                         "ns_per_step": ref_stage[2] * 1e6 / depth_steps,
+                         "ns_per_step": ms_step * 1e6 / depth_steps,
                          "note": "one wave walks windows of up to 2 x 64 requests (one lane "
                                  "set for even depths, one for odd) packed from the "
                                  "dependency levels of 2048-request blocks, runs of up to three "
                                  "same-pair requests sharing a level; each step is an LDS "
                                  "round trip plus the run replay and the decision; time from "
-                                 "the unpipelined stage (record packing and levels included)"},
+                                 "the timed steps, whose walks follow one another (window "
+                                 "changes and the gaps between walks included)"},
         "unpipelined": {"ms_per_step": ms_ref, "requests_per_s": n / (ms_ref * 1e-3),
                         "steps": n_ref,
                         "stage_ms": {"keys_groups": ref_stage[0], "hash_match": ref_stage[1],
-                                     "select": ref_stage[2], "block_offsets": ref_stage[3]}},
+                                     "select": ref_stage[2], "block_offsets": ref_stage[3],
+                                     "note": "a call of more than 65,536 requests and 200 M "
+                                             "tokens is selected in two parts: hash_match "
+                                             "holds the first quarter's packing as well, its "
+                                             "walk runs beside the rest of hash_match, and "
+                                             "select is what follows"}},
         "roofline": {"bound": "hbm",
-                     "kernel": "hash+match stage: ring_key_kernel<16>, lookup_kernel, "
-                               "radix sort passes, group_head_kernel, "
+                     "kernel": "hash+match stage: ring_key_kernel<16>, "
+                               "radix sort passes, group_count_kernel, "
                                "group scan, group_leader_kernel, "
                                "walk_kernel<16> (leaders, resume), member_record_kernel, "
                                "member_kernel<16>, probe_pending_kernel",

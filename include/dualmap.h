@@ -172,7 +172,8 @@ typedef struct {
  * loads: device int64 [max_slots], read and updated in place.  Requires
  * rings (DM_ESTATE otherwise).  The call does not wait for the device: its
  * work arrays are sized from n and n_tokens (they grow, synchronising once,
- * only when a batch needs more than any before it).  n = 0 is a no-op; n must be at most
+ * only when a batch has more requests or tokens than any before it).  n = 0 is a
+ * no-op; n must be at most
  * 1,041,203,200 (DM_EINVAL): the selection indexes its per-request slots in
  * 32 bits.  Match lengths are 32-bit: a request with 2^32 or more full
  * blocks sets the device status word (DM_EINVAL from dm_sync). */
@@ -187,8 +188,9 @@ dm_status dm_route_batch(dm_ctx* ctx, const int32_t* tokens, uint64_t n_tokens,
  * static area of 64 MiB per GPU that the library holds until the process
  * ends, instead of the context's growable scratch: the call allocates and
  * frees nothing.  The batch is planned on the host first; if its work
- * arrays do not fit (about 550 bytes per request plus, when block_keys is
- * NULL, 8 bytes per n_tokens / B), the call returns DM_EINVAL with the
+ * arrays do not fit (about 600 bytes per request, 1,100 in batches of at most
+ * 4,096, plus, when block_keys is NULL, 8 bytes per n_tokens / B), the call
+ * returns DM_EINVAL with the
  * sizes in dm_last_error and launches nothing.  Runs unpipelined on the
  * context's stream (after any pipelined batch).  Every call on one GPU
  * shares that GPU's area: calls that overlap on one GPU (other contexts,
@@ -332,7 +334,11 @@ dm_status dm_scale(dm_ctx* ctx, const uint32_t* add, uint32_t n_add, const uint3
  * then every other request), [2] record packing and in-order selection
  * (with pipelining: from the end of the batch's stage [1] to the end of its
  * selection, so it includes waiting for the previous batch's selection),
- * [3] per-request block offsets and the offsets check.
+ * [3] per-request block offsets and the offsets check.  Without pipelining a
+ * call of more than 65,536 requests and at least 200 M tokens is selected in
+ * two parts: [1] then contains the first part's record packing as well, the
+ * first part's selection runs beside the rest of [1], and [2] is the second
+ * part's, with what is left of the first one's.
  * dm_route_stage_ms returns DM_ESTATE if timing is off or no batch was
  * timed. */
 dm_status dm_set_timing(dm_ctx* ctx, int on);
@@ -416,9 +422,8 @@ dm_status dm_keylen_export(dm_ctx* ctx, uint64_t* keys_host, uint64_t cap, uint6
  * dm_rebalance calls.  Every rule updates the loads in request order as the
  * SLO-aware one does; flag bit0 marks a chosen candidate with fewer cached
  * blocks than the other (under the SLO-aware rule exactly its switches for
- * the SLO).  The minimum-TTFT rule always takes the one-request-at-a-time
- * selection path.  Applies to batches routed after the call; DM_EINVAL for
- * an unknown rule. */
+ * the SLO).  Applies to batches routed after the call; DM_EINVAL for an
+ * unknown rule. */
 typedef enum {
     DM_POLICY_SLO_AWARE = 0,
     DM_POLICY_CACHE_AFFINITY = 1,

@@ -47,13 +47,15 @@ constexpr uint32_t kLeaderBlocks = 2048;    // resume walk: at most 8,192 waves
 constexpr uint32_t kLeaderGrid = 8192;      // leaders: up to 32,768 waves, one leader each
 
 enum : int { kLeaders = 1, kResume = 2 };
-// most requests of a members pass in one launch (member_probe_kernel); at
-// 131,072 the one launch and the four take the same time
+// most requests of a members pass in one launch (member_probe_kernel); past it
+// the four launches and the one meet: 65,537 requests on 128 instances 619 and 615
+// us (short prompts), 658 and 636 (long ones), 100,000 840 and 841, 892 and 866,
+// 131,072 1,048 and 1,061, 1,108 and 1,077
 constexpr uint64_t kInlineTo = 1u << 16;
 // Most requests of one wave of the tree walk: an empty wave costs more than one
 // of four requests takes, but one after the other they take four times as long,
 // so a batch that leaves waves idle (up to kExtendFrom requests) goes one a wave:
-// 8 prompts of 7,000 blocks 251 us by fours, 75 by ones.
+// 8 prompts of 7,000 blocks 251 us by fours, 72 by ones.
 constexpr uint32_t kExtend = 4;
 constexpr uint64_t kExtendFrom = 8192;
 constexpr uint64_t kPendKeys = 8;  // keys kept per request for the pending probes

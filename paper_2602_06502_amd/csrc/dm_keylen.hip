@@ -295,7 +295,7 @@ __global__ __launch_bounds__(256) void kl_hist_zero_kernel(KlRuns a)
 // prompt ends; 131,072 runs 161 us without this, 36 with it).  A run goes on
 // alone, 64 entries a step and after kStep1 of them kAhead steps at once, and few
 // runs (kAloneTo) take a wave each, for they may be long: 64 prompts of 7,000
-// blocks 195 us with neither, 40 with both.
+// blocks 195 us with neither, 44 with both.
 constexpr uint32_t kCommonWaves = 16, kManyAlike = 8, kAhead = 8;
 constexpr uint64_t kAloneTo = 2048, kStep1 = 512;
 

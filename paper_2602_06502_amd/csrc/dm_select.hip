@@ -351,6 +351,12 @@ __global__ __launch_bounds__(256) void sel_prep_kernel(
 // the two meet.  Blocks of 64 for at most kTinyTo: 1,024 requests 106 us with
 // blocks of 256, 92 with 128, 83 with 64; 4,096 chat requests 236, 223 and 224;
 // at 16,384 the three meet, and 65,536 on 512 instances take 561, 595 and 598.
+// Just past both lines the smaller blocks would still be ahead, by little: 256
+// against 64 on 32 instances, 4,097 chat requests 203 and 194 us, 6,000 231 and
+// 225, 8,192 260 and 259, 12,000 315 and 318 (short prompts 206 and 191, 235 and
+// 225, 275 and 266, 342 and 334); 1024 against 256 on 128 instances, 65,537
+// requests 658 and 629, 80,000 755 and 734, 100,000 892 and 865, 131,072 1,108 and
+// 1,089 (short prompts 619 and 591, 712 and 687, 840 and 826, 1,048 and 1,048).
 // Pipelined, the kernel runs beside the previous walk, which is what the
 // batches wait for.
 template <uint32_t LB>
