@@ -225,3 +225,33 @@ def test_an_old_entry_costs_little():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     assert _saves(1, 1 << 19, 256, True) < 2.5 * _saves(1, 1 << 19, 256, False)
+
+
+@pytest.mark.parametrize("cap", [0, 3000])
+def test_requests_in_parts(cap):
+    """Requests around the number of blocks that one wave touches (512) and its
+    multiples, among short ones, with keys that they share."""
+    import paper_2602_06502_amd as pk
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    S, B = 3, 16
+    cfg = dict(workloads.small_random(5, S, 2, B, 10).route.as_dict(), max_slots=S, index_log2_slots=16)
+    eng = pk.DualMap(cfg, device="cuda:0")
+    eng.build_rings(range(S))
+    rng = np.random.default_rng(cap + 1)
+    pool = rng.integers(2, 2**63, size=9000, dtype=np.uint64)
+    model, clock = {}, 0
+    for i in range(3):
+        f = np.array([511, 512, 513, 0, 1, 1023, 1024, 1025, 1535, 1536, 1537, 3, 2600], np.int64)[rng.permutation(13)]
+        off = np.zeros(14, np.int64)
+        off[1:] = np.cumsum(f) * B
+        keys = np.concatenate([pool[int(rng.integers(0, 6000)):][:k] for k in f])
+        inst = rng.integers(0, S, size=13).astype(np.uint32)
+        print("[case] parts", cap, i, f.tolist(), flush=True)
+        got = eng.kv_save(_dev(off), _dev(keys), _dev(inst), clock, cap)
+        eng.sync()
+        assert got == _save(model, off, keys, inst, clock, cap, B), i
+        for c in range(S):
+            held = _held(eng, c, pool)
+            assert set(pool[held].tolist()) == set(model.get(c, {})), (i, c)
+        clock += len(keys)
