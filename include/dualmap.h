@@ -172,8 +172,7 @@ typedef struct {
  * loads: device int64 [max_slots], read and updated in place.  Requires
  * rings (DM_ESTATE otherwise).  The call does not wait for the device: its
  * work arrays are sized from n and n_tokens (they grow, synchronising once,
- * only when a batch has more requests or tokens than any before it).  n = 0 is a
- * no-op; n must be at most
+ * only when a batch needs more than any before it).  n = 0 is a no-op; n must be at most
  * 1,041,203,200 (DM_EINVAL): the selection indexes its per-request slots in
  * 32 bits.  Match lengths are 32-bit: a request with 2^32 or more full
  * blocks sets the device status word (DM_EINVAL from dm_sync). */

